@@ -346,9 +346,9 @@ int mbf_write_field(mbf_handle* h, int field_id, const void* src, int mem_kind);
  *     fill the device and exceed its caches (a batch of 320^3 realizations),
  *     slower on small ones.
  *   MBF_VARIANT_FUSED: rows a1-a5 in one z-marching kernel in which every
- *     wave owns a row and forms again the few H^{n+1/2} values of the
- *     neighbouring row, column and plane that it needs (waves exchange no
- *     field values).
+ *     wave owns a tile of 16 x 4 columns and forms again the few H^{n+1/2}
+ *     values of the neighbouring row, column and plane that it needs (waves
+ *     exchange no field values); a workgroup is tile_y such tiles.
  *   MBF_VARIANT_FUSED_LDS: rows a1-a5 in one z-marching kernel whose waves
  *     advance plane by plane together (one barrier per plane) and hand the
  *     H^{n+1/2} of their rows to the neighbouring row's E update through
@@ -402,9 +402,9 @@ int mbf_autotune(mbf_handle* h, int budget_ms, mbf_tuning* chosen);
 /* Queue nsteps steps without graph capture, bracketing the field kernels of
  * every step with HIP events on the handle's stream.  On return
  * (synchronised) kernel_ms[0] holds the summed duration of the first field
- * kernel (the fused step kernel, or the Faraday pass of the two-pass variant)
- * and kernel_ms[1] that of the second (the Ampere/Bloch pass; 0 for the
- * fused variant); *launches is the number of steps.  Used to time the kernels
+ * kernel (the single-pass step kernel, or the Faraday pass) and kernel_ms[1]
+ * that of the second (the Ampere/Bloch pass; 0 where one kernel runs the
+ * step); *launches is the number of steps.  Used to time the kernels
  * against their roofline. */
 int mbf_step_timed(mbf_handle* h, int64_t nsteps, double* kernel_ms /* [2] */, int64_t* launches);
 
@@ -414,8 +414,8 @@ int mbf_step_timed(mbf_handle* h, int64_t nsteps, double* kernel_ms /* [2] */, i
  * P^{n-1} read, P^{n+1} written, N1..N3 read and written (9 values).  A value
  * is 4 B in FP32 and 8 B in FP64, so a cell whose three E-sites carry gain
  * costs 157 B in FP32.  bytes[1] and bytes[2]: the same count for the first
- * and second field kernel of the current variant (the two-pass variant reads
- * H^{n+1/2} and the material byte in both passes).  From the current
+ * and second field kernel of the current schedule (two passes read H^{n+1/2}
+ * and the material byte in both; one kernel: bytes[1] = bytes[0]).  From the current
  * material map. */
 int mbf_step_bytes(const mbf_handle* h, double* bytes /* [3] */);
 

@@ -54,13 +54,14 @@ struct mbf_handle {
     size_t esz = 4;
     void* pool = nullptr;     // E and H
     void* gpool = nullptr;    // compact Bloch state
-    void* arr[27] = {};       // E_a[3] E_b[3] H_a[3] H_b[3] | P_a[3] P_b[3] N1[3] N2[3] N3[3] (compact)
+    void* arr[27] = {};       // E_a[3] E_b[3] H_a[3] H_b[3] | P_a[3] P_b[3] N1[3] N2[3] N3[3] (compact: the first entry's component, stride 3)
     int64_t ngain = 0;        // gain cells
     int64_t glen = 0;         // allocated length of each compact array
     uint32_t* seg_base = nullptr;   // gain cells before each 64-wide x segment of a row
     int nbx = 0;              // segments per row
+    uint32_t* seg16 = nullptr;      // the same count before each 16-wide segment
     uint8_t* mat = nullptr;
-    void* lut = nullptr;      // inv_eps[256], eps[256], mur[256] in the field type
+    void* lut = nullptr;      // inv_eps[256], eps[256], mur[256], (eps, inv_eps)[256] in the field type
     mbf::Ctl* ctl = nullptr;
     double* e_part = nullptr;
     double* l_part = nullptr;
@@ -102,7 +103,6 @@ struct mbf_handle {
     uint64_t version = 0;     // bumped whenever the device view of the handle changes
     void* tap = nullptr;      // trajectory recording buffer of the adjoint (nullptr: off)
     int64_t tap_stride = 0;   // values per trajectory slot
-    int64_t tap_base = 0;     // host copy of ctl->tap_base
     // device copy of the view, geometry and work table the step kernels read
     void* d_view = nullptr;
     mbf::Geom* d_geom = nullptr;
@@ -278,15 +278,14 @@ mbf::SimView<T> view(mbf_handle* h) {
         v.E[1][c] = A<T>(h, 3 + c);
         v.H[0][c] = A<T>(h, 6 + c);
         v.H[1][c] = A<T>(h, 9 + c);
-        v.P[0][c] = A<T>(h, 12 + c);
-        v.P[1][c] = A<T>(h, 15 + c);
-        v.N[0][c] = A<T>(h, 18 + c);
-        v.N[1][c] = A<T>(h, 21 + c);
-        v.N[2][c] = A<T>(h, 24 + c);
+        v.N[c] = A<T>(h, 18 + 3 * c);
     }
+    v.P[0] = A<T>(h, 12);
+    v.P[1] = A<T>(h, 15);
     const T* lut = reinterpret_cast<const T*>(h->lut);
     v.seg_base = h->seg_base;
     v.nbx = h->nbx;
+    v.seg16 = h->seg16;
     v.tap = reinterpret_cast<T*>(h->tap);
     v.tap_stride = h->tap_stride;
     v.tap_e = h->nsite;
@@ -295,6 +294,7 @@ mbf::SimView<T> view(mbf_handle* h) {
     v.lut_inv_eps = lut;
     v.lut_eps = lut + mbf::kMaxMat;
     v.lut_mur = lut + 2 * mbf::kMaxMat;
+    v.lut_pair = lut + 3 * mbf::kMaxMat;
     v.nx = h->cfg.nx;
     v.ny = h->cfg.ny;
     v.nz = h->cfg.nz;
@@ -356,28 +356,48 @@ mbf::SimView<T> view(mbf_handle* h) {
 int default_zseg(const mbf_tuning& t) {
     return t.variant == MBF_VARIANT_TWO_PASS_SPLIT ? 2 : (t.variant == MBF_VARIANT_FUSED_LDS ? 8 : 4);
 }
-bool single_pass(int variant) {
-    return variant == MBF_VARIANT_FUSED || variant == MBF_VARIANT_FUSED_LDS || variant == MBF_VARIANT_FUSED_PERSISTENT;
-}
 int step_zseg(const mbf_handle* h, const mbf_tuning& t) {
     return t.zseg > 0 ? std::min(t.zseg, h->cfg.nz) : std::min(default_zseg(t), h->cfg.nz);
 }
 int step_zseg(const mbf_handle* h) { return step_zseg(h, h->tun); }
 
+// Device bytes a step of the handle touches: both buffers of E and H, the
+// Bloch state and the material.
+double state_bytes(const mbf_handle* h) {
+    return (double)h->nsite * (12.0 * h->esz + 1.0) + 15.0 * (double)h->glen * h->esz;
+}
+
+// Whether a launch under schedule t runs the tile kernel (one pass).
+bool tile_schedule(const mbf_tuning& t, double bytes) {
+    (void)bytes;
+    return t.variant == MBF_VARIANT_FUSED || t.variant == MBF_VARIANT_FUSED_PERSISTENT;
+}
+bool uses_tiles(const mbf_handle* h) { return tile_schedule(h->tun, state_bytes(h)); }
+
 // Work-item geometry of a handle's grid under schedule t (a batch steps its
-// members under the batch's schedule, whatever the members' own).
-mbf::Geom step_geom(const mbf_handle* h, const mbf_tuning& t) {
+// members under the batch's schedule, whatever the members' own): blocks of
+// 64 x tile_y columns, or the tile kernel's 16 x 4 tiles, tile_y a workgroup.
+mbf::Geom step_geom(const mbf_handle* h, const mbf_tuning& t, bool tiles) {
     mbf::Geom g{};
     const int ty = t.tile_y;
-    g.tiles_x = (h->cfg.nx + 63) / 64;
-    g.tiles_y = (h->cfg.ny + ty - 1) / ty;
+    g.tiles_x = tiles ? (h->cfg.nx + 15) / 16 : (h->cfg.nx + 63) / 64;
+    g.tiles_y = tiles ? (h->cfg.ny + 3) / 4 : (h->cfg.ny + ty - 1) / ty;
     g.zseg = step_zseg(h, t);
     g.segs = (h->cfg.nz + g.zseg - 1) / g.zseg;
-    g.nblk = g.tiles_x * g.tiles_y * g.segs;
+    g.per_seg = tiles ? (g.tiles_x * g.tiles_y + ty - 1) / ty : g.tiles_x * g.tiles_y;
+    g.nblk = g.per_seg * g.segs;
     g.xcd_remap = t.xcd_remap;
     return g;
 }
-mbf::Geom step_geom(const mbf_handle* h) { return step_geom(h, h->tun); }
+
+// Energy partials of a step: one per 16 x 4 tile (16 x 2 for workgroups of two
+// rows) and segment.
+int step_parts(const mbf_handle* h, const mbf_tuning& t, bool tiles) {
+    const int rb = !tiles && t.tile_y == 2 ? 2 : 4;
+    const int zs = step_zseg(h, t);
+    return (h->cfg.nx + 15) / 16 * ((h->cfg.ny + rb - 1) / rb) * ((h->cfg.nz + zs - 1) / zs);
+}
+mbf::Geom step_geom(const mbf_handle* h) { return step_geom(h, h->tun, uses_tiles(h)); }
 
 // Reorder the work-table entries [i0, i1) (member by member, items in order)
 // into dispatch order.  remap 0: as they are; 1: XCD x takes the x-th
@@ -399,7 +419,7 @@ void dispatch_order(std::vector<uint32_t>& items, int i0, int i1, const std::vec
         int layer = 0;
         for (int e = 0; e < n;) {
             const int r = (int)(src[(size_t)e] >> 24);
-            const int Q = geoms[(size_t)r].tiles_x * geoms[(size_t)r].tiles_y;
+            const int Q = geoms[(size_t)r].per_seg;
             const int len = std::min(Q, n - e);
             for (int t = 0; t < len; ++t) queue[(size_t)(layer & 7)].push_back(src[(size_t)(e + t)]);
             e += len;
@@ -451,14 +471,14 @@ hipError_t launch_two_pass(hipStream_t st, int ty, const mbf::SimView<T>* vw, co
 // the device holds at once (occupancy x compute units, asked once per device
 // and tile height), a multiple of 8 so that every one of the eight queues
 // has workgroups, and no more than the items need.
-template <typename T, int TY>
+template <typename T, int TY, bool LAY>
 int persist_grid(int ni) {
     static int per_dev[64] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
     if (per_dev[dev] == 0) {
         int nb = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)mbf::k_step_fused_persist<T, TY>,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)mbf::k_step_fused_persist<T, TY, LAY>,
                                                          64 * TY, 0) != hipSuccess || nb < 1)
             nb = 1;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
@@ -469,52 +489,44 @@ int persist_grid(int ni) {
     return std::max(8, std::min(per_dev[dev], need) / 8 * 8);
 }
 
-// The field kernels of one step (both passes, or the fused pass) over the
+// The single-pass kernels at NW (waves per workgroup, or rows of a tile).
+template <typename T, int NW, bool LAY>
+void launch_one_pass(hipStream_t st, int variant, const mbf::SimView<T>* vw, const mbf::Geom* gw, const uint32_t* it,
+                     int ni, int rm, uint32_t* queue) {
+    const dim3 g((unsigned)ni), b(64, NW);
+    if (variant == MBF_VARIANT_FUSED_PERSISTENT)
+        hipLaunchKernelGGL((mbf::k_step_fused_persist<T, NW, LAY>), dim3((unsigned)persist_grid<T, NW, LAY>(ni)), b, 0,
+                           st, vw, gw, it, ni, queue);
+    else if (variant == MBF_VARIANT_FUSED_LDS)
+        hipLaunchKernelGGL((mbf::k_step_lds_batch<T, NW>), g, b, 0, st, vw, gw, it, ni, rm);
+    else
+        hipLaunchKernelGGL((mbf::k_step_fused_batch<T, NW, LAY>), g, b, 0, st, vw, gw, it, ni, rm);
+}
+
+// The field kernels of one step (both passes, or the single pass) over the
 // work table it[0..ni) of the views vw and geometries gw; evm (optional) is
 // recorded between the two passes; queue holds the persistent variant's
-// counters (zero between launches).
+// counters (zero between launches); lay: some member has an absorbing layer;
+// tiles: the table is the tile kernel's.
 template <typename T>
-hipError_t launch_fields(hipStream_t st, const mbf_tuning& tun, const mbf::SimView<T>* vw,
-                         const mbf::Geom* gw, const uint32_t* it, int ni, hipEvent_t evm, uint32_t* queue) {
-    const int rm = tun.xcd_remap;
-    const dim3 g((unsigned)ni);
-    hipError_t e = hipSuccess;
-    if (tun.variant == MBF_VARIANT_FUSED_PERSISTENT) {
-        if (!queue) return hipErrorInvalidValue;
-        switch (tun.tile_y) {
-            case 2: hipLaunchKernelGGL((mbf::k_step_fused_persist<T, 2>), dim3((unsigned)persist_grid<T, 2>(ni)),
-                                       dim3(64, 2), 0, st, vw, gw, it, ni, queue); break;
-            case 4: hipLaunchKernelGGL((mbf::k_step_fused_persist<T, 4>), dim3((unsigned)persist_grid<T, 4>(ni)),
-                                       dim3(64, 4), 0, st, vw, gw, it, ni, queue); break;
-            case 16: hipLaunchKernelGGL((mbf::k_step_fused_persist<T, 16>), dim3((unsigned)persist_grid<T, 16>(ni)),
-                                        dim3(64, 16), 0, st, vw, gw, it, ni, queue); break;
-            default: hipLaunchKernelGGL((mbf::k_step_fused_persist<T, 8>), dim3((unsigned)persist_grid<T, 8>(ni)),
-                                        dim3(64, 8), 0, st, vw, gw, it, ni, queue); break;
+hipError_t launch_fields(hipStream_t st, const mbf_tuning& tun, const mbf::SimView<T>* vw, const mbf::Geom* gw,
+                         const uint32_t* it, int ni, hipEvent_t evm, uint32_t* queue, bool lay, bool tiles) {
+    const int rm = tun.xcd_remap, var = tun.variant;
+    if (tiles || var == MBF_VARIANT_FUSED_LDS) {
+        if (var == MBF_VARIANT_FUSED_PERSISTENT && !queue) return hipErrorInvalidValue;
+        switch (tun.tile_y * 2 + (lay ? 1 : 0)) {
+            case 4: launch_one_pass<T, 2, false>(st, var, vw, gw, it, ni, rm, queue); break;
+            case 5: launch_one_pass<T, 2, true>(st, var, vw, gw, it, ni, rm, queue); break;
+            case 8: launch_one_pass<T, 4, false>(st, var, vw, gw, it, ni, rm, queue); break;
+            case 9: launch_one_pass<T, 4, true>(st, var, vw, gw, it, ni, rm, queue); break;
+            case 32: launch_one_pass<T, 16, false>(st, var, vw, gw, it, ni, rm, queue); break;
+            case 33: launch_one_pass<T, 16, true>(st, var, vw, gw, it, ni, rm, queue); break;
+            case 16: launch_one_pass<T, 8, false>(st, var, vw, gw, it, ni, rm, queue); break;
+            default: launch_one_pass<T, 8, true>(st, var, vw, gw, it, ni, rm, queue); break;
         }
-        if (evm) e = hipEventRecord(evm, st);
-        return e;
+        return evm ? hipEventRecord(evm, st) : hipSuccess;
     }
-    if (tun.variant == MBF_VARIANT_FUSED_LDS) {
-        switch (tun.tile_y) {
-            case 2: hipLaunchKernelGGL((mbf::k_step_lds_batch<T, 2>), g, dim3(64, 2), 0, st, vw, gw, it, ni, rm); break;
-            case 4: hipLaunchKernelGGL((mbf::k_step_lds_batch<T, 4>), g, dim3(64, 4), 0, st, vw, gw, it, ni, rm); break;
-            case 16: hipLaunchKernelGGL((mbf::k_step_lds_batch<T, 16>), g, dim3(64, 16), 0, st, vw, gw, it, ni, rm); break;
-            default: hipLaunchKernelGGL((mbf::k_step_lds_batch<T, 8>), g, dim3(64, 8), 0, st, vw, gw, it, ni, rm); break;
-        }
-        if (evm) e = hipEventRecord(evm, st);
-        return e;
-    }
-    if (tun.variant == MBF_VARIANT_FUSED) {
-        switch (tun.tile_y) {
-            case 2: hipLaunchKernelGGL((mbf::k_step_fused_batch<T, 2>), g, dim3(64, 2), 0, st, vw, gw, it, ni, rm); break;
-            case 4: hipLaunchKernelGGL((mbf::k_step_fused_batch<T, 4>), g, dim3(64, 4), 0, st, vw, gw, it, ni, rm); break;
-            case 16: hipLaunchKernelGGL((mbf::k_step_fused_batch<T, 16>), g, dim3(64, 16), 0, st, vw, gw, it, ni, rm); break;
-            default: hipLaunchKernelGGL((mbf::k_step_fused_batch<T, 8>), g, dim3(64, 8), 0, st, vw, gw, it, ni, rm); break;
-        }
-        if (evm) e = hipEventRecord(evm, st);
-        return e;
-    }
-    if (tun.variant == MBF_VARIANT_TWO_PASS_SPLIT) return launch_two_pass<T, true>(st, tun.tile_y, vw, gw, it, ni, rm, evm);
+    if (var == MBF_VARIANT_TWO_PASS_SPLIT) return launch_two_pass<T, true>(st, tun.tile_y, vw, gw, it, ni, rm, evm);
     return launch_two_pass<T, false>(st, tun.tile_y, vw, gw, it, ni, rm, evm);
 }
 
@@ -549,7 +561,7 @@ int self_tables(mbf_handle* h, const mbf::Geom& g) {
         h->items_cap = g.nblk;
     }
     mbf::SimView<T> v = view<T>(h);
-    v.n_part = g.nblk;
+    v.n_part = step_parts(h, h->tun, uses_tiles(h));
     std::vector<uint32_t> items((size_t)g.nblk);
     for (int w = 0; w < g.nblk; ++w) items[(size_t)w] = (uint32_t)w;      // member 0
     dispatch_order(items, 0, g.nblk, std::vector<mbf::Geom>{g}, g.xcd_remap);
@@ -576,10 +588,10 @@ int launch_step(mbf_handle* h, hipEvent_t ev0 = nullptr, hipEvent_t evm = nullpt
     const int rc = self_tables<T>(h, gm);
     if (rc) return rc;
     mbf::SimView<T> v = view<T>(h);
-    v.n_part = gm.nblk;
+    v.n_part = step_parts(h, h->tun, uses_tiles(h));
     if (ev0) HIPCHK(h, hipEventRecord(ev0, h->stream));
     HIPCHK(h, (launch_fields<T>(h->stream, h->tun, reinterpret_cast<const mbf::SimView<T>*>(h->d_view),
-                                h->d_geom, h->d_items, gm.nblk, evm, h->d_queue)));
+                                h->d_geom, h->d_items, gm.nblk, evm, h->d_queue, h->has_layer, uses_tiles(h))));
     if (ev1) HIPCHK(h, hipEventRecord(ev1, h->stream));
     if (h->mur_tasks > 0) {
         const int nmax = std::max({h->cfg.nx, h->cfg.ny, h->cfg.nz}) + 1;
@@ -1012,13 +1024,15 @@ int mbf_create(const mbf_config* cfg, void* stream, mbf_handle** out) {
     if (hipMalloc(&h->pool, bytes * 12) != hipSuccess) return bail(MBF_ENOMEM, "device allocation of the fields failed");
     for (int q = 0; q < 12; ++q) h->arr[q] = (char*)h->pool + (size_t)q * bytes;
     h->nbx = (c.nx + 63) / 64;
+    const size_t n16 = (size_t)((c.nx + 15) / 16) * c.ny * c.nz;
     if (hipMalloc(&h->seg_base, sizeof(uint32_t) * (size_t)h->nbx * c.ny * c.nz) != hipSuccess ||
+        hipMalloc(&h->seg16, sizeof(uint32_t) * n16) != hipSuccess ||
         hipMalloc(&h->mat, (size_t)h->nsite) != hipSuccess ||
-        hipMalloc(&h->lut, 3 * mbf::kMaxMat * h->esz) != hipSuccess ||
+        hipMalloc(&h->lut, 5 * mbf::kMaxMat * h->esz) != hipSuccess ||
         hipMalloc(&h->ctl, sizeof(mbf::Ctl)) != hipSuccess)
         return bail(MBF_ENOMEM, "device allocation failed");
-    // enough partial-sum slots for every kernel variant (one per workgroup)
-    h->n_part = ((c.nx + 63) / 64) * c.ny * c.nz;
+    // enough partial-sum slots for every schedule (one per 16 x 2 tile and plane)
+    h->n_part = ((c.nx + 15) / 16) * ((c.ny + 1) / 2) * c.nz;
     if (hipMalloc(&h->e_part, sizeof(double) * h->n_part) != hipSuccess ||
         hipMalloc(&h->l_part, sizeof(double) * h->n_part) != hipSuccess)
         return bail(MBF_ENOMEM, "device allocation failed");
@@ -1027,8 +1041,9 @@ int mbf_create(const mbf_config* cfg, void* stream, mbf_handle** out) {
         return bail(MBF_ENOMEM, "energy history allocation failed");
     if (hipMemsetAsync(h->pool, 0, bytes * 12, h->stream) != hipSuccess ||
         hipMemsetAsync(h->seg_base, 0, sizeof(uint32_t) * (size_t)h->nbx * c.ny * c.nz, h->stream) != hipSuccess ||
+        hipMemsetAsync(h->seg16, 0, sizeof(uint32_t) * n16, h->stream) != hipSuccess ||
         hipMemsetAsync(h->mat, 0, (size_t)h->nsite, h->stream) != hipSuccess ||
-        hipMemsetAsync(h->lut, 0, 3 * mbf::kMaxMat * h->esz, h->stream) != hipSuccess ||
+        hipMemsetAsync(h->lut, 0, 5 * mbf::kMaxMat * h->esz, h->stream) != hipSuccess ||
         hipMemsetAsync(h->ctl, 0, sizeof(mbf::Ctl), h->stream) != hipSuccess ||
         hipMemsetAsync(h->l_part, 0, sizeof(double) * h->n_part, h->stream) != hipSuccess ||
         hipStreamSynchronize(h->stream) != hipSuccess)
@@ -1060,7 +1075,7 @@ void mbf_destroy(mbf_handle* h) {
     if (h->stream) hipStreamSynchronize(h->stream);
     drop_graph(h);
     free_probes(h);
-    hipFree(h->pool); hipFree(h->gpool); hipFree(h->seg_base);
+    hipFree(h->pool); hipFree(h->gpool); hipFree(h->seg_base); hipFree(h->seg16);
     hipFree(h->mat); hipFree(h->lut);
     hipFree(h->ctl); hipFree(h->e_part); hipFree(h->l_part); hipFree(h->hist); hipFree(h->lev); hipFree(h->lc);
     hipFree(h->d_view); hipFree(h->d_geom); hipFree(h->d_items); hipFree(h->d_queue); hipFree(h->map);
@@ -1140,11 +1155,13 @@ int mbf_set_material(mbf_handle* h, const float* eps_r, const uint8_t* gain, int
     // gain cells, numbered in memory order (z, y, x); the count before every
     // 64-wide x segment of every row is the segment's base in the compact arrays
     int64_t gsites = 0, ngain = 0;
-    std::vector<uint32_t> seg((size_t)h->nbx * c.ny * c.nz);
+    const int nb16 = (c.nx + 15) / 16;
+    std::vector<uint32_t> seg((size_t)h->nbx * c.ny * c.nz), seg16((size_t)nb16 * c.ny * c.nz);
     for (int k = 0; k < c.nz; ++k)
         for (int j = 0; j < c.ny; ++j)
             for (int i = 0; i < c.nx; ++i) {
                 if ((i & 63) == 0) seg[(size_t)(i >> 6) + (size_t)h->nbx * (j + (size_t)c.ny * k)] = (uint32_t)ngain;
+                if ((i & 15) == 0) seg16[(size_t)(i >> 4) + (size_t)nb16 * (j + (size_t)c.ny * k)] = (uint32_t)ngain;
                 if (cell_id[(size_t)i + (size_t)c.nx * (j + (size_t)c.ny * k)] < mbf::kGainId) continue;
                 ++ngain;
                 gsites += (j >= 1 && k >= 1) + (i >= 1 && k >= 1) + (i >= 1 && j >= 1);
@@ -1158,19 +1175,22 @@ int mbf_set_material(mbf_handle* h, const float* eps_r, const uint8_t* gain, int
         const double sp = Sx / std::sqrt(e);
         mur[q] = (sp - 1.0) / (sp + 1.0);
     }
-    std::vector<uint8_t> lutbuf(3 * mbf::kMaxMat * h->esz);
+    std::vector<uint8_t> lutbuf(5 * mbf::kMaxMat * h->esz);
     for (int q = 0; q < mbf::kMaxMat; ++q) {
         if (h->esz == 8) {
             double* d = reinterpret_cast<double*>(lutbuf.data());
             d[q] = inv[q]; d[mbf::kMaxMat + q] = ep[q]; d[2 * mbf::kMaxMat + q] = mur[q];
+            d[3 * mbf::kMaxMat + 2 * q] = ep[q]; d[3 * mbf::kMaxMat + 2 * q + 1] = inv[q];
         } else {
             float* d = reinterpret_cast<float*>(lutbuf.data());
             d[q] = (float)inv[q]; d[mbf::kMaxMat + q] = (float)ep[q]; d[2 * mbf::kMaxMat + q] = (float)mur[q];
+            d[3 * mbf::kMaxMat + 2 * q] = (float)ep[q]; d[3 * mbf::kMaxMat + 2 * q + 1] = (float)inv[q];
         }
     }
     HIPCHK(h, hipStreamSynchronize(h->stream));
     drop_graph(h);
-    // compact Bloch-state arrays, 15 of glen values (a multiple of 64, at least 64)
+    // compact Bloch-state arrays, five of glen entries of three components (glen
+    // a multiple of 64, at least 64)
     const int64_t glen = std::max<int64_t>(64, (ngain + 63) / 64 * 64);
     if (glen != h->glen) {
         hipFree(h->gpool);
@@ -1181,11 +1201,12 @@ int mbf_set_material(mbf_handle* h, const float* eps_r, const uint8_t* gain, int
         if (hipMalloc(&h->gpool, (size_t)glen * h->esz * 15) != hipSuccess)
             return fail(h, MBF_ENOMEM, "device allocation of the Bloch state failed");
         h->glen = glen;
-        for (int q = 0; q < 15; ++q) h->arr[12 + q] = (char*)h->gpool + (size_t)q * glen * h->esz;
+        for (int q = 0; q < 15; ++q) h->arr[12 + q] = (char*)h->gpool + ((size_t)(q / 3) * 3 * glen + q % 3) * h->esz;
     }
     HIPCHK(h, hipMemset(h->gpool, 0, (size_t)glen * h->esz * 15));
     h->ngain = ngain;
     HIPCHK(h, hipMemcpy(h->seg_base, seg.data(), sizeof(uint32_t) * seg.size(), hipMemcpyHostToDevice));
+    HIPCHK(h, hipMemcpy(h->seg16, seg16.data(), sizeof(uint32_t) * seg16.size(), hipMemcpyHostToDevice));
     HIPCHK(h, hipMemcpy(h->mat, site.data(), site.size(), hipMemcpyHostToDevice));
     HIPCHK(h, hipMemcpy(h->lut, lutbuf.data(), lutbuf.size(), hipMemcpyHostToDevice));
     h->gain_sites = gsites;
@@ -1438,6 +1459,17 @@ int run_steps(mbf_handle* h, int64_t nsteps, std::vector<hipEvent_t>* ev) {
     return MBF_OK;
 }
 
+// Algorithmic bytes of a member's step and of its first and second field
+// kernel (one kernel: one_pass).
+void member_step_bytes(const mbf_handle* h, bool one_pass, double* bytes) {
+    const double cells = (double)h->cfg.nx * h->cfg.ny * h->cfg.nz;
+    const double v = (double)h->esz;
+    const double gs = (double)h->gain_sites;
+    bytes[0] = cells * (12.0 * v + 1.0) + gs * 9.0 * v;                          // the step
+    bytes[1] = one_pass ? bytes[0] : cells * (9.0 * v + 1.0);                    // E read, H read + written, material
+    bytes[2] = one_pass ? 0.0 : cells * (9.0 * v + 1.0) + gs * 9.0 * v;          // H read, E read + written, material, Bloch state
+}
+
 }  // namespace
 
 extern "C" {
@@ -1478,17 +1510,7 @@ int mbf_step_timed(mbf_handle* h, int64_t nsteps, double* kernel_ms, int64_t* la
 
 int mbf_step_bytes(const mbf_handle* h, double* bytes) {
     if (!h || !bytes) return fail(nullptr, MBF_EINVAL, "null argument");
-    const double cells = (double)h->cfg.nx * h->cfg.ny * h->cfg.nz;
-    const double v = (double)h->esz;
-    const double gs = (double)h->gain_sites;
-    bytes[0] = cells * (12.0 * v + 1.0) + gs * 9.0 * v;      // the step
-    if (single_pass(h->tun.variant)) {
-        bytes[1] = bytes[0];
-        bytes[2] = 0.0;
-    } else {
-        bytes[1] = cells * (9.0 * v + 1.0);                  // E read, H read + written, material
-        bytes[2] = cells * (9.0 * v + 1.0) + gs * 9.0 * v;   // H read, E read + written, material, Bloch state
-    }
+    member_step_bytes(h, h->tun.variant == MBF_VARIANT_FUSED_LDS || uses_tiles(h), bytes);
     return MBF_OK;
 }
 
@@ -2330,6 +2352,8 @@ struct mbf_batch {
     };
     std::vector<Group> groups;
     Group all{0, 0, 0, 0, 0, 0};  // every member as one group (timed steps)
+    bool any_layer = false;       // some member has an absorbing layer
+    bool tiles = false;           // the tables are the tile kernel's
     std::vector<uint64_t> seen;   // member versions the device tables describe
     bool tables = false;
     hipGraphExec_t gexec = nullptr;
@@ -2364,6 +2388,22 @@ void batch_free_tables(mbf_batch* b) {
     b->tables = false;
 }
 
+// Whether the batch's schedule runs the tile kernel: the rule goes by the
+// largest group of members, since a group runs a whole chunk of steps before
+// the next.
+bool batch_uses_tiles(const mbf_batch* b) {
+    const double budget = (double)b->tun.group_mb * 1048576.0;
+    double gbytes = 0.0, gstate = 0.0, largest = 0.0;
+    for (const mbf_handle* h : b->m) {
+        const double mb = (double)snap_bytes(h);
+        if (budget > 0.0 && gbytes > 0.0 && gbytes + mb > budget) gbytes = gstate = 0.0;
+        gbytes += mb;
+        gstate += state_bytes(h);
+        largest = std::max(largest, gstate);
+    }
+    return tile_schedule(b->tun, largest);
+}
+
 // Rebuild the device views, geometries and work table when a member changed.
 template <typename T>
 int batch_tables(mbf_batch* b) {
@@ -2378,13 +2418,16 @@ int batch_tables(mbf_batch* b) {
     std::vector<mbf::Geom> geoms(R);
     std::vector<uint32_t> items;
     b->groups.clear();
+    b->any_layer = false;
+    for (const mbf_handle* h : b->m) b->any_layer = b->any_layer || h->has_layer;
     const double budget = (double)b->tun.group_mb * 1048576.0;
+    b->tiles = batch_uses_tiles(b);
     double gbytes = 0.0;
     for (int r = 0; r < R; ++r) {
         mbf_handle* h = b->m[r];
-        geoms[r] = step_geom(h, b->tun);
+        geoms[r] = step_geom(h, b->tun, b->tiles);
         views[r] = view<T>(h);
-        views[r].n_part = geoms[r].nblk;
+        views[r].n_part = step_parts(h, b->tun, b->tiles);
         if (geoms[r].nblk >= (1 << 24)) return bfail(b, MBF_EINVAL, "member grid has too many work items");
         // a new group when this member would overflow the budget
         const double mb = (double)snap_bytes(h);
@@ -2444,7 +2487,7 @@ int batch_launch_step(mbf_batch* b, int gi, hipEvent_t ev0 = nullptr, hipEvent_t
     const int ni = gr.i1 - gr.i0;
     hipStream_t st = b->stream;
     if (ev0) BHIPCHK(b, hipEventRecord(ev0, st));
-    BHIPCHK(b, (launch_fields<T>(st, b->tun, vw, gw, it, ni, evm, b->d_queue)));
+    BHIPCHK(b, (launch_fields<T>(st, b->tun, vw, gw, it, ni, evm, b->d_queue, b->any_layer, b->tiles)));
     if (ev1) BHIPCHK(b, hipEventRecord(ev1, st));
     const mbf::SimView<T>* views = reinterpret_cast<const mbf::SimView<T>*>(b->d_views) + gr.r0;
     const unsigned nm = (unsigned)(gr.r1 - gr.r0);
@@ -2829,10 +2872,10 @@ int mbf_batch_autotune(mbf_batch* b, int budget_ms, mbf_tuning* chosen) {
 int mbf_batch_step_bytes(const mbf_batch* b, double* bytes) {
     if (!b || !bytes) return bfail(nullptr, MBF_EINVAL, "null argument");
     bytes[0] = bytes[1] = bytes[2] = 0.0;
+    const bool one_pass = b->tun.variant == MBF_VARIANT_FUSED_LDS || batch_uses_tiles(b);
     for (const mbf_handle* h : b->m) {
         double x[3];
-        const int rc = mbf_step_bytes(h, x);
-        if (rc) return rc;
+        member_step_bytes(h, one_pass, x);
         for (int q = 0; q < 3; ++q) bytes[q] += x[q];
     }
     return MBF_OK;
@@ -2877,14 +2920,15 @@ int set_tap(mbf_handle* h, void* buffer, int64_t base) {
         drop_graph(h);
     }
     if (!buffer) return MBF_OK;
-    h->tap_base = base;
-    HIPCHK(h, hipMemcpyAsync(&h->ctl->tap_base, &h->tap_base, sizeof(int64_t), hipMemcpyHostToDevice, h->stream));
-    // slot of the current state
+    // slot 0, and the base as a kernel argument: a copy of eight bytes from
+    // host memory kept the device idle for 130-200 us a segment
     hipLaunchKernelGGL(mbf::k_tap_state<T>, dim3((unsigned)h->nbx, (unsigned)h->cfg.ny, (unsigned)h->cfg.nz),
-                       dim3(64), 0, h->stream, view<T>(h));
+                       dim3(64), 0, h->stream, view<T>(h), base);
     HIPCHK(h, hipGetLastError());
     return MBF_OK;
 }
+
+constexpr double kAdjTileBytes = 128e6;   // see adjoint_run
 
 template <typename T>
 int adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int mem_kind, double* grad_Na,
@@ -2902,18 +2946,31 @@ int adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int mem_ki
         if (!rc) rc = snap_alloc(h, q);
     if (!rc) rc = snap_alloc(h, B.end);
     if (rc) return rc;
+    // reverse steps in one pass while their state (twice E and H, the compact
+    // arrays, two trajectory slots, the gradient) takes at most half of the
+    // 256 MB last-level cache, past which the trajectory streams.  A whole run
+    // (forward, recomputation, reverse) in us a step, two kernels and one:
+    // 48^3 62.8 and 41, 64^3 70 and 59, 80^3 96 and 87, 96^3 (111 MB) 128 and
+    // 126, 112^3 (174 MB) 176 and 185.  One plane a wave: on such grids two or
+    // four leave the device waves short (96^3: 124.9, 126.2 and 128.9 for 1, 2
+    // and 4 planes)
+    const double adj_bytes = (double)esz * (12.0 * h->nsite + 15.0 * h->glen) + 2.0 * (double)slot + 8.0 * (double)ncell;
+    const bool tiles = adj_bytes <= kAdjTileBytes;
     mbf::Geom gm{};
-    gm.tiles_x = h->nbx;
+    gm.tiles_x = tiles ? (c.nx + 15) / 16 : h->nbx;
     gm.tiles_y = (c.ny + 3) / 4;
-    gm.zseg = std::min(4, c.nz);
+    gm.per_seg = tiles ? (gm.tiles_x * gm.tiles_y + 3) / 4 : gm.tiles_x * gm.tiles_y;
+    gm.zseg = tiles ? 1 : std::min(4, c.nz);
     gm.segs = (c.nz + gm.zseg - 1) / gm.zseg;
-    gm.nblk = gm.tiles_x * gm.tiles_y * gm.segs;
+    gm.nblk = gm.per_seg * gm.segs;
     gm.xcd_remap = 1;
+    const size_t nna = tiles ? (size_t)gm.tiles_x * gm.tiles_y * gm.segs : (size_t)gm.nblk;   // N_a partials
+    const size_t EU = (tiles ? 2 : 1) * E3;           // u, and htot
     const size_t npop = (size_t)h->nbx * c.ny * c.nz;
     if (hipMalloc(&B.traj, slot * (size_t)(K + 1)) != hipSuccess ||
-        hipMalloc(&B.adj, (2 * E3 + 5 * C3) * esz) != hipSuccess ||
+        hipMalloc(&B.adj, (2 * EU + 5 * C3) * esz) != hipSuccess ||
         hipMalloc(&B.g_eps, ncell * sizeof(double)) != hipSuccess ||
-        hipMalloc(&B.g_na, (size_t)gm.nblk * sizeof(double)) != hipSuccess ||
+        hipMalloc(&B.g_na, nna * sizeof(double)) != hipSuccess ||
         hipMalloc(&B.g_pop, npop * sizeof(double)) != hipSuccess)
         return fail(h, MBF_ENOMEM, "device allocation for the adjoint failed");
     struct TapOff {                                   // recording ends with the run
@@ -2936,22 +2993,23 @@ int adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int mem_ki
     if (ctl.nonfinite) return fail(h, MBF_ENONFINITE, "the forward run produced a non-finite energy");
     // ---- reverse sweep
     char* adj = (char*)B.adj;
-    HIPCHK(h, hipMemsetAsync(adj, 0, (2 * E3 + 5 * C3) * esz, h->stream));
+    HIPCHK(h, hipMemsetAsync(adj, 0, (2 * EU + 5 * C3) * esz, h->stream));
     HIPCHK(h, hipMemsetAsync(B.g_eps, 0, ncell * sizeof(double), h->stream));
-    HIPCHK(h, hipMemsetAsync(B.g_na, 0, (size_t)gm.nblk * sizeof(double), h->stream));
+    HIPCHK(h, hipMemsetAsync(B.g_na, 0, nna * sizeof(double), h->stream));
     mbf::AdjView<T> v{};
     for (int q = 0; q < 3; ++q) {
         v.u[q] = (T*)(adj + ((size_t)q * h->nsite) * esz);
-        v.hb[q] = (T*)(adj + (E3 + (size_t)q * h->nsite) * esz);
-        v.lp[q] = (T*)(adj + (2 * E3 + (size_t)q * h->glen) * esz);
-        v.lq[q] = (T*)(adj + (2 * E3 + C3 + (size_t)q * h->glen) * esz);
-        for (int p = 0; p < 3; ++p) v.ln[p][q] = (T*)(adj + (2 * E3 + (2 + p) * C3 + (size_t)q * h->glen) * esz);
+        v.hb[q] = (T*)(adj + (EU + (size_t)q * h->nsite) * esz);
+        v.ln[q] = (T*)(adj + (2 * EU + (2 + q) * C3) * esz);
     }
+    v.lp = (T*)(adj + 2 * EU * esz);
+    v.lq = (T*)(adj + (2 * EU + C3) * esz);
     v.g_eps = B.g_eps;
     v.g_na = B.g_na;
     v.mat = h->mat;
     v.seg_base = h->seg_base;
     v.nbx = h->nbx;
+    v.seg16 = h->seg16;
     v.lut_inv_eps = reinterpret_cast<const T*>(h->lut);
     v.nx = c.nx; v.ny = c.ny; v.nz = c.nz;
     v.sx = h->sx; v.sxy = h->sxy;
@@ -2985,6 +3043,11 @@ int adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int mem_ki
     const dim3 gblk((unsigned)gm.nblk), tb(64, 4);
     // the reverse step of slot q of a segment (step tap_base + q)
     auto reverse_step = [&](int q) {
+        if (tiles) {
+            if (h->has_layer) hipLaunchKernelGGL((mbf::k_adj_tile<T, 4, true>), gblk, tb, 0, h->stream, dv, gm, q);
+            else hipLaunchKernelGGL((mbf::k_adj_tile<T, 4, false>), gblk, tb, 0, h->stream, dv, gm, q);
+            return;
+        }
         hipLaunchKernelGGL((mbf::k_adj_h<T, 4>), gblk, tb, 0, h->stream, dv, gm);
         hipLaunchKernelGGL((mbf::k_adj_e<T, 4>), gblk, tb, 0, h->stream, dv, gm, q);
     };
@@ -3001,7 +3064,7 @@ int adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int mem_ki
         // ctl->tap_base)
         if (sg == nseg - 1)                           // etot = 2 E^N in the box
             hipLaunchKernelGGL(mbf::k_adj_seed<T>, dim3((unsigned)((c.nx + 64) / 64), (unsigned)(c.ny + 1), (unsigned)(c.nz + 1)),
-                               dim3(64), 0, h->stream, v, (int)kp - 1);
+                               dim3(64), 0, h->stream, v, (int)kp - 1, tiles ? (int64_t)((nsteps - 1) & 1) * 3 * h->nsite : (int64_t)0);
         if (kp == K) {                                 // a whole segment: the captured sequence
             if (!B.rev) {
                 hipGraph_t g = nullptr;
@@ -3035,7 +3098,7 @@ int adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int mem_ki
     hipLaunchKernelGGL(mbf::k_adj_init_pop<T>, dim3((unsigned)h->nbx, (unsigned)c.ny, (unsigned)c.nz), dim3(64), 0,
                        h->stream, v, r[0], r[1], r[2], B.g_pop);
     HIPCHK(h, hipGetLastError());
-    std::vector<double> pa((size_t)gm.nblk), pb(npop);
+    std::vector<double> pa(nna), pb(npop);
     HIPCHK(h, hipStreamSynchronize(h->stream));
     HIPCHK(h, hipMemcpy(pa.data(), B.g_na, pa.size() * sizeof(double), hipMemcpyDeviceToHost));
     HIPCHK(h, hipMemcpy(pb.data(), B.g_pop, pb.size() * sizeof(double), hipMemcpyDeviceToHost));

@@ -46,20 +46,23 @@ struct SimView {
     using value_type = T;
     T* E[2][3];
     T* H[2][3];
-    T* P[2][3];               // compact, one value per gain cell
-    T* N[3][3];               // N1, N2, N3 x component, compact
+    // compact, one entry per gain cell: the three components side by side
+    T* P[2];
+    T* N[3];                  // N1, N2, N3
     const uint32_t* seg_base; // gain cells before segment (bx, j, k), bx + nbx (j + ny k)
     // trajectory recording for the adjoint (tap == nullptr: off): the E pass
     // writes E^{n+1}, P^{n+1} - P^n and N1 - N2 at n+1 into slot
     // n + 1 - ctl->tap_base of tap_stride values: E (3 x tap_e dense), dP
-    // (3 x tap_c compact), N1 - N2 (3 x tap_c compact)
+    // (tap_c compact entries of three), N1 - N2 (likewise)
     T* tap;
     int64_t tap_stride, tap_e, tap_c;
     int nbx;                  // 64-wide segments per row
+    const uint32_t* seg16;    // gain cells before 16-wide segment (q, j, k), q + nb16 (j + ny k)
     const uint8_t* mat;       // per site of the extended range
     const T* lut_inv_eps;     // per material id
     const T* lut_eps;
     const T* lut_mur;
+    const T* lut_pair;        // (eps_r, 1/eps_r) per material id
     int nx, ny, nz;
     int64_t sx, sxy;          // strides of the extended range
     T S, a, b, ck, cF, beta, dt32, dt21, dt10, dtWp, Na;
@@ -170,27 +173,6 @@ __device__ __forceinline__ void noise3(const V& v, uint32_t cell, uint32_t step,
     box_muller3(x0, x1, x2, x3, xi);
 }
 
-// -------------------------------------------------------------- reductions
-__device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
-
-// Sum over a workgroup in a fixed order (deterministic); thread 0 gets the sum.
-__device__ __forceinline__ double block_sum(double x, double* sh) {
-    const int t = threadIdx.x + threadIdx.y * blockDim.x;
-    x = wave_sum(x);
-    if ((t & 63) == 0) sh[t >> 6] = x;
-    __syncthreads();
-    double r = 0.0;
-    if (t == 0) {
-        const int nw = (blockDim.x * blockDim.y + 63) >> 6;
-        for (int w = 0; w < nw; ++w) r += sh[w];
-    }
-    return r;
-}
-
 // Loads and stores at a 32-bit element offset from a uniform base: the
 // address is base + zero-extended 32-bit byte offset, which maps to the
 // scalar-base form of the global memory instructions.  The pointers are
@@ -207,6 +189,30 @@ __device__ __forceinline__ void sto(T* base, uint32_t off, T val) {
     MBF_GLOBAL char* b = (MBF_GLOBAL char*)base;
     *(MBF_GLOBAL T*)(b + off * (uint32_t)sizeof(T)) = val;
 }
+// The compact arrays hold a gain cell's three components side by side, so a
+// wave's cells are one contiguous run of 12-byte (24 in FP64) entries that one
+// instruction moves.  The vector memory path takes as long for a run of lanes
+// that starts anywhere as for whole lines, and one access of three values
+// costs it less than three of one value at three such places: reading five
+// quantities and writing four with 26 of 64 lanes active ran at 4.95 TB/s
+// against 3.93 for 15 and 12 arrays of single values (409 MB), and 1.4 times
+// as fast for rows of 16.  Entry offsets go beyond 32 bits.
+template <typename T>
+struct Vec3 {
+    T c[3];
+};
+template <typename T>
+__device__ __forceinline__ Vec3<T> ld3(const T* base, uint32_t gi) {
+    const MBF_GLOBAL T* p = (const MBF_GLOBAL T*)base + (uint64_t)gi * 3u;
+    return {{p[0], p[1], p[2]}};
+}
+template <typename T>
+__device__ __forceinline__ void st3(T* base, uint32_t gi, T x, T y, T z) {
+    MBF_GLOBAL T* p = (MBF_GLOBAL T*)base + (uint64_t)gi * 3u;
+    p[0] = x;
+    p[1] = y;
+    p[2] = z;
+}
 // Streaming store (non-temporal: the line is not kept in the caches).
 template <typename T>
 __device__ __forceinline__ void sto_nt(T* base, uint32_t off, T val) {
@@ -218,6 +224,76 @@ __device__ __forceinline__ T gld(const T* p) {
     return *(const MBF_GLOBAL T*)p;
 }
 
+// -------------------------------------------------------------- reductions
+__device__ __forceinline__ double wave_sum(double x) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
+
+// Sum over each row of 16 lanes; every lane of the row gets it.
+__device__ __forceinline__ double row16_sum(double x) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
+
+// Energy and loss partials: one per tile of 16 x RB columns of a z segment (RB
+// = 4, or 2 for workgroups of two rows), formed as the sum over each row of
+// 16 sites and then over the rows in order, and numbered (x, y, segment), x
+// fastest, whatever workgroups a kernel cuts the grid into.  So a step's sums
+// depend on its segment length alone (and on RB).
+
+// A wave owns one row of 64 sites, its workgroup TY rows: the workgroup's
+// tiles of partial array `part` from every lane's share x.
+template <int TY, typename V>
+__device__ __forceinline__ void tile_sums_rows(const V& v, double* part, int bx, int by, int bz, double x,
+                                               double (*sh)[4]) {
+    constexpr int RB = TY >= 4 ? 4 : TY;
+    const int lane = (int)threadIdx.x, row = (int)threadIdx.y;
+    x = row16_sum(x);
+    __syncthreads();                                  // earlier readers of sh are done
+    if ((lane & 15) == 0) sh[row][lane >> 4] = x;
+    __syncthreads();
+    const int t = lane + 64 * row;
+    if (t >= TY / RB * 4) return;
+    const int tx = bx * 4 + (t & 3), ty = by * (TY / RB) + (t >> 2);
+    const int ntx = (v.nx + 15) >> 4, nty = (v.ny + RB - 1) / RB;
+    if (tx >= ntx || ty >= nty) return;
+    double r = 0.0;
+#pragma unroll
+    for (int q = 0; q < RB; ++q) r += sh[(t >> 2) * RB + q][t & 3];
+    sto(part, (uint32_t)(tx + ntx * (ty + nty * bz)), r);
+}
+
+// A wave owns a whole tile of 16 x 4 sites (lane = 16 row + column).
+// add: the sum is added to the slot.
+__device__ __forceinline__ void tile_sum_wave(double* part, uint32_t slot, double x, bool add = false) {
+    x = row16_sum(x);
+    double r = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int lo = __builtin_amdgcn_readlane(__double2loint(x), 16 * q);
+        const int hi = __builtin_amdgcn_readlane(__double2hiint(x), 16 * q);
+        r += __hiloint2double(hi, lo);
+    }
+    if (threadIdx.x == 0) sto(part, slot, add ? gld(part + slot) + r : r);
+}
+
+// Sum over a workgroup in a fixed order (deterministic); thread 0 gets the sum.
+__device__ __forceinline__ double block_sum(double x, double* sh) {
+    const int t = threadIdx.x + threadIdx.y * blockDim.x;
+    x = wave_sum(x);
+    if ((t & 63) == 0) sh[t >> 6] = x;
+    __syncthreads();
+    double r = 0.0;
+    if (t == 0) {
+        const int nw = (blockDim.x * blockDim.y + 63) >> 6;
+        for (int w = 0; w < nw; ++w) r += sh[w];
+    }
+    return r;
+}
+
 // Field pointers of one step, chosen once per kernel from the step parity
 // (uniform selects; the kernel-argument arrays are only ever indexed with
 // compile-time constants, so nothing is copied to private memory).
@@ -227,11 +303,11 @@ struct Fields {
     T* en[3];         // E^{n+1}
     const T* h[3];    // H^{n-1/2}
     T* hn[3];         // H^{n+1/2}
-    const T* p[3];    // P^n
-    T* q[3];          // P^{n-1} on entry, P^{n+1} on exit
-    T* n1[3];
-    T* n2[3];
-    T* n3[3];
+    const T* p;       // P^n
+    T* q;             // P^{n-1} on entry, P^{n+1} on exit
+    T* n1;
+    T* n2;
+    T* n3;
 };
 
 template <typename T>
@@ -243,12 +319,12 @@ __device__ __forceinline__ Fields<T> bind_fields(const SimView<T>& v, int par) {
         f.en[c] = par ? v.E[0][c] : v.E[1][c];
         f.h[c] = par ? v.H[1][c] : v.H[0][c];
         f.hn[c] = par ? v.H[0][c] : v.H[1][c];
-        f.p[c] = par ? v.P[1][c] : v.P[0][c];
-        f.q[c] = par ? v.P[0][c] : v.P[1][c];
-        f.n1[c] = v.N[0][c];
-        f.n2[c] = v.N[1][c];
-        f.n3[c] = v.N[2][c];
     }
+    f.p = par ? v.P[1] : v.P[0];
+    f.q = par ? v.P[0] : v.P[1];
+    f.n1 = v.N[0];
+    f.n2 = v.N[1];
+    f.n3 = v.N[2];
     return f;
 }
 
@@ -341,6 +417,7 @@ __device__ __forceinline__ T source_value(const SimView<T>& v, int64_t n) {
 // z segments of zseg planes, one workgroup each, on a 1-D grid of nblk.
 struct Geom {
     int tiles_x, tiles_y, segs, zseg, nblk, xcd_remap;
+    int per_seg;              // workgroups per z segment
 };
 
 // Workgroups are dealt to the 8 XCDs in turn (id mod 8); with remapping, XCD
@@ -424,7 +501,7 @@ __device__ __forceinline__ void load_hplane(HPlane<T>& p, const Fields<T>& f, co
 // caches, where the E pass reads it back from HBM anyway).
 template <typename T, int TY, bool NT>
 __device__ __forceinline__ void curl_h_body(const SimView<T>& v, const Geom& gm, int w) {
-    __shared__ double sh[TY];
+    __shared__ double sh[TY][4];
     int bx, by, bz;
     decode_item(gm, w, bx, by, bz);
     const int i = bx * 64 + threadIdx.x;
@@ -507,8 +584,7 @@ __device__ __forceinline__ void curl_h_body(const SimView<T>& v, const Geom& gm,
             P = Q;
         }
     }
-    const double s = block_sum((double)wsum, sh);
-    if (threadIdx.x == 0 && threadIdx.y == 0) sto(v.e_part, (uint32_t)w, s);
+    tile_sums_rows<TY>(v, v.e_part, bx, by, bz, (double)wsum, sh);
 }
 
 // The tables are separate no-alias read-only arguments, so the compiler may
@@ -523,49 +599,40 @@ __global__ void __launch_bounds__(64 * TY) k_curl_h_batch(const SimView<T>* __re
 }
 
 // ---------------------------------------------------- rows a2, a3, a4, a5
-// Per-site Bloch state of one E-site: P^n, P^{n-1} and N1..N3 (zero where
-// the site carries no gain).  Loaded ahead of the update so that the loads are
-// in flight while the field part of the step is computed.
+// Bloch state of a cell's three E-sites: P^n, P^{n-1} (P^{n+1} once updated)
+// and N1..N3; zero where the cell carries no gain.  Loaded ahead of the update
+// so that the loads are in flight while the field part of the step is computed.
 template <typename T>
-struct BlochIn {
-    T P, Pp, n1, n2, n3;
+struct Bloch {
+    Vec3<T> P, Pp, n1, n2, n3;
 };
 
 template <typename T>
-__device__ __forceinline__ BlochIn<T> bloch_load(const Fields<T>& f, int c, uint32_t gi, bool gain) {
-    BlochIn<T> b{(T)0, (T)0, (T)0, (T)0, (T)0};
-    if (gain) {
-        b.P = ldo(f.p[c], gi);
-        b.Pp = ldo(f.q[c], gi);
-        b.n1 = ldo(f.n1[c], gi);
-        b.n2 = ldo(f.n2[c], gi);
-        b.n3 = ldo(f.n3[c], gi);
-    }
+__device__ __forceinline__ Bloch<T> bloch_load(const Fields<T>& f, uint32_t gi, bool gain) {
+    Bloch<T> b{};
+    if (gain) b = {ld3(f.p, gi), ld3(f.q, gi), ld3(f.n1, gi), ld3(f.n2, gi), ld3(f.n3, gi)};
     return b;
 }
 
-// Rows a2-a5 at one E-site from its loaded Bloch state.  `upd` marks an
-// interior site (updated by Ampere's law; other sites keep E), `gain` an
-// interior site of a gain cell, gi the cell's compact index.  Returns E^{n+1}.
-template <typename T>
-__device__ __forceinline__ T bloch_site(const SimView<T>& v, const Fields<T>& f, int c, uint32_t gi,
-                                        T e, T curl, T ie, bool upd, bool gain,
-                                        const BlochIn<T>& b, T xi, T src, LayC<T> lay, T* tslot) {
-    T dP = (T)0;
-    T Pn = (T)0;
-    if (gain) {
-        Pn = v.a * b.P + v.b * b.Pp + v.ck * (b.n1 - b.n2) * e + v.cF * xi;
-        dP = Pn - b.P;
-    }
+// Rows a2-a5 at E-site c from the cell's loaded Bloch state, which is brought
+// to n+1 in place.  `upd` marks an interior site (updated by Ampere's law;
+// other sites keep E), `gain` an interior site of a gain cell.  LAY: the
+// launch may have a lossy layer.  Returns E^{n+1}.
+template <typename T, bool LAY>
+__device__ __forceinline__ T bloch_site(const SimView<T>& v, int c, T e, T curl, T ie, bool upd, bool gain,
+                                        Bloch<T>& b, T xi, T src, LayC<T> lay) {
+    const T n1 = b.n1.c[c], n2 = b.n2.c[c], n3 = b.n3.c[c];
+    const T Pn = v.a * b.P.c[c] + v.b * b.Pp.c[c] + v.ck * (n1 - n2) * e + v.cF * xi;
+    const T dP = gain ? Pn - b.P.c[c] : (T)0;
     // semi-implicit loss of the layer: (E' - E) = (1/eps)(S curl - dP) - a (E' + E)
-    T en = lay.ca * e + lay.cb * (ie * (v.S * curl - dP));
+    T en;
+    if constexpr (LAY) en = lay.ca * e + lay.cb * (ie * (v.S * curl - dP));
+    else en = e + ie * (v.S * curl - dP);
     en += src;
     en = upd ? en : e;
     if (gain) {
-        sto(f.q[c], gi, Pn);
-        T d12 = b.n1 - b.n2;
+        b.Pp.c[c] = Pn;
         if (!v.frozen_pop) {
-            const T n1 = b.n1, n2 = b.n2, n3 = b.n3;
             const T W = v.beta * ((T)0.5 * (en + e)) * dP;
             // N0 = N_a - N1 - N2 - N3, with N_a - N2 taken first: N2 holds
             // nearly all atoms of a pumped site, that difference of nearly
@@ -573,19 +640,31 @@ __device__ __forceinline__ T bloch_site(const SimView<T>& v, const Fields<T>& f,
             // N1 from N_a first would round at the scale of N_a, a relative
             // error of order 1e-4 in N0, whose pump term sets N3's fixed point)
             const T n0 = (v.Na - n2) - (n1 + n3);
-            const T m2 = n2 + (v.dt32 * n3 - v.dt21 * n2) + W;
-            const T m1 = n1 + (v.dt21 * n2 - v.dt10 * n1) - W;
-            sto(f.n3[c], gi, n3 + (v.dtWp * n0 - v.dt32 * n3));
-            sto(f.n2[c], gi, m2);
-            sto(f.n1[c], gi, m1);
-            d12 = m1 - m2;
-        }
-        if (tslot) {
-            sto(tslot + 3 * v.tap_e + c * v.tap_c, gi, dP);
-            sto(tslot + 3 * v.tap_e + 3 * v.tap_c + c * v.tap_c, gi, d12);
+            b.n3.c[c] = n3 + (v.dtWp * n0 - v.dt32 * n3);
+            b.n2.c[c] = n2 + (v.dt32 * n3 - v.dt21 * n2) + W;
+            b.n1.c[c] = n1 + (v.dt21 * n2 - v.dt10 * n1) - W;
         }
     }
     return en;
+}
+
+// The updated state of a gain cell; sites that bloch_site left alone get back
+// what they held.  tslot: the trajectory slot's compact part, or nullptr.
+template <typename T>
+__device__ __forceinline__ void bloch_store(const SimView<T>& v, const Fields<T>& f, uint32_t gi, const Bloch<T>& b,
+                                            T* tslot) {
+    const auto put = [gi](T* base, const Vec3<T>& x) { st3(base, gi, x.c[0], x.c[1], x.c[2]); };
+    put(f.q, b.Pp);
+    if (!v.frozen_pop) {
+        put(f.n3, b.n3);
+        put(f.n2, b.n2);
+        put(f.n1, b.n1);
+    }
+    if (tslot) {
+        T* const t = tslot + 3 * v.tap_e;
+        put(t, {{b.Pp.c[0] - b.P.c[0], b.Pp.c[1] - b.P.c[1], b.Pp.c[2] - b.P.c[2]}});
+        put(t + 3 * v.tap_c, {{b.n1.c[0] - b.n2.c[0], b.n1.c[1] - b.n2.c[1], b.n1.c[2] - b.n2.c[2]}});
+    }
 }
 
 // Base of the trajectory slot that step n writes (nullptr when not recording).
@@ -612,7 +691,7 @@ __device__ __forceinline__ void source3(const SimView<T>& v, int i, int j, int k
 // three sites, E^n, H^{n+1/2} and the H neighbours at y-1 and x-1.
 template <typename T>
 struct EPlane {
-    BlochIn<T> b0, b1, b2;
+    Bloch<T> b;
     T ex, ey, ez, hx, hy, hz, hzy, hzx, hyx, hxy;
 };
 
@@ -632,10 +711,8 @@ __device__ __forceinline__ void load_dense(EPlane<T>& p, const Fields<T>& f, uin
 // A whole plane: the Bloch state of its three sites and the dense part.
 template <typename T>
 __device__ __forceinline__ void load_plane(EPlane<T>& p, const Fields<T>& f, uint32_t x, uint32_t sx,
-                                           uint32_t gi, bool g, bool inx, bool iny, bool inz, int i, int j) {
-    p.b0 = bloch_load(f, 0, gi, g && inx);
-    p.b1 = bloch_load(f, 1, gi, g && iny);
-    p.b2 = bloch_load(f, 2, gi, g && inz);
+                                           uint32_t gi, bool g, int i, int j) {
+    p.b = bloch_load(f, gi, g);
     load_dense(p, f, x, sx, i, j);
 }
 
@@ -648,7 +725,7 @@ __device__ __forceinline__ void load_plane(EPlane<T>& p, const Fields<T>& f, uin
 // also writes H with streaming stores, NT).
 template <typename T, int TY, bool SPLIT>
 __device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm, int w) {
-    __shared__ double sh[TY];
+    __shared__ double sh[TY][4];
     // the member's 1/eps_r table in LDS: one gather per plane fewer on the
     // vector memory path
     __shared__ T s_ie[kMaxMat];
@@ -667,7 +744,6 @@ __device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm,
     if (i < v.nx && j < v.ny) {
         const uint32_t sx = (uint32_t)v.sx, sxy = (uint32_t)v.sxy;
         uint32_t x = (uint32_t)i + sx * (uint32_t)j + sxy * (uint32_t)kz0;
-        const bool iny0 = i >= 1, inz0 = i >= 1 && j >= 1;
         uint8_t m = ldo(v.mat, x);
         uint32_t gi = gain_index(v, bx, j, kz0, m >= kGainId, true);
         uint8_t m_n = (kz0 + 1 < kz1) ? ldo(v.mat, x + sxy) : (uint8_t)0;
@@ -688,7 +764,7 @@ __device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm,
         const LayC<T> h0 = lay_coef(v.lc, txy0), h1 = lay_coef(v.lc, txy1), h2 = lay_coef(v.lc, txy2);
         EPlane<T> P, Q;
         if constexpr (SPLIT) load_dense(P, f, x, sx, i, j);
-        else load_plane(P, f, x, sx, gi, m >= kGainId, j >= 1 && kz0 >= 1, iny0 && kz0 >= 1, inz0, i, j);
+        else load_plane(P, f, x, sx, gi, m >= kGainId, i, j);
         for (int k = kz0; k < kz1; ++k, x += sxy) {
             // software pipelining: the next plane's loads (its compact index
             // from the material byte read one plane earlier) go out before this
@@ -698,18 +774,14 @@ __device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm,
             // issue loads goes ahead of the others' arithmetic (0.3% on the
             // batch of 320^3 grids; the same in the H pass costs 0.9%)
             __builtin_amdgcn_s_setprio(2);
-            if constexpr (SPLIT) {
-                P.b0 = bloch_load(f, 0, gi, m >= kGainId && j >= 1 && k >= 1);
-                P.b1 = bloch_load(f, 1, gi, m >= kGainId && iny0 && k >= 1);
-                P.b2 = bloch_load(f, 2, gi, m >= kGainId && inz0);
-            }
+            if constexpr (SPLIT) P.b = bloch_load(f, gi, m >= kGainId);
             uint32_t gi_n = 0;
             uint8_t m_nn = 0;
             if (k + 1 < kz1) {
                 gi_n = gain_index(v, bx, j, k + 1, m_n >= kGainId, true);
                 if (k + 2 < kz1) m_nn = ldo(v.mat, x + 2u * sxy);
                 if constexpr (SPLIT) load_dense(Q, f, x + sxy, sx, i, j);
-                else load_plane(Q, f, x + sxy, sx, gi_n, m_n >= kGainId, j >= 1, iny0, inz0, i, j);
+                else load_plane(Q, f, x + sxy, sx, gi_n, m_n >= kGainId, i, j);
             }
             __builtin_amdgcn_s_setprio(0);
             const bool g = m >= kGainId;
@@ -739,28 +811,26 @@ __device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm,
             T acc = (T)0;
             {
                 const T curl = inx ? dcurl(P.hz, P.hzy, P.hy, hym) : (T)0;
-                const T en = bloch_site(v, f, 0, gi, P.ex, curl, ie, inx, g && inx, P.b0, xi[0], s0,
-                                        l0, tslot);
+                const T en = bloch_site<T, true>(v, 0, P.ex, curl, ie, inx, g && inx, P.b, xi[0], s0, l0);
                 sto(f.en[0], x, en);
                 if (tslot) sto(tslot, x, en);
                 if (inx) acc += en * en;
             }
             {
                 const T curl = iny ? dcurl(P.hx, hxm, P.hz, P.hzx) : (T)0;
-                const T en = bloch_site(v, f, 1, gi, P.ey, curl, ie, iny, g && iny, P.b1, xi[1], s1,
-                                        l1, tslot);
+                const T en = bloch_site<T, true>(v, 1, P.ey, curl, ie, iny, g && iny, P.b, xi[1], s1, l1);
                 sto(f.en[1], x, en);
                 if (tslot) sto(tslot + v.tap_e, x, en);
                 if (iny) acc += en * en;
             }
             {
                 const T curl = inz ? dcurl(P.hy, P.hyx, P.hx, P.hxy) : (T)0;
-                const T en = bloch_site(v, f, 2, gi, P.ez, curl, ie, inz, g && inz, P.b2, xi[2], s2,
-                                        l2, tslot);
+                const T en = bloch_site<T, true>(v, 2, P.ez, curl, ie, inz, g && inz, P.b, xi[2], s2, l2);
                 sto(f.en[2], x, en);
                 if (tslot) sto(tslot + 2 * v.tap_e, x, en);
                 if (inz) acc += en * en;
             }
+            if (g) bloch_store(v, f, gi, P.b, tslot);
             if (v.box_on && i >= v.box[0] && i < v.box[3] && j >= v.box[1] && j < v.box[4] &&
                 k >= v.box[2] && k < v.box[5])
                 lsum += (double)acc;
@@ -772,10 +842,7 @@ __device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm,
             gi = gi_n;
         }
     }
-    if (v.box_on) {
-        const double s = block_sum(lsum, sh);
-        if (threadIdx.x == 0 && threadIdx.y == 0) sto(v.l_part, (uint32_t)w, s);
-    }
+    if (v.box_on) tile_sums_rows<TY>(v, v.l_part, bx, by, bz, lsum, sh);
 }
 
 // The tables are separate no-alias read-only arguments, so the compiler may
@@ -790,189 +857,356 @@ __global__ void __launch_bounds__(64 * TY) k_curl_e_batch(const SimView<T>* __re
 }
 
 // ------------------------------------------------ fused step (a1 to a5)
-// Each wave owns one row (64 sites along x) of a 64 x TY tile and marches
-// along z over a segment [z0, z1) of planes; after one barrier (the material
-// tables into LDS) the waves never wait for each other and exchange no field
-// values.  Per plane k a wave forms H^{n+1/2}(k) on its own
-// row and stores it, forms again the two components of row j-1 that its E
-// update needs (Hx, Hz), takes Hy and Hz at x-1 from the next lower lane (lane
-// 0 forms them again at the tile edge), and then updates E, P and the
-// populations of its row.  H^{n+1/2}(k-1) of its own row stays in registers;
-// a segment that does not start at z = 0 first forms Hx, Hy of plane z0-1.
-// Every recomputed value is the same expression on the same inputs as where
-// it is owned (k_curl_h), so all kernel variants give bitwise identical fields.
-template <typename T, int TY>
-__device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom& gm, int w) {
-    __shared__ double sh[TY];
-    // the member's eps_r and 1/eps_r tables in LDS: two gathers per plane
-    // fewer on the vector memory path
-    __shared__ T s_ie[kMaxMat], s_eps[kMaxMat];
-    for (int q = (int)(threadIdx.x + 64 * threadIdx.y); q < kMaxMat; q += 64 * TY) {
-        s_ie[q] = gld(v.lut_inv_eps + q);
-        s_eps[q] = gld(v.lut_eps + q);
+// One pass over the fields per step.  A wave owns a tile of 16 x 4 columns
+// (lane = 16 row + column) and marches along z over a segment of planes; the
+// tiles of a plane are numbered x fastest and a workgroup takes NW of them in
+// a row, whose waves share nothing (no barrier, no LDS).  Per plane a wave forms H^{n+1/2}
+// of its sites and stores it, takes the H values that its E update needs at
+// x-1 and y-1 from the lanes beside it, and updates E, P and the populations.
+// H^{n+1/2}(k-1) stays in registers; a segment that does not start at z = 0
+// first forms Hx, Hy of plane z0-1.  The values at the tile's two edges are
+// formed again, all four kinds in one pass with one site per lane: Hx of row
+// j0-1 on lanes 0-15, Hz of row j0-1 on lanes 48-63, Hy and Hz of column i0-1
+// on lanes 16-19 and 32-35.  Every recomputed value is the same expression on
+// the same inputs as where it is owned (k_curl_h), so all kernel variants
+// give bitwise identical fields.
+
+// Value of another lane (byte index 4 * lane), and of the lane one below in a
+// row of 16 (the row's first lane keeps `first`).
+__device__ __forceinline__ int lane_read(int byte, int x) { return __builtin_amdgcn_ds_bpermute(byte, x); }
+__device__ __forceinline__ float lane_read(int byte, float x) {
+    return __int_as_float(lane_read(byte, __float_as_int(x)));
+}
+__device__ __forceinline__ double lane_read(int byte, double x) {
+    return __hiloint2double(lane_read(byte, __double2hiint(x)), lane_read(byte, __double2loint(x)));
+}
+__device__ __forceinline__ int lane_below(int first, int x) {
+    return __builtin_amdgcn_update_dpp(first, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+}
+__device__ __forceinline__ float lane_below(float first, float x) {
+    return __int_as_float(lane_below(__float_as_int(first), __float_as_int(x)));
+}
+__device__ __forceinline__ double lane_below(double first, double x) {
+    return __hiloint2double(lane_below(__double2hiint(first), __double2hiint(x)),
+                            lane_below(__double2loint(first), __double2loint(x)));
+}
+
+// Compact index of the calling lane's cell: the count of gain cells before
+// its 16-wide x segment plus the gain lanes below it in its row of 16.
+__device__ __forceinline__ uint32_t gain_index16(uint32_t base, bool g, int lane) {
+    const uint64_t mask = __ballot(g);
+    const uint32_t half = lane < 32 ? (uint32_t)mask : (uint32_t)(mask >> 32);
+    return base + __builtin_popcount(__builtin_amdgcn_ubfe(half, (uint32_t)lane & 16u, (uint32_t)lane & 15u));
+}
+
+// Dense accesses of the tile kernels: the 12 arrays lie end to end in one
+// allocation, so every access is a base in scalar registers (the allocation
+// plus a uniform byte offset: array, row, plane) plus one 32-bit lane offset.
+using GlobalBytes = MBF_GLOBAL char*;
+template <typename T>
+__device__ __forceinline__ T bld(GlobalBytes base, uint32_t lane, uint64_t uni) {
+    return *(const MBF_GLOBAL T*)((base + uni) + lane);
+}
+template <typename T>
+__device__ __forceinline__ void bst(GlobalBytes base, uint32_t lane, uint64_t uni, T x) {
+    *(MBF_GLOBAL T*)((base + uni) + lane) = x;
+}
+
+// eps_r and 1/eps_r of a material id (a few distinct lines, which stay in the
+// first-level cache: no table in LDS, so a workgroup starts without a barrier).
+template <typename T>
+struct EpsPair {
+    T eps, ie;
+};
+template <typename T>
+__device__ __forceinline__ EpsPair<T> load_eps(const SimView<T>& v, uint8_t m) {
+    typedef T pair __attribute__((ext_vector_type(2)));
+    const pair q = ((const MBF_GLOBAL pair*)v.lut_pair)[m];
+    return {q.x, q.y};
+}
+
+// Everything the H part of one plane reads: E^n and H^{n-1/2} of the wave's
+// own sites and their +x, +y, +z neighbours, and of its edge site.
+template <typename T>
+struct TilePlane {
+    T ez, exk, eyk, ezy, ezx, eyx, exy, hx, hy, hz;
+    T h, a0, a1, b0, b1;
+};
+
+// Uniform byte offsets of one step: E^n, H^{n-1/2}, E^{n+1}, H^{n+1/2} in the
+// dense allocation.
+struct TileOffs {
+    uint64_t e[3], h[3], en[3], hn[3];
+    uint32_t row, plane;
+};
+
+// A lane's edge site: its H component and the inputs of its curl (a1 - a0) -
+// (b1 - b0), a1 and b1 lying da and db bytes further on.
+struct TileEdge {
+    GlobalBytes h, a, b;
+    uint32_t da, db;
+};
+
+template <typename T>
+__device__ __forceinline__ void load_tile(TilePlane<T>& p, GlobalBytes F, const TileOffs& o, uint32_t xb, const TileEdge& e, bool on) {
+    constexpr uint32_t B = sizeof(T);
+    p.ez = bld<T>(F, xb, o.e[2]);
+    p.exk = bld<T>(F, xb, o.e[0] + o.plane);
+    p.eyk = bld<T>(F, xb, o.e[1] + o.plane);
+    p.ezy = bld<T>(F, xb, o.e[2] + o.row);
+    p.ezx = bld<T>(F, xb + B, o.e[2]);
+    p.eyx = bld<T>(F, xb + B, o.e[1]);
+    p.exy = bld<T>(F, xb, o.e[0] + o.row);
+    p.hx = bld<T>(F, xb, o.h[0]);
+    p.hy = bld<T>(F, xb, o.h[1]);
+    p.hz = bld<T>(F, xb, o.h[2]);
+    if (on) {
+        p.h = *(const MBF_GLOBAL T*)e.h;
+        p.a0 = *(const MBF_GLOBAL T*)e.a;
+        p.a1 = *(const MBF_GLOBAL T*)(e.a + e.da);
+        p.b0 = *(const MBF_GLOBAL T*)e.b;
+        p.b1 = *(const MBF_GLOBAL T*)(e.b + e.db);
     }
-    __syncthreads();
-    int bx, by, bz;
-    decode_item(gm, w, bx, by, bz);
-    const int i = bx * 64 + threadIdx.x;
-    const int j = by * TY + threadIdx.y;
+}
+
+// The lane's edge site: component c at column i, row j (on = false: it has
+// none; it then reads site 0 and its value is not used).
+struct TileLane {
+    TileEdge e;
+    int c, i, j;
+    bool on;
+};
+template <typename V>
+__device__ __forceinline__ TileLane tile_lane(const V& v, GlobalBytes F, const TileOffs& o, int lane, int i0, int j0, int ic,
+                                              int k, uint32_t B) {
+    TileLane l;
+    const bool row = lane < 16 || lane >= 48;
+    l.i = row ? ic : i0 - 1;
+    l.j = row ? j0 - 1 : j0 + (lane & 15);
+    const int c = lane < 16 ? 0 : (lane < 32 ? 1 : 2);
+    l.c = c;
+    l.on = row ? (j0 >= 1) : ((lane & 15) < 4 && i0 >= 1 && l.j < v.ny);
+    const uint32_t x = B * (l.on ? (uint32_t)l.i + (uint32_t)v.sx * (uint32_t)l.j + (uint32_t)v.sxy * (uint32_t)k : 0u);
+    const auto pick = [c](auto u0, auto u1, auto u2) { return c == 0 ? u0 : (c == 1 ? u1 : u2); };
+    l.e.h = F + (pick(o.h[0], o.h[1], o.h[2]) + x);
+    l.e.a = F + (pick(o.e[2], o.e[0], o.e[1]) + x);
+    l.e.b = F + (pick(o.e[1], o.e[2], o.e[0]) + x);
+    l.e.da = pick(o.row, o.plane, B);
+    l.e.db = pick(o.plane, B, o.row);
+    return l;
+}
+
+// H at y-1 (16 lanes below; the edge site's for the tile's first row) and at
+// x-1 (the next lower lane; the edge site's for its first column).
+template <typename T>
+struct TileNear {
+    T hx_y, hz_y, hy_x, hz_x;
+};
+template <typename T>
+__device__ __forceinline__ TileNear<T> tile_near(int lane, T hx, T hy, T hz, T edge) {
+    TileNear<T> r;
+    const int below = ((lane - 16) & 63) * 4;
+    const T hxm = lane_read(below, hx);
+    r.hx_y = lane < 16 ? edge : hxm;
+    r.hz_y = lane_read(below, lane >= 48 ? edge : hz);
+    r.hy_x = lane_below(lane_read((16 + (lane >> 4)) * 4, edge), hy);
+    r.hz_x = lane_below(lane_read((32 + (lane >> 4)) * 4, edge), hz);
+    return r;
+}
+
+// LAY: some member of the launch has an absorbing layer.
+template <typename T, int NW, bool LAY>
+__device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom& gm, int w) {
+    constexpr uint32_t B = sizeof(T);
+    const int lane = (int)threadIdx.x;
+    const int bz = w / gm.per_seg;
+    const int t = __builtin_amdgcn_readfirstlane((w - bz * gm.per_seg) * NW + (int)threadIdx.y);
+    if (t >= gm.tiles_x * gm.tiles_y) return;
+    const int i0 = t % gm.tiles_x * 16, j0 = t / gm.tiles_x * 4;
     const int64_t n = gld(&v.ctl->step);
-    const Fields<T> f = bind_fields(v, (int)(n & 1));
     T* const tslot = tap_slot(v, n);
     T wsum = (T)0;
     double lsum = 0.0;
     const int kz0 = bz * gm.zseg, kz1 = min(kz0 + gm.zseg, v.nz);
-    if (j < v.ny) {                                   // wave-uniform
-        const bool act = i < v.nx;
-        const int ic = act ? i : v.nx;                // lanes past the grid read a valid site
-        const uint32_t sx = (uint32_t)v.sx, sxy = (uint32_t)v.sxy;
-        const T* __restrict__ Ex = f.e[0];
-        const T* __restrict__ Ey = f.e[1];
-        const T* __restrict__ Ez = f.e[2];
-        const T* __restrict__ Hx0 = f.h[0];
-        const T* __restrict__ Hy0 = f.h[1];
-        const T* __restrict__ Hz0 = f.h[2];
-        const bool up = j >= 1;                       // row j-1 exists (wave-uniform)
-        const bool edge = threadIdx.x == 0 && i >= 1; // lane 0 of a tile past x = 0
-        uint32_t x = (uint32_t)ic + sx * (uint32_t)j + sxy * (uint32_t)kz0;
-        uint8_t m_next = ldo(v.mat, x);
-        uint32_t gi_next = gain_index(v, bx, j, kz0, act && m_next >= kGainId, true);
-        T ex = ldo(Ex, x), ey = ldo(Ey, x);           // E^n(k) of the row, carried along z
-        T eym = up ? ldo(Ey, x - sx) : (T)0;          // Ey^n(k) of row j-1, carried along z
-        // H^{n+1/2}(k-1) of the row: formed again at a segment start
-        T hxp = (T)0, hyp = (T)0;
-        if (kz0 >= 1) {
-            const uint32_t xp = x - sxy;
-            const T ezp = ldo(Ez, xp), eyp = ldo(Ey, xp), exp_ = ldo(Ex, xp);
-            const T cx = dcurl(ldo(Ez, xp + sx), ezp, ey, eyp);
-            const T cy = dcurl(ex, exp_, ldo(Ez, xp + 1u), ezp);
-            hxp = h_update(ldo(Hx0, xp), v.S, cx, lay_coef_h(v, 0, ic, j, kz0 - 1));
-            hyp = h_update(ldo(Hy0, xp), v.S, cy, lay_coef_h(v, 1, ic, j, kz0 - 1));
+    const Fields<T> f = bind_fields(v, (int)(n & 1));
+    const GlobalBytes F = (GlobalBytes)(char*)v.E[0][0];
+    TileOffs o;
+    {
+        const uint32_t par = (uint32_t)n & 1u;
+        const uint64_t ds = (uint64_t)v.tap_e * B;
+#pragma unroll
+        for (uint32_t c = 0; c < 3; ++c) {
+            o.e[c] = (3u * par + c) * ds;
+            o.en[c] = (3u - 3u * par + c) * ds;
+            o.h[c] = (6u + 3u * par + c) * ds;
+            o.hn[c] = (9u - 3u * par + c) * ds;
         }
-        for (int k = kz0; k < kz1; ++k, x += sxy) {
-            const uint8_t m = m_next;
-            const uint32_t gi = gi_next;
-            if (k + 1 < kz1) m_next = ldo(v.mat, x + sxy);     // one plane ahead
-            const bool g = act && m >= kGainId;
-            const bool inx = (j >= 1 && k >= 1), iny = (i >= 1 && k >= 1), inz = (i >= 1 && j >= 1);
-            const BlochIn<T> b0 = bloch_load(f, 0, gi, g && inx);
-            const BlochIn<T> b1 = bloch_load(f, 1, gi, g && iny);
-            const BlochIn<T> b2 = bloch_load(f, 2, gi, g && inz);
-            // ---- a1 on the own row
-            const T ez = ldo(Ez, x);
-            const T exk = ldo(Ex, x + sxy), eyk = ldo(Ey, x + sxy);
-            const T hx = ldo(Hx0, x), hy = ldo(Hy0, x), hz = ldo(Hz0, x);
-            const T cx = dcurl(ldo(Ez, x + sx), ez, eyk, ey);
-            const T cy = dcurl(exk, ex, ldo(Ez, x + 1u), ez);
-            const T cz = dcurl(ldo(Ey, x + 1u), ey, ldo(Ex, x + sx), ex);
-            const LayC<T> ax = lay_coef_h(v, 0, ic, j, k);
-            const LayC<T> ay = lay_coef_h(v, 1, ic, j, k);
-            const LayC<T> az = lay_coef_h(v, 2, ic, j, k);
-            const T nhx = h_update(hx, v.S, cx, ax);
-            const T nhy = h_update(hy, v.S, cy, ay);
-            const T nhz = h_update(hz, v.S, cz, az);
-            if (act) {
-                sto(f.hn[0], x, nhx);
-                sto(f.hn[1], x, nhy);
-                sto(f.hn[2], x, nhz);
-                const T eps = s_eps[m];
-                if (v.map != nullptr && k == v.map_k) plane_energy(v, i, j, eps, ex, ey, ez, nhx, nhy, nhz);
-                T acc = (T)0;
-                if (j >= 1 && k >= 1) acc += eps * ex * ex;
-                if (i >= 1 && k >= 1) acc += eps * ey * ey;
-                if (i >= 1 && j >= 1) acc += eps * ez * ez;
-                if (i >= 1) acc += hx * nhx;
-                if (j >= 1) acc += hy * nhy;
-                if (k >= 1) acc += hz * nhz;
-                wsum += (T)0.5 * acc;
-            }
-            // ---- Hx, Hz of row j-1 (its owner's expressions)
-            T nhx_m = (T)0, nhz_m = (T)0, eymk = (T)0;
-            if (up) {
-                const uint32_t xm = x - sx;
-                const T ezm = ldo(Ez, xm), exm = ldo(Ex, xm);
-                eymk = ldo(Ey, xm + sxy);
-                const T cxm = dcurl(ez, ezm, eymk, eym);
-                const T czm = dcurl(ldo(Ey, xm + 1u), eym, ex, exm);
-                nhx_m = h_update(ldo(Hx0, xm), v.S, cxm, lay_coef_h(v, 0, ic, j - 1, k));
-                nhz_m = h_update(ldo(Hz0, xm), v.S, czm, lay_coef_h(v, 2, ic, j - 1, k));
-            }
-            // ---- Hy, Hz at x-1 of the own row
-            T nhy_l = __shfl_up(nhy, 1, 64);
-            T nhz_l = __shfl_up(nhz, 1, 64);
-            if (edge) {
-                const uint32_t xl = x - 1u;
-                const T exl = ldo(Ex, xl), eyl = ldo(Ey, xl), ezl = ldo(Ez, xl);
-                const T cyl = dcurl(ldo(Ex, xl + sxy), exl, ez, ezl);
-                const T czl = dcurl(ey, eyl, ldo(Ex, xl + sx), exl);
-                nhy_l = h_update(ldo(Hy0, xl), v.S, cyl, lay_coef_h(v, 1, i - 1, j, k));
-                nhz_l = h_update(ldo(Hz0, xl), v.S, czl, lay_coef_h(v, 2, i - 1, j, k));
-            }
-            // ---- a2-a5 on the own row
-            if (act) {
-                const T ie = s_ie[m];
-                T xi[3] = {(T)0, (T)0, (T)0};
-                if (g && v.noise && (inx || iny || inz)) {
-                    const uint32_t cell = (uint32_t)(i + v.nx * (j + v.ny * k));
-                    noise3(v, cell, (uint32_t)n, xi);
-                }
-                T s0, s1, s2;
-                source3(v, i, j, k, n, s0, s1, s2);
-                T acc = (T)0;
-                {
-                    const T curl = inx ? dcurl(nhz, nhz_m, nhy, hyp) : (T)0;
-                    const T en = bloch_site(v, f, 0, gi, ex, curl, ie, inx, g && inx, b0, xi[0], s0,
-                                            lay_coef_e(v, 0, i, j, k), tslot);
-                    sto(f.en[0], x, en);
-                    if (tslot) sto(tslot, x, en);
-                    if (inx) acc += en * en;
-                }
-                {
-                    const T curl = iny ? dcurl(nhx, hxp, nhz, nhz_l) : (T)0;
-                    const T en = bloch_site(v, f, 1, gi, ey, curl, ie, iny, g && iny, b1, xi[1], s1,
-                                            lay_coef_e(v, 1, i, j, k), tslot);
-                    sto(f.en[1], x, en);
-                    if (tslot) sto(tslot + v.tap_e, x, en);
-                    if (iny) acc += en * en;
-                }
-                {
-                    const T curl = inz ? dcurl(nhy, nhy_l, nhx, nhx_m) : (T)0;
-                    const T en = bloch_site(v, f, 2, gi, ez, curl, ie, inz, g && inz, b2, xi[2], s2,
-                                            lay_coef_e(v, 2, i, j, k), tslot);
-                    sto(f.en[2], x, en);
-                    if (tslot) sto(tslot + 2 * v.tap_e, x, en);
-                    if (inz) acc += en * en;
-                }
-                if (v.box_on && i >= v.box[0] && i < v.box[3] && j >= v.box[1] && j < v.box[4] &&
-                    k >= v.box[2] && k < v.box[5])
-                    lsum += (double)acc;
-            }
-            hxp = nhx;
-            hyp = nhy;
-            ex = exk;
-            ey = eyk;
-            eym = eymk;
-            if (k + 1 < kz1) gi_next = gain_index(v, bx, j, k + 1, act && m_next >= kGainId, true);
+        o.row = (uint32_t)v.sx * B;
+        o.plane = (uint32_t)v.sxy * B;
+    }
+    const int i = i0 + (lane & 15), j = j0 + (lane >> 4);
+    const bool act = i < v.nx && j < v.ny;
+    const int ic = min(i, v.nx - 1), jc = min(j, v.ny - 1);   // lanes past the grid read a valid site
+    uint32_t x = (uint32_t)ic + (uint32_t)v.sx * (uint32_t)jc + (uint32_t)v.sxy * (uint32_t)kz0;
+    const TileLane tl = tile_lane(v, F, o, lane, i0, j0, ic, kz0, B);
+    TileEdge e = tl.e;
+    const int ec = tl.c;
+    // ---- layer coefficients of the three E-sites, the three H-sites and
+    // the edge site: the x and y parts of their table entries stay fixed
+    // along the march, so the pairs are loaded again only on the planes
+    // of the z layers and on the first plane after them
+    uint32_t tx0 = 0u, tx1 = 0u, ty0 = 0u, ty1 = 0u, tg = 0u;
+    LayC<T> l0{(T)1, (T)1}, l1 = l0, l2 = l0, ax = l0, ay = l0, az = l0, ag = l0;
+    bool zlay = true;
+    if constexpr (LAY) {
+        if (v.has_layer) {
+            tx0 = lay_part(v, 0, 0, ic);
+            tx1 = lay_part(v, 0, 1, ic);
+            ty0 = lay_part(v, 1, 0, jc);
+            ty1 = lay_part(v, 1, 1, jc);
+            if (tl.on) tg = lay_part(v, 0, ec != 0, tl.i) + lay_part(v, 1, ec != 1, tl.j);
+        } else {
+            zlay = false;
         }
     }
-    const double ws = block_sum((double)wsum, sh);
-    __syncthreads();
-    const double ls = v.box_on ? block_sum(lsum, sh) : 0.0;
-    if (threadIdx.x == 0 && threadIdx.y == 0) {
-        sto(v.e_part, (uint32_t)w, ws);
-        if (v.box_on) sto(v.l_part, (uint32_t)w, ls);
+    // ---- material and compact index of the first two planes
+    const uint32_t nb16 = ((uint32_t)v.nx + 15u) >> 4, pseg = nb16 * (uint32_t)v.ny;
+    uint32_t seg = (uint32_t)(i0 >> 4) + nb16 * (uint32_t)jc + pseg * (uint32_t)kz0;
+    uint8_t m = ldo(v.mat, x), m_n = 0;
+    uint32_t gi = ldo(v.seg16, seg), s_n = 0;
+    if (kz0 + 1 < kz1) {
+        m_n = ldo(v.mat, x + (uint32_t)v.sxy);
+        s_n = ldo(v.seg16, seg + pseg);
     }
+    T ex = bld<T>(F, x * B, o.e[0]), ey = bld<T>(F, x * B, o.e[1]);   // E^n(k), carried along z
+    // H^{n+1/2}(k-1): formed again at a segment start
+    T hxp = (T)0, hyp = (T)0;
+    if (kz0 >= 1) {
+        const uint32_t xp = x * B - o.plane;
+        const T ezp = bld<T>(F, xp, o.e[2]), eyp = bld<T>(F, xp, o.e[1]), exp_ = bld<T>(F, xp, o.e[0]);
+        const T cx = dcurl(bld<T>(F, xp, o.e[2] + o.row), ezp, ey, eyp);
+        const T cy = dcurl(ex, exp_, bld<T>(F, xp + B, o.e[2]), ezp);
+        hxp = h_update(bld<T>(F, xp, o.h[0]), v.S, cx, lay_coef_h(v, 0, ic, jc, kz0 - 1));
+        hyp = h_update(bld<T>(F, xp, o.h[1]), v.S, cy, lay_coef_h(v, 1, ic, jc, kz0 - 1));
+    }
+    TilePlane<T> D;
+    D.h = D.a0 = D.a1 = D.b0 = D.b1 = (T)0;
+    load_tile(D, F, o, x * B, e, tl.on);
+    gi = gain_index16(gi, act && m >= kGainId, lane);
+    EpsPair<T> mp = load_eps(v, m), mp_n{(T)1, (T)1};
+    for (int k = kz0; k < kz1; ++k, x += (uint32_t)v.sxy, seg += pseg) {
+        const bool g = act && m >= kGainId;
+        const bool inx = (j >= 1 && k >= 1), iny = (i >= 1 && k >= 1), inz = (i >= 1 && j >= 1);
+        const uint32_t xb = x * B;
+        // the plane's Bloch state, and the material two planes ahead
+        Bloch<T> b = bloch_load(f, gi, g);
+        uint8_t m_nn = 0;
+        uint32_t s_nn = 0;
+        if (k + 1 < kz1) mp_n = load_eps(v, m_n);
+        if (k + 2 < kz1) {
+            m_nn = ldo(v.mat, x + 2u * (uint32_t)v.sxy);
+            s_nn = ldo(v.seg16, seg + 2u * pseg);
+        }
+        if constexpr (LAY) {
+            const bool in_z = v.has_layer && (k < v.lay_kz[0] || k >= v.lay_kz[1]);
+            if (in_z || zlay) {
+                const uint32_t tz0 = lay_part(v, 2, 0, k), tz1 = lay_part(v, 2, 1, k);
+                l0 = lay_coef(v.lc, tx1 + ty0 + tz0);
+                l1 = lay_coef(v.lc, tx0 + ty1 + tz0);
+                l2 = lay_coef(v.lc, tx0 + ty0 + tz1);
+                ax = lay_coef(v.lc, tx0 + ty1 + tz1);
+                ay = lay_coef(v.lc, tx1 + ty0 + tz1);
+                az = lay_coef(v.lc, tx1 + ty1 + tz0);
+                ag = lay_coef(v.lc, tg + (ec == 2 ? tz0 : tz1));
+                zlay = in_z;
+            }
+        }
+        // ---- a1 on the own sites and the edge site
+        const T ez = D.ez, exk = D.exk, eyk = D.eyk;
+        const T nhx = h_update(D.hx, v.S, dcurl(D.ezy, ez, eyk, ey), ax);
+        const T nhy = h_update(D.hy, v.S, dcurl(exk, ex, D.ezx, ez), ay);
+        const T nhz = h_update(D.hz, v.S, dcurl(D.eyx, ey, D.exy, ex), az);
+        const T edge = h_update(D.h, v.S, dcurl(D.a1, D.a0, D.b1, D.b0), ag);
+        if (act) {
+            bst(F, xb, o.hn[0], nhx);
+            bst(F, xb, o.hn[1], nhy);
+            bst(F, xb, o.hn[2], nhz);
+        }
+        const T eps = mp.eps, ie = mp.ie;
+        if (v.map != nullptr && k == v.map_k && act) plane_energy(v, i, j, eps, ex, ey, ez, nhx, nhy, nhz);
+        {
+            T acc = (T)0;
+            if (inx) acc += eps * ex * ex;
+            if (iny) acc += eps * ey * ey;
+            if (inz) acc += eps * ez * ez;
+            if (i >= 1) acc += D.hx * nhx;
+            if (j >= 1) acc += D.hy * nhy;
+            if (k >= 1) acc += D.hz * nhz;
+            wsum += act ? (T)0.5 * acc : (T)0;
+        }
+        // ---- the next plane's loads go out before the E part
+        if (k + 1 < kz1) {
+            e.h += o.plane;
+            e.a += o.plane;
+            e.b += o.plane;
+            load_tile(D, F, o, (x + (uint32_t)v.sxy) * B, e, tl.on);
+        }
+        const TileNear<T> nb = tile_near(lane, nhx, nhy, nhz, edge);
+        // ---- a2-a5 on the own sites
+        T xi[3] = {(T)0, (T)0, (T)0};
+        if (v.noise) {
+            const uint32_t cell = (uint32_t)(i + v.nx * (j + v.ny * k));
+            noise3(v, cell, (uint32_t)n, xi);
+        }
+        T s0, s1, s2;
+        source3(v, i, j, k, n, s0, s1, s2);
+        T acc = (T)0;
+        {
+            const T en = bloch_site<T, LAY>(v, 0, ex, dcurl(nhz, nb.hz_y, nhy, hyp), ie, inx, g && inx, b, xi[0], s0, l0);
+            if (act) bst(F, xb, o.en[0], en);
+            if (tslot && act) sto(tslot, x, en);
+            if (inx) acc += en * en;
+        }
+        {
+            const T en = bloch_site<T, LAY>(v, 1, ey, dcurl(nhx, hxp, nhz, nb.hz_x), ie, iny, g && iny, b, xi[1], s1, l1);
+            if (act) bst(F, xb, o.en[1], en);
+            if (tslot && act) sto(tslot + v.tap_e, x, en);
+            if (iny) acc += en * en;
+        }
+        {
+            const T en = bloch_site<T, LAY>(v, 2, ez, dcurl(nhy, nb.hy_x, nhx, nb.hx_y), ie, inz, g && inz, b, xi[2], s2, l2);
+            if (act) bst(F, xb, o.en[2], en);
+            if (tslot && act) sto(tslot + 2 * v.tap_e, x, en);
+            if (inz) acc += en * en;
+        }
+        if (g) bloch_store(v, f, gi, b, tslot);
+        if (v.box_on && act && i >= v.box[0] && i < v.box[3] && j >= v.box[1] && j < v.box[4] &&
+            k >= v.box[2] && k < v.box[5])
+            lsum += (double)acc;
+        hxp = nhx;
+        hyp = nhy;
+        ex = exk;
+        ey = eyk;
+        m = m_n;
+        m_n = m_nn;
+        mp = mp_n;
+        if (k + 1 < kz1) gi = gain_index16(s_n, act && m >= kGainId, lane);
+        s_n = s_nn;
+    }
+    const uint32_t slot = (uint32_t)(t + gm.tiles_x * gm.tiles_y * bz);
+    tile_sum_wave(v.e_part, slot, (double)wsum);
+    if (v.box_on) tile_sum_wave(v.l_part, slot, lsum);
 }
 
 // The tables are separate no-alias read-only arguments, so the compiler may
 // keep the member's view in scalar registers across the kernel's stores.
-template <typename T, int TY>
-__global__ void __launch_bounds__(64 * TY) k_step_fused_batch(const SimView<T>* __restrict__ views,
+template <typename T, int NW, bool LAY>
+__global__ void __launch_bounds__(64 * NW) k_step_fused_batch(const SimView<T>* __restrict__ views,
                                                 const Geom* __restrict__ geoms,
                                                 const uint32_t* __restrict__ items, int nitems, int remap) {
     int r, w;
     batch_item(items, nitems, remap, r, w);
-    step_fused_body<T, TY>(views[r], geoms[r], w);
+    step_fused_body<T, NW, LAY>(views[r], geoms[r], w);
 }
 
 
@@ -985,7 +1219,7 @@ __global__ void __launch_bounds__(64 * TY) k_step_fused_batch(const SimView<T>* 
 // by one lane with device-scope atomics; the last workgroup to leave zeroes
 // all nine counters (eight queues and the leave count) for the next launch.
 // Every workgroup leaves once its queue is empty, so the grid always drains.
-template <typename T, int TY>
+template <typename T, int TY, bool LAY>
 __global__ void __launch_bounds__(64 * TY) k_step_fused_persist(const SimView<T>* __restrict__ views,
                                                               const Geom* __restrict__ geoms,
                                                               const uint32_t* __restrict__ items, int nitems,
@@ -1001,7 +1235,7 @@ __global__ void __launch_bounds__(64 * TY) k_step_fused_persist(const SimView<T>
         if (p >= nitems) break;
         const uint32_t e = items[p];
         const int r = (int)(e >> 24), w = (int)(e & 0xFFFFFFu);
-        step_fused_body<T, TY>(views[r], geoms[r], w);
+        step_fused_body<T, TY, LAY>(views[r], geoms[r], w);
     }
     if (lead && atomicAdd(queue + 8, 1u) == gridDim.x - 1u) {
         for (int q = 0; q < 9; ++q) atomicExch(queue + q, 0u);
@@ -1026,7 +1260,7 @@ __global__ void __launch_bounds__(64 * TY) k_step_fused_persist(const SimView<T>
 // of plane z0-1; so every variant gives bitwise identical fields.
 template <typename T, int TY>
 __device__ __forceinline__ void step_lds_body(const SimView<T>& v, const Geom& gm, int w) {
-    __shared__ double sh[TY];
+    __shared__ double sh[TY][4];
     __shared__ T s_ie[kMaxMat], s_eps[kMaxMat];
     __shared__ T s_hx[2][TY][64], s_hz[2][TY][64];
     for (int q = (int)(threadIdx.x + 64 * threadIdx.y); q < kMaxMat; q += 64 * TY) {
@@ -1090,7 +1324,7 @@ __device__ __forceinline__ void step_lds_body(const SimView<T>& v, const Geom& g
         T nhy_l = (T)0, nhz_l = (T)0;                 // Hy, Hz of column i0-1 (lane 0)
         T exk = (T)0, eyk = (T)0, ezk = (T)0;         // E^n(k+1) of the row
         T eymk = (T)0, exlk = (T)0;
-        BlochIn<T> b0{}, b1{}, b2{};
+        Bloch<T> b{};
         bool g = false;
         const bool inx = (j >= 1 && k >= 1), iny = (i >= 1 && k >= 1), inz = (i >= 1 && j >= 1);
         if (row) {
@@ -1098,9 +1332,7 @@ __device__ __forceinline__ void step_lds_body(const SimView<T>& v, const Geom& g
             gi = gi_next;
             if (k + 1 < kz1) m_next = ldo(v.mat, x + sxy);
             g = act && m >= kGainId;
-            b0 = bloch_load(f, 0, gi, g && inx);
-            b1 = bloch_load(f, 1, gi, g && iny);
-            b2 = bloch_load(f, 2, gi, g && inz);
+            b = bloch_load(f, gi, g);
             // ---- a1 on the own row (the H pass's expressions)
             exk = ldo(Ex, x + sxy);
             eyk = ldo(Ey, x + sxy);
@@ -1173,28 +1405,29 @@ __device__ __forceinline__ void step_lds_body(const SimView<T>& v, const Geom& g
                 T acc = (T)0;
                 {
                     const T curl = inx ? dcurl(nhz, hz_jm, nhy, hyp) : (T)0;
-                    const T en = bloch_site(v, f, 0, gi, ex, curl, ie, inx, g && inx, b0, xi[0], s0,
-                                            lay_coef_e(v, 0, i, j, k), tslot);
+                    const T en = bloch_site<T, true>(v, 0, ex, curl, ie, inx, g && inx, b, xi[0], s0,
+                                                     lay_coef_e(v, 0, i, j, k));
                     sto(f.en[0], x, en);
                     if (tslot) sto(tslot, x, en);
                     if (inx) acc += en * en;
                 }
                 {
                     const T curl = iny ? dcurl(nhx, hxp, nhz, hz_im) : (T)0;
-                    const T en = bloch_site(v, f, 1, gi, ey, curl, ie, iny, g && iny, b1, xi[1], s1,
-                                            lay_coef_e(v, 1, i, j, k), tslot);
+                    const T en = bloch_site<T, true>(v, 1, ey, curl, ie, iny, g && iny, b, xi[1], s1,
+                                                     lay_coef_e(v, 1, i, j, k));
                     sto(f.en[1], x, en);
                     if (tslot) sto(tslot + v.tap_e, x, en);
                     if (iny) acc += en * en;
                 }
                 {
                     const T curl = inz ? dcurl(nhy, hy_im, nhx, hx_jm) : (T)0;
-                    const T en = bloch_site(v, f, 2, gi, ez, curl, ie, inz, g && inz, b2, xi[2], s2,
-                                            lay_coef_e(v, 2, i, j, k), tslot);
+                    const T en = bloch_site<T, true>(v, 2, ez, curl, ie, inz, g && inz, b, xi[2], s2,
+                                                     lay_coef_e(v, 2, i, j, k));
                     sto(f.en[2], x, en);
                     if (tslot) sto(tslot + 2 * v.tap_e, x, en);
                     if (inz) acc += en * en;
                 }
+                if (g) bloch_store(v, f, gi, b, tslot);
                 if (v.box_on && i >= v.box[0] && i < v.box[3] && j >= v.box[1] && j < v.box[4] &&
                     k >= v.box[2] && k < v.box[5])
                     lsum += (double)acc;
@@ -1209,13 +1442,8 @@ __device__ __forceinline__ void step_lds_body(const SimView<T>& v, const Geom& g
             if (k + 1 < kz1) gi_next = gain_index(v, bx, j, k + 1, act && m_next >= kGainId, true);
         }
     }
-    const double ws = block_sum((double)wsum, sh);
-    __syncthreads();
-    const double ls = v.box_on ? block_sum(lsum, sh) : 0.0;
-    if (threadIdx.x == 0 && threadIdx.y == 0) {
-        sto(v.e_part, (uint32_t)w, ws);
-        if (v.box_on) sto(v.l_part, (uint32_t)w, ls);
-    }
+    tile_sums_rows<TY>(v, v.e_part, bx, by, bz, (double)wsum, sh);
+    if (v.box_on) tile_sums_rows<TY>(v, v.l_part, bx, by, bz, lsum, sh);
 }
 
 template <typename T, int TY>
@@ -1403,40 +1631,38 @@ __global__ void __launch_bounds__(64) k_init_pop(SimView<T> v, T n1, T n2, T n3)
     const uint32_t gi = gain_index(v, (int)blockIdx.x, j, k, g, true);
     if (!g) return;
     const bool in[3] = {j >= 1 && k >= 1, i >= 1 && k >= 1, i >= 1 && j >= 1};
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        v.N[0][c][gi] = in[c] ? n1 : (T)0;
-        v.N[1][c][gi] = in[c] ? n2 : (T)0;
-        v.N[2][c][gi] = in[c] ? n3 : (T)0;
-    }
+    const auto put = [&](T* base, T x) { st3(base, gi, in[0] ? x : (T)0, in[1] ? x : (T)0, in[2] ? x : (T)0); };
+    put(v.N[0], n1);
+    put(v.N[1], n2);
+    put(v.N[2], n3);
 }
 
-// Record the current state (step n = ctl->step) into trajectory slot
-// n - ctl->tap_base: E^n, P^n - P^{n-1} and N1 - N2, as the E pass does for
-// the states it produces.  Grid (nbx, ny, nz) of one wave each.
+// Begin a trajectory at the current state (step `base` = ctl->step): slot 0
+// holds E^n, P^n - P^{n-1} and N1 - N2, as the E pass writes them for the
+// states it produces.  Grid (nbx, ny, nz) of one wave each.
 template <typename T>
-__global__ void __launch_bounds__(64) k_tap_state(SimView<T> v) {
+__global__ void __launch_bounds__(64) k_tap_state(SimView<T> v, int64_t base) {
+    if (blockIdx.x + blockIdx.y + blockIdx.z + threadIdx.x == 0) v.ctl->tap_base = base;
     const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y, k = blockIdx.z;
     const bool act = i < v.nx;
     const uint32_t x = (uint32_t)(act ? i : 0) + (uint32_t)v.sx * j + (uint32_t)v.sxy * k;
     const bool g = act && v.mat[x] >= kGainId;
     const uint32_t gi = gain_index(v, (int)blockIdx.x, j, k, g, true);
     if (!act) return;
-    const int64_t n = gld(&v.ctl->step);
-    const Fields<T> f = bind_fields(v, (int)(n & 1));
-    T* slot = v.tap + (n - gld(&v.ctl->tap_base)) * v.tap_stride;
+    const Fields<T> f = bind_fields(v, (int)(base & 1));
+    T* slot = v.tap;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        sto(slot + c * v.tap_e, x, ldo(f.e[c], x));
-        if (g) {
-            sto(slot + 3 * v.tap_e + c * v.tap_c, gi, ldo(f.p[c], gi) - ldo(f.q[c], gi));
-            sto(slot + 3 * v.tap_e + 3 * v.tap_c + c * v.tap_c, gi, ldo(f.n1[c], gi) - ldo(f.n2[c], gi));
-        }
-    }
+    for (int c = 0; c < 3; ++c) sto(slot + c * v.tap_e, x, ldo(f.e[c], x));
+    if (!g) return;
+    const auto put = [gi](T* base, const Vec3<T>& a, const Vec3<T>& b) {
+        st3(base, gi, a.c[0] - b.c[0], a.c[1] - b.c[1], a.c[2] - b.c[2]);
+    };
+    put(slot + 3 * v.tap_e, ld3(f.p, gi), ld3(f.q, gi));
+    put(slot + 3 * v.tap_e + 3 * v.tap_c, ld3(f.n1, gi), ld3(f.n2, gi));
 }
 
-// Dense copy of one compact Bloch-state array in the packed exchange layout
-// (rows of nx+1 values, zero off the gain cells and on the upper walls, which
+// Dense copy of one component of a compact Bloch-state array (src: its value
+// in the first entry) in the packed exchange layout (rows of nx+1 values, zero off the gain cells and on the upper walls, which
 // the caller clears first), and the reverse.  Grid (nbx, ny, nz).
 template <typename T>
 __global__ void __launch_bounds__(64) k_gather(SimView<T> v, const T* __restrict__ src, T* __restrict__ dst) {
@@ -1446,7 +1672,7 @@ __global__ void __launch_bounds__(64) k_gather(SimView<T> v, const T* __restrict
     const bool g = act && v.mat[act ? x : 0u] >= kGainId;
     const uint32_t gi = gain_index(v, (int)blockIdx.x, j, k, g, true);
     if (act)
-        dst[(int64_t)i + (int64_t)(v.nx + 1) * (j + (int64_t)(v.ny + 1) * k)] = g ? src[gi] : (T)0;
+        dst[(int64_t)i + (int64_t)(v.nx + 1) * (j + (int64_t)(v.ny + 1) * k)] = g ? src[(uint64_t)gi * 3u] : (T)0;
 }
 
 template <typename T>
@@ -1456,7 +1682,7 @@ __global__ void __launch_bounds__(64) k_scatter(SimView<T> v, const T* __restric
     const uint32_t x = (uint32_t)i + (uint32_t)v.sx * j + (uint32_t)v.sxy * k;
     const bool g = act && v.mat[act ? x : 0u] >= kGainId;
     const uint32_t gi = gain_index(v, (int)blockIdx.x, j, k, g, true);
-    if (g) dst[gi] = src[(int64_t)i + (int64_t)(v.nx + 1) * (j + (int64_t)(v.ny + 1) * k)];
+    if (g) dst[(uint64_t)gi * 3u] = src[(int64_t)i + (int64_t)(v.nx + 1) * (j + (int64_t)(v.ny + 1) * k)];
 }
 
 }  // namespace mbf

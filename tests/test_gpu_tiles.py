@@ -1,0 +1,49 @@
+"""The single-pass tile kernel (16 x 4 columns a wave) at the edges of its
+tiles, rows and segments: fields against the two passes bit for bit, and the
+energy and loss sums, whose partials do not follow a kernel's workgroups."""
+import numpy as np
+import pytest
+
+from paper_0809_1547_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(n, bc, precision, variant, tile_y, zseg, steps=37):
+    from paper_0809_1547_amd import mbf
+    eps, gain = I.voxelize(I.rsa_pack(n, seed=3, count=1, radius=0.3 * min(n)))
+    sim = mbf.Sim(n, boundary=bc, precision=precision, seed=7, E_sp=1e-2, energy_history=steps)
+    sim.set_tuning(variant, tile_y=tile_y, zseg=zseg, xcd_remap=2)
+    sim.set_material(eps, gain)
+    sim.set_pump(2e24)
+    sim.set_source(2, n[0] // 2, n[1] // 2, n[2] // 2, amp=0.5)
+    sim.set_loss_box((0, 0, 0), (max(1, n[0] - 1), n[1], n[2]))
+    sim.set_plane_monitor(n[2] // 2)
+    f = I.random_fields(n, seed=5, amplitude=1e-2)
+    for c in range(3):
+        sim.set_field(c, f[c])
+    sim.step(steps)
+    out = [sim.field(q) for q in range(21)]
+    sums = [np.array(sim.energy()), np.array(sim.loss()), sim.energy_history(), sim.plane_monitor()[0]]
+    one_kernel = sim.step_bytes()[2] == 0.0
+    sim.close()
+    return out, sums, one_kernel
+
+
+# sides around the tile (16, 4), the workgroup (64) and the segment (zseg)
+@pytest.mark.parametrize("n", [(2, 2, 2), (15, 3, 5), (16, 4, 2), (17, 5, 3), (63, 8, 4), (64, 9, 7), (65, 7, 9), (130, 6, 3)])
+@pytest.mark.parametrize("bc,precision", [("pec", "fp32"), ("absorb", "fp32"), (("mur", "pec", "absorb"), "fp32"),
+                                          ("absorb", "fp64")])
+def test_tile_kernel_equals_the_two_passes(n, bc, precision):
+    ref, ref_sums, one = _run(n, bc, precision, "two_pass_split", 4, 2)
+    assert not one
+    for variant, tile_y, zseg, same_sums in (("fused", 8, 2, True), ("fused", 4, 2, True),
+                                             ("fused_persistent", 16, 2, True), ("fused", 4, 1, False)):
+        got, sums, one = _run(n, bc, precision, variant, tile_y, zseg)
+        assert one
+        for q, (a, b) in enumerate(zip(ref, got)):
+            assert np.array_equal(a, b), (variant, tile_y, zseg, q)
+        assert np.array_equal(ref_sums[3], sums[3])
+        if same_sums:
+            for a, b in zip(ref_sums, sums):
+                assert np.array_equal(a, b), (variant, tile_y, zseg)
