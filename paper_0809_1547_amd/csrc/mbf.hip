@@ -367,10 +367,20 @@ double state_bytes(const mbf_handle* h) {
     return (double)h->nsite * (12.0 * h->esz + 1.0) + 15.0 * (double)h->glen * h->esz;
 }
 
-// Whether a launch under schedule t runs the tile kernel (one pass).
+// Whether a launch under schedule t over members of `bytes` state in all runs
+// the tile kernel (one pass): the fused variants do, and so does the two-pass
+// schedule while the state stays in the 256 MB last-level cache (its fields
+// and monitors are the same bit for bit).  Per step, two passes and one, the
+// best segment length of each (us): FP32 32^3 13.2 and 9.0, 64^3 15.8 and 13.5,
+// 96^3 34.6 and 26.3, 128^3 (200 MB) 57.9 and 49.1, 136^3 (240 MB) 72.1 and
+// 58.6; FP64 96^3 63.3 and 47.9, 112^3 (250 MB) 85.8 and 68.4.  Beyond the
+// cache the tiles' half lines are read and written more than once and the two
+// passes stream faster (144^3, 280 MB: 91.6 and 88.9, with layers 96.5 and
+// 96.9; 152^3 100.5 and 112.8, 160^3 117.3 and 130.8).
+constexpr double kCacheBytes = 250e6;
 bool tile_schedule(const mbf_tuning& t, double bytes) {
-    (void)bytes;
-    return t.variant == MBF_VARIANT_FUSED || t.variant == MBF_VARIANT_FUSED_PERSISTENT;
+    return t.variant == MBF_VARIANT_FUSED || t.variant == MBF_VARIANT_FUSED_PERSISTENT ||
+           (t.variant == MBF_VARIANT_TWO_PASS && t.tile_y >= 4 && bytes <= kCacheBytes);
 }
 bool uses_tiles(const mbf_handle* h) { return tile_schedule(h->tun, state_bytes(h)); }
 
@@ -2928,8 +2938,6 @@ int set_tap(mbf_handle* h, void* buffer, int64_t base) {
     return MBF_OK;
 }
 
-constexpr double kAdjTileBytes = 128e6;   // see adjoint_run
-
 template <typename T>
 int adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int mem_kind, double* grad_Na,
                 double* loss) {
@@ -2947,15 +2955,15 @@ int adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int mem_ki
     if (!rc) rc = snap_alloc(h, B.end);
     if (rc) return rc;
     // reverse steps in one pass while their state (twice E and H, the compact
-    // arrays, two trajectory slots, the gradient) takes at most half of the
-    // 256 MB last-level cache, past which the trajectory streams.  A whole run
-    // (forward, recomputation, reverse) in us a step, two kernels and one:
-    // 48^3 62.8 and 41, 64^3 70 and 59, 80^3 96 and 87, 96^3 (111 MB) 128 and
-    // 126, 112^3 (174 MB) 176 and 185.  One plane a wave: on such grids two or
-    // four leave the device waves short (96^3: 124.9, 126.2 and 128.9 for 1, 2
-    // and 4 planes)
+    // arrays, two trajectory slots, the gradient) stays in the last-level
+    // cache.  A whole run (forward, recomputation, reverse) in us a step, two
+    // kernels and one: 48^3 62.8 and 38.4, 64^3 70 and 53.6, 96^3 (130 MB) 118
+    // and 109.9, 112^3 (206 MB) 163.6 and 158.6, 128^3 (307 MB) 237.6 and 243.
+    // One plane a wave: two or four leave such grids short of waves (96^3:
+    // 124.9, 126.2 and 128.9 for 1, 2 and 4 planes, with the compact arrays in
+    // another layout)
     const double adj_bytes = (double)esz * (12.0 * h->nsite + 15.0 * h->glen) + 2.0 * (double)slot + 8.0 * (double)ncell;
-    const bool tiles = adj_bytes <= kAdjTileBytes;
+    const bool tiles = adj_bytes <= kCacheBytes;
     mbf::Geom gm{};
     gm.tiles_x = tiles ? (c.nx + 15) / 16 : h->nbx;
     gm.tiles_y = (c.ny + 3) / 4;

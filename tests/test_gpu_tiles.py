@@ -37,8 +37,9 @@ def _run(n, bc, precision, variant, tile_y, zseg, steps=37):
 def test_tile_kernel_equals_the_two_passes(n, bc, precision):
     ref, ref_sums, one = _run(n, bc, precision, "two_pass_split", 4, 2)
     assert not one
-    for variant, tile_y, zseg, same_sums in (("fused", 8, 2, True), ("fused", 4, 2, True),
-                                             ("fused_persistent", 16, 2, True), ("fused", 4, 1, False)):
+    for variant, tile_y, zseg, same_sums in (("two_pass", 4, 2, True), ("fused", 8, 2, True), ("fused", 2, 2, True),
+                                             ("fused_persistent", 16, 2, True), ("two_pass", 16, 3, False),
+                                             ("fused", 4, 1, False)):
         got, sums, one = _run(n, bc, precision, variant, tile_y, zseg)
         assert one
         for q, (a, b) in enumerate(zip(ref, got)):
@@ -47,3 +48,21 @@ def test_tile_kernel_equals_the_two_passes(n, bc, precision):
         if same_sums:
             for a, b in zip(ref_sums, sums):
                 assert np.array_equal(a, b), (variant, tile_y, zseg)
+
+
+def test_two_pass_schedule_leaves_the_tile_kernel_beyond_the_cache():
+    # 136^3 (240 MB of state) takes one kernel, 144^3 (280 MB) two
+    from paper_0809_1547_amd import mbf
+    for n, want in ((136, True), (144, False)):
+        eps, gain = I.homogeneous(n, 1.0, 1)
+        gain[:, :, : int(0.4 * n)] = 0
+        sim = mbf.Sim(n)
+        sim.set_tuning("two_pass", tile_y=4, zseg=4)
+        sim.set_material(eps, gain)
+        sim.set_pump(2e24)
+        assert (sim.step_bytes()[2] == 0.0) == want
+        sim.set_tuning("two_pass", tile_y=2, zseg=4)
+        assert sim.step_bytes()[2] > 0.0
+        sim.step(2)
+        sim.sync()
+        sim.close()
