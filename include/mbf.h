@@ -456,7 +456,7 @@ int mbf_adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int me
  * whose positive bound state exists for E > 1, with E = (p - 1)/(kappa
  * sqrt(p)) (Eq. ee, p the pump relative to the high-Q loss) and the
  * threshold E = 1 at p_th = 1 + kappa^2/2 + kappa sqrt(4 + kappa^2)/2.
- * mbf_gp_solve solves it for n_E eigenvalues at once (one workgroup each) on
+ * mbf_gp_solve solves it for n_E eigenvalues at once (one wave each) on
  * M interior points tau_i = -L + (i+1) h, h = 2L/(M+1), phi(+-L) = 0,
  * second differences: a semi-implicit gradient flow from the near-threshold
  * Gaussian (E < 3) or the Thomas-Fermi profile, then Newton steps to an update

@@ -1869,7 +1869,7 @@ int mbf_gp_solve(const double* E, int n_E, int M, double L, int n_nu, double dnu
         dE = const_cast<double*>(E); dphi = phi; dspec = spec; dst = stats;
     }
     mbf::GpArgs g{dE, M, L, n_nu, dnu, 400, 60, dphi, dspec, dst};
-    hipLaunchKernelGGL(mbf::k_gp_solve, dim3((unsigned)n_E), dim3(mbf::kGpThreads), 0, st, g);
+    mbf::gp_launch(g, n_E, st);
     HIPCHK(nullptr, hipGetLastError());
     if (mem_kind == MBF_MEM_HOST) {
         HIPCHK(nullptr, hipMemcpyAsync(phi, dphi, sizeof(double) * nphi, hipMemcpyDeviceToHost, st));
@@ -1915,7 +1915,7 @@ int mbf_kappa_fit(const double* Na, const double* W, int n, double N_th, double 
         }
         mbf::GpArgs g{dE, M, L, n_nu, dnu, 400, 60, dphi, dspec, dst};
         if (hipMemcpyAsync(dE, E.data(), sizeof(double) * n, hipMemcpyHostToDevice, st) != hipSuccess) err = MBF_EHIP;
-        hipLaunchKernelGGL(mbf::k_gp_solve, dim3((unsigned)n), dim3(mbf::kGpThreads), 0, st, g);
+        mbf::gp_launch(g, n, st);
         if (hipGetLastError() != hipSuccess ||
             hipMemcpyAsync(stats.data(), dst, sizeof(double) * stats.size(), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
