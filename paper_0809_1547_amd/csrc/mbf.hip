@@ -2067,7 +2067,7 @@ int mbf_pack_md(int n, const double* box, const double* diam, double* centres, c
     int *cnt = nullptr, *lst = nullptr, *flag = nullptr;
     double *dd = nullptr, *dx = nullptr, *e = nullptr, *mo = nullptr, *out = nullptr;
     const size_t nc = (size_t)ncell, ncap = nc * mbf::kPackCap;
-    if (!mem.get(&P[0], nn) || !mem.get(&P[1], nn) || !mem.get(&cnt, 2 * nc) || !mem.get(&lst, 2 * ncap) ||
+    if (!mem.get(&P[0], nn) || !mem.get(&P[1], nn) || !mem.get(&cnt, 3 * nc) || !mem.get(&lst, 2 * ncap) ||
         !mem.get(&flag, 1) || !mem.get(&e, nn) || !mem.get(&mo, nn) || !mem.get(&out, 2))
         return fail(nullptr, MBF_ENOMEM, "device allocation for the packing failed");
     if (mem_kind == MBF_MEM_HOST) {
@@ -2079,32 +2079,32 @@ int mbf_pack_md(int n, const double* box, const double* diam, double* centres, c
         dd = const_cast<double*>(diam);
         dx = centres;
     }
-    // two cell tables (counts + lists): a step reads one and bins into the other
-    int* ct[2] = {cnt, cnt + nc};
+    // two cell tables: a step reads one and bins into the other; the counts have
+    // a third buffer, which a step clears for the next
+    int* ct[3] = {cnt, cnt + nc, cnt + 2 * nc};
     int* lt[2] = {lst, lst + ncap};
     const unsigned b256 = (unsigned)((nn + 255) / 256);
     const unsigned bstep = (unsigned)((nn + mbf::kPackThreads / mbf::kPackLanes - 1) / (mbf::kPackThreads / mbf::kPackLanes));
     const unsigned bcell = (unsigned)((nc + 255) / 256);
-    hipLaunchKernelGGL(mbf::k_pack_load, dim3(b256), dim3(256), 0, st, dx, dd, n, P[0], cnt, 2 * gr.ncell);
+    hipLaunchKernelGGL(mbf::k_pack_load, dim3(b256), dim3(256), 0, st, dx, dd, n, P[0], cnt, 3 * gr.ncell);
     hipLaunchKernelGGL(mbf::k_pack_clear_flag, dim3(1), dim3(64), 0, st, flag);
     hipLaunchKernelGGL(mbf::k_pack_bin, dim3(b256), dim3(256), 0, st, P[0], n, gr, ct[0], lt[0], flag);
-    hipLaunchKernelGGL(mbf::k_pack_sort, dim3(bcell), dim3(256), 0, st, ct[0], lt[0], gr.ncell, ct[1]);
     HIPCHK(nullptr, hipGetLastError());
-    int cur = 0, par = 0;
+    int cur = 0, par = 0;                             // centres and lists; counts
     for (int m = 0; m <= prm->stages; ++m) {
         const double s = prm->stages > 0 ? prm->s0 + (1.0 - prm->s0) * (double)m / (double)prm->stages : 1.0;
         const int steps = m < prm->stages ? prm->iters : prm->final_iters;
         for (int t = 0; t < steps; ++t) {
             hipLaunchKernelGGL(mbf::k_pack_step, dim3(bstep), dim3(mbf::kPackThreads), 0, st, P[cur], P[cur ^ 1], n,
-                               gr, ct[par], lt[par], s, prm->eta, ct[par ^ 1], lt[par ^ 1], flag);
-            hipLaunchKernelGGL(mbf::k_pack_sort, dim3(bcell), dim3(256), 0, st, ct[par ^ 1], lt[par ^ 1], gr.ncell,
-                               ct[par]);
+                               gr, ct[par], lt[cur], s, prm->eta, ct[(par + 1) % 3], lt[cur ^ 1], ct[(par + 2) % 3],
+                               flag);
             cur ^= 1;
-            par ^= 1;
+            par = (par + 1) % 3;
         }
         HIPCHK(nullptr, hipGetLastError());
     }
-    hipLaunchKernelGGL(mbf::k_pack_measure, dim3(b256), dim3(256), 0, st, P[cur], n, gr, ct[par], lt[par], e, mo);
+    hipLaunchKernelGGL(mbf::k_pack_sort, dim3(bcell), dim3(256), 0, st, ct[par], lt[cur], gr.ncell);
+    hipLaunchKernelGGL(mbf::k_pack_measure, dim3(b256), dim3(256), 0, st, P[cur], n, gr, ct[par], lt[cur], e, mo);
     hipLaunchKernelGGL(mbf::k_pack_reduce, dim3(1), dim3(256), 0, st, e, mo, n, out);
     hipLaunchKernelGGL(mbf::k_pack_store, dim3(b256), dim3(256), 0, st, P[cur], n, dx);
     HIPCHK(nullptr, hipGetLastError());
