@@ -63,6 +63,7 @@ struct mbf_handle {
     uint8_t* mat = nullptr;
     void* lut = nullptr;      // inv_eps[256], eps[256], mur[256], (eps, inv_eps)[256] in the field type
     mbf::Ctl* ctl = nullptr;
+    double* src_tab = nullptr;   // source values of the next steps
     double* e_part = nullptr;
     double* l_part = nullptr;
     int n_part = 0;
@@ -310,6 +311,7 @@ mbf::SimView<T> view(mbf_handle* h) {
     v.seed_hi = (uint32_t)(h->cfg.seed >> 32);
     v.realization = h->cfg.realization;
     v.src_on = h->src_on;
+    v.src_tab = h->src_tab;
     v.src_comp = h->src_comp;
     v.src_i = h->src_i; v.src_j = h->src_j; v.src_k = h->src_k;
     v.src_kind = h->src_kind;
@@ -335,7 +337,7 @@ mbf::SimView<T> view(mbf_handle* h) {
     v.ctl = h->ctl;
     v.e_part = h->e_part;
     v.l_part = h->l_part;
-    v.n_part = h->n_part;
+    v.n_part = v.part_cap = h->n_part;
     v.hist = h->hist;
     v.hist_cap = h->hist_cap;
     v.n_probes = h->n_probes;
@@ -449,29 +451,29 @@ void dispatch_order(std::vector<uint32_t>& items, int i0, int i1, const std::vec
 // SPLIT: the split E pass and streaming H stores.
 template <typename T, bool SPLIT>
 hipError_t launch_two_pass(hipStream_t st, int ty, const mbf::SimView<T>* vw, const mbf::Geom* gw, const uint32_t* it,
-                           int ni, int rm, hipEvent_t evm) {
-    const dim3 g((unsigned)ni);
+                           int ni, mbf::StepEnds se, hipEvent_t evm) {
+    const dim3 g((unsigned)ni), ge((unsigned)(ni + se.ends));
     hipError_t e = hipSuccess;
     switch (ty) {
         case 2:
-            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 2, SPLIT>), g, dim3(64, 2), 0, st, vw, gw, it, ni, rm);
+            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 2, SPLIT>), g, dim3(64, 2), 0, st, vw, gw, it, se.q);
             if (evm) e = hipEventRecord(evm, st);
-            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 2, SPLIT>), g, dim3(64, 2), 0, st, vw, gw, it, ni, rm);
+            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 2, SPLIT>), ge, dim3(64, 2), 0, st, vw, gw, it, se);
             break;
         case 4:
-            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 4, SPLIT>), g, dim3(64, 4), 0, st, vw, gw, it, ni, rm);
+            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 4, SPLIT>), g, dim3(64, 4), 0, st, vw, gw, it, se.q);
             if (evm) e = hipEventRecord(evm, st);
-            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 4, SPLIT>), g, dim3(64, 4), 0, st, vw, gw, it, ni, rm);
+            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 4, SPLIT>), ge, dim3(64, 4), 0, st, vw, gw, it, se);
             break;
         case 16:
-            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 16, SPLIT>), g, dim3(64, 16), 0, st, vw, gw, it, ni, rm);
+            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 16, SPLIT>), g, dim3(64, 16), 0, st, vw, gw, it, se.q);
             if (evm) e = hipEventRecord(evm, st);
-            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 16, SPLIT>), g, dim3(64, 16), 0, st, vw, gw, it, ni, rm);
+            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 16, SPLIT>), ge, dim3(64, 16), 0, st, vw, gw, it, se);
             break;
         default:
-            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 8, SPLIT>), g, dim3(64, 8), 0, st, vw, gw, it, ni, rm);
+            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 8, SPLIT>), g, dim3(64, 8), 0, st, vw, gw, it, se.q);
             if (evm) e = hipEventRecord(evm, st);
-            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 8, SPLIT>), g, dim3(64, 8), 0, st, vw, gw, it, ni, rm);
+            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 8, SPLIT>), ge, dim3(64, 8), 0, st, vw, gw, it, se);
             break;
     }
     return e;
@@ -502,42 +504,60 @@ int persist_grid(int ni) {
 // The single-pass kernels at NW (waves per workgroup, or rows of a tile).
 template <typename T, int NW, bool LAY>
 void launch_one_pass(hipStream_t st, int variant, const mbf::SimView<T>* vw, const mbf::Geom* gw, const uint32_t* it,
-                     int ni, int rm, uint32_t* queue) {
+                     int ni, mbf::StepEnds se, uint32_t* queue) {
     const dim3 g((unsigned)ni), b(64, NW);
     if (variant == MBF_VARIANT_FUSED_PERSISTENT)
         hipLaunchKernelGGL((mbf::k_step_fused_persist<T, NW, LAY>), dim3((unsigned)persist_grid<T, NW, LAY>(ni)), b, 0,
                            st, vw, gw, it, ni, queue);
     else if (variant == MBF_VARIANT_FUSED_LDS)
-        hipLaunchKernelGGL((mbf::k_step_lds_batch<T, NW>), g, b, 0, st, vw, gw, it, ni, rm);
+        hipLaunchKernelGGL((mbf::k_step_lds_batch<T, NW>), g, b, 0, st, vw, gw, it);
     else
-        hipLaunchKernelGGL((mbf::k_step_fused_batch<T, NW, LAY>), g, b, 0, st, vw, gw, it, ni, rm);
+        hipLaunchKernelGGL((mbf::k_step_fused_batch<T, NW, LAY>), dim3((unsigned)(ni + se.ends)), b, 0, st, vw, gw, it, se);
 }
+
+// Whether a schedule's kernels end the step before in the next step's launch;
+// the others (a persistent grid, or a barrier on every plane) end each step by
+// itself.
+bool defers_ends(const mbf_tuning& t) {
+    return t.variant != MBF_VARIANT_FUSED_PERSISTENT && t.variant != MBF_VARIANT_FUSED_LDS;
+}
+// Step q of a sequence of len steps of members [r0, r0 + m).
+mbf::StepEnds step_ends(const mbf_tuning& t, int64_t q, int64_t len, int r0, int m) {
+    if (len <= 1 || !defers_ends(t)) return {0, 0, r0, m};
+    return {(int)q, (m + 7) / 8 * 8, r0, m};
+}
+// n steps as sequences of kSeqSteps: the place of step s in its sequence, and
+// that sequence's length.
+int64_t seq_step(int64_t s) { return s % mbf::kSeqSteps; }
+int64_t seq_len(int64_t s, int64_t n) { return std::min<int64_t>(mbf::kSeqSteps, n - s / mbf::kSeqSteps * mbf::kSeqSteps); }
+// Whether step q of the sequence is followed by the launch that ends it.
+bool ends_here(const mbf_tuning& t, int64_t q, int64_t len) { return q == len - 1 || !defers_ends(t); }
 
 // The field kernels of one step (both passes, or the single pass) over the
 // work table it[0..ni) of the views vw and geometries gw; evm (optional) is
 // recorded between the two passes; queue holds the persistent variant's
-// counters (zero between launches); lay: some member has an absorbing layer;
-// tiles: the table is the tile kernel's.
+// counters (zero between launches); se: the step's place in its sequence; lay:
+// some member has an absorbing layer; tiles: the table is the tile kernel's.
 template <typename T>
 hipError_t launch_fields(hipStream_t st, const mbf_tuning& tun, const mbf::SimView<T>* vw, const mbf::Geom* gw,
-                         const uint32_t* it, int ni, hipEvent_t evm, uint32_t* queue, bool lay, bool tiles) {
-    const int rm = tun.xcd_remap, var = tun.variant;
+                         const uint32_t* it, int ni, mbf::StepEnds se, hipEvent_t evm, uint32_t* queue, bool lay, bool tiles) {
+    const int var = tun.variant;
     if (tiles || var == MBF_VARIANT_FUSED_LDS) {
         if (var == MBF_VARIANT_FUSED_PERSISTENT && !queue) return hipErrorInvalidValue;
         switch (tun.tile_y * 2 + (lay ? 1 : 0)) {
-            case 4: launch_one_pass<T, 2, false>(st, var, vw, gw, it, ni, rm, queue); break;
-            case 5: launch_one_pass<T, 2, true>(st, var, vw, gw, it, ni, rm, queue); break;
-            case 8: launch_one_pass<T, 4, false>(st, var, vw, gw, it, ni, rm, queue); break;
-            case 9: launch_one_pass<T, 4, true>(st, var, vw, gw, it, ni, rm, queue); break;
-            case 32: launch_one_pass<T, 16, false>(st, var, vw, gw, it, ni, rm, queue); break;
-            case 33: launch_one_pass<T, 16, true>(st, var, vw, gw, it, ni, rm, queue); break;
-            case 16: launch_one_pass<T, 8, false>(st, var, vw, gw, it, ni, rm, queue); break;
-            default: launch_one_pass<T, 8, true>(st, var, vw, gw, it, ni, rm, queue); break;
+            case 4: launch_one_pass<T, 2, false>(st, var, vw, gw, it, ni, se, queue); break;
+            case 5: launch_one_pass<T, 2, true>(st, var, vw, gw, it, ni, se, queue); break;
+            case 8: launch_one_pass<T, 4, false>(st, var, vw, gw, it, ni, se, queue); break;
+            case 9: launch_one_pass<T, 4, true>(st, var, vw, gw, it, ni, se, queue); break;
+            case 32: launch_one_pass<T, 16, false>(st, var, vw, gw, it, ni, se, queue); break;
+            case 33: launch_one_pass<T, 16, true>(st, var, vw, gw, it, ni, se, queue); break;
+            case 16: launch_one_pass<T, 8, false>(st, var, vw, gw, it, ni, se, queue); break;
+            default: launch_one_pass<T, 8, true>(st, var, vw, gw, it, ni, se, queue); break;
         }
         return evm ? hipEventRecord(evm, st) : hipSuccess;
     }
-    if (var == MBF_VARIANT_TWO_PASS_SPLIT) return launch_two_pass<T, true>(st, tun.tile_y, vw, gw, it, ni, rm, evm);
-    return launch_two_pass<T, false>(st, tun.tile_y, vw, gw, it, ni, rm, evm);
+    if (var == MBF_VARIANT_TWO_PASS_SPLIT) return launch_two_pass<T, true>(st, tun.tile_y, vw, gw, it, ni, se, evm);
+    return launch_two_pass<T, false>(st, tun.tile_y, vw, gw, it, ni, se, evm);
 }
 
 // A handle steps through the same kernels as a batch, as a batch of one: its
@@ -589,27 +609,28 @@ int prepare_tables(mbf_handle* h) {
     return h->cfg.precision == MBF_FP64 ? self_tables<double>(h, g) : self_tables<float>(h, g);
 }
 
-// Queue one step.  When ev0/ev1 are given they bracket the step's field
-// kernels (the dominant cost) on the handle's stream.
+// Queue step q of a sequence of len.  When ev0/ev1 are given they bracket the
+// step's field kernels (the dominant cost) on the handle's stream.
 template <typename T>
-int launch_step(mbf_handle* h, hipEvent_t ev0 = nullptr, hipEvent_t evm = nullptr,
-                hipEvent_t ev1 = nullptr) {
+int launch_step(mbf_handle* h, int64_t q, int64_t len, hipEvent_t ev0, hipEvent_t evm, hipEvent_t ev1) {
     const mbf::Geom gm = step_geom(h);
     const int rc = self_tables<T>(h, gm);
     if (rc) return rc;
     mbf::SimView<T> v = view<T>(h);
     v.n_part = step_parts(h, h->tun, uses_tiles(h));
+    const mbf::StepEnds se = step_ends(h->tun, q, len, 0, 1);
     if (ev0) HIPCHK(h, hipEventRecord(ev0, h->stream));
     HIPCHK(h, (launch_fields<T>(h->stream, h->tun, reinterpret_cast<const mbf::SimView<T>*>(h->d_view),
-                                h->d_geom, h->d_items, gm.nblk, evm, h->d_queue, h->has_layer, uses_tiles(h))));
+                                h->d_geom, h->d_items, gm.nblk, se, evm, h->d_queue, h->has_layer, uses_tiles(h))));
     if (ev1) HIPCHK(h, hipEventRecord(ev1, h->stream));
     if (h->mur_tasks > 0) {
         const int nmax = std::max({h->cfg.nx, h->cfg.ny, h->cfg.nz}) + 1;
         const int64_t sites = (int64_t)nmax * nmax;
         dim3 gmur((unsigned)((sites + 255) / 256), (unsigned)h->mur_tasks, 1);
-        hipLaunchKernelGGL(mbf::k_mur<T>, gmur, dim3(256), 0, h->stream, v);
+        hipLaunchKernelGGL(mbf::k_mur<T>, gmur, dim3(256), 0, h->stream, v, se.q);
     }
-    hipLaunchKernelGGL(mbf::k_end_step<T>, dim3(1), dim3(mbf::kEndThreads), 0, h->stream, v);
+    if (ends_here(h->tun, q, len))
+        hipLaunchKernelGGL(mbf::k_end_step<T>, dim3(1), dim3(64, mbf::kEndThreads / 64), 0, h->stream, v, se.q);
     HIPCHK(h, hipGetLastError());
     return MBF_OK;
 }
@@ -625,10 +646,10 @@ int launch_dft(mbf_handle* h, int count) {
     return MBF_OK;
 }
 
-int dispatch_step(mbf_handle* h, hipEvent_t ev0 = nullptr, hipEvent_t evm = nullptr,
+int dispatch_step(mbf_handle* h, int64_t q, int64_t len, hipEvent_t ev0 = nullptr, hipEvent_t evm = nullptr,
                   hipEvent_t ev1 = nullptr) {
-    return h->cfg.precision == MBF_FP64 ? launch_step<double>(h, ev0, evm, ev1)
-                                        : launch_step<float>(h, ev0, evm, ev1);
+    return h->cfg.precision == MBF_FP64 ? launch_step<double>(h, q, len, ev0, evm, ev1)
+                                        : launch_step<float>(h, q, len, ev0, evm, ev1);
 }
 
 int dispatch_dft(mbf_handle* h, int count) {
@@ -661,7 +682,7 @@ int build_graph(mbf_handle* h, int64_t n) {
     hipGraph_t g = nullptr;
     HIPCHK(h, hipStreamBeginCapture(h->stream, hipStreamCaptureModeRelaxed));
     int rc = MBF_OK;
-    for (int64_t s = 0; s < n && rc == MBF_OK; ++s) rc = dispatch_step(h);
+    for (int64_t s = 0; s < n && rc == MBF_OK; ++s) rc = dispatch_step(h, seq_step(s), seq_len(s, n));
     if (rc == MBF_OK && h->n_probes > 0) rc = dispatch_dft(h, (int)n);
     hipError_t e = hipStreamEndCapture(h->stream, &g);
     if (rc != MBF_OK) {
@@ -768,7 +789,7 @@ size_t map_bytes(const mbf_handle* h) {
 }
 
 size_t snap_bytes(const mbf_handle* h) {
-    return (size_t)h->nsite * h->esz * 12 + (size_t)h->glen * h->esz * 15 + sizeof(mbf::Ctl) +
+    return (size_t)h->nsite * h->esz * 12 + (size_t)h->glen * h->esz * 15 + sizeof(mbf::Ctl) + sizeof(double) * mbf::kSeqSteps +
            sizeof(double) * (size_t)h->hist_cap + sizeof(double) * 2 * (size_t)h->n_probes * h->n_freq +
            h->esz * (size_t)h->n_probes * h->decim + map_bytes(h);
 }
@@ -779,6 +800,7 @@ int snap_copy(mbf_handle* h, Snap& s, bool save) {
         {h->pool, (size_t)h->nsite * h->esz * 12},
         {h->gpool, (size_t)h->glen * h->esz * 15},
         {h->ctl, sizeof(mbf::Ctl)},
+        {h->src_tab, sizeof(double) * mbf::kSeqSteps},
         {h->hist, sizeof(double) * (size_t)h->hist_cap},
         {h->d_spec, sizeof(double) * 2 * (size_t)h->n_probes * h->n_freq},
         {h->d_ring, h->esz * (size_t)h->n_probes * h->decim},
@@ -1039,12 +1061,14 @@ int mbf_create(const mbf_config* cfg, void* stream, mbf_handle** out) {
         hipMalloc(&h->seg16, sizeof(uint32_t) * n16) != hipSuccess ||
         hipMalloc(&h->mat, (size_t)h->nsite) != hipSuccess ||
         hipMalloc(&h->lut, 5 * mbf::kMaxMat * h->esz) != hipSuccess ||
-        hipMalloc(&h->ctl, sizeof(mbf::Ctl)) != hipSuccess)
+        hipMalloc(&h->ctl, sizeof(mbf::Ctl)) != hipSuccess ||
+        hipMalloc(&h->src_tab, sizeof(double) * mbf::kSeqSteps) != hipSuccess)
         return bail(MBF_ENOMEM, "device allocation failed");
-    // enough partial-sum slots for every schedule (one per 16 x 2 tile and plane)
+    // enough partial-sum slots for every schedule (one per 16 x 2 tile and
+    // plane), for a step and the one that ends it
     h->n_part = ((c.nx + 15) / 16) * ((c.ny + 1) / 2) * c.nz;
-    if (hipMalloc(&h->e_part, sizeof(double) * h->n_part) != hipSuccess ||
-        hipMalloc(&h->l_part, sizeof(double) * h->n_part) != hipSuccess)
+    if (hipMalloc(&h->e_part, sizeof(double) * 2 * (size_t)h->n_part) != hipSuccess ||
+        hipMalloc(&h->l_part, sizeof(double) * 2 * (size_t)h->n_part) != hipSuccess)
         return bail(MBF_ENOMEM, "device allocation failed");
     h->hist_cap = c.energy_history;
     if (h->hist_cap > 0 && hipMalloc(&h->hist, sizeof(double) * h->hist_cap) != hipSuccess)
@@ -1055,7 +1079,7 @@ int mbf_create(const mbf_config* cfg, void* stream, mbf_handle** out) {
         hipMemsetAsync(h->mat, 0, (size_t)h->nsite, h->stream) != hipSuccess ||
         hipMemsetAsync(h->lut, 0, 5 * mbf::kMaxMat * h->esz, h->stream) != hipSuccess ||
         hipMemsetAsync(h->ctl, 0, sizeof(mbf::Ctl), h->stream) != hipSuccess ||
-        hipMemsetAsync(h->l_part, 0, sizeof(double) * h->n_part, h->stream) != hipSuccess ||
+        hipMemsetAsync(h->l_part, 0, sizeof(double) * 2 * (size_t)h->n_part, h->stream) != hipSuccess ||
         hipStreamSynchronize(h->stream) != hipSuccess)
         return bail(MBF_EHIP, "device initialisation failed");
     // Mur tasks: (axis a, side, tangential component c)
@@ -1087,7 +1111,7 @@ void mbf_destroy(mbf_handle* h) {
     free_probes(h);
     hipFree(h->pool); hipFree(h->gpool); hipFree(h->seg_base); hipFree(h->seg16);
     hipFree(h->mat); hipFree(h->lut);
-    hipFree(h->ctl); hipFree(h->e_part); hipFree(h->l_part); hipFree(h->hist); hipFree(h->lev); hipFree(h->lc);
+    hipFree(h->ctl); hipFree(h->src_tab); hipFree(h->e_part); hipFree(h->l_part); hipFree(h->hist); hipFree(h->lev); hipFree(h->lc);
     hipFree(h->d_view); hipFree(h->d_geom); hipFree(h->d_items); hipFree(h->d_queue); hipFree(h->map);
     if (h->own_stream && h->stream) hipStreamDestroy(h->stream);
     delete h;
@@ -1453,11 +1477,15 @@ int run_steps(mbf_handle* h, int64_t nsteps, std::vector<hipEvent_t>* ev) {
             left -= chunk;
             continue;
         }
-        int rc = ev ? dispatch_step(h, (*ev)[e], (*ev)[e + 1], (*ev)[e + 2]) : dispatch_step(h);
+        // the steps up to the next chunk's start (timed steps one by one)
+        const int64_t len = ev ? 1 : std::min<int64_t>({left, chunk - pending, mbf::kSeqSteps});
+        int rc = MBF_OK;
+        for (int64_t q = 0; q < len && !rc; ++q)
+            rc = ev ? dispatch_step(h, q, len, (*ev)[e], (*ev)[e + 1], (*ev)[e + 2]) : dispatch_step(h, q, len);
         if (rc) return rc;
         e += 3;
-        h->step += 1;
-        left -= 1;
+        h->step += len;
+        left -= len;
         if (h->n_probes == 0) {
             h->flushed = h->step;
         } else if (h->step - h->flushed == h->decim) {
@@ -2486,34 +2514,36 @@ int batch_tables(mbf_batch* b) {
     return MBF_OK;
 }
 
-// One step of the members of group gi, or of all members when gi < 0.
+// Step q of a sequence of len of the members of group gi, or of all members
+// when gi < 0.
 template <typename T>
-int batch_launch_step(mbf_batch* b, int gi, hipEvent_t ev0 = nullptr, hipEvent_t evm = nullptr,
-                      hipEvent_t ev1 = nullptr) {
+int batch_launch_step(mbf_batch* b, int gi, int64_t q, int64_t len, hipEvent_t ev0, hipEvent_t evm, hipEvent_t ev1) {
     const mbf_batch::Group& gr = gi < 0 ? b->all : b->groups[gi];
     const mbf::SimView<T>* vw = reinterpret_cast<const mbf::SimView<T>*>(b->d_views);
     const mbf::Geom* gw = b->d_geoms;
     const uint32_t* it = b->d_items + gr.i0;
     const int ni = gr.i1 - gr.i0;
     hipStream_t st = b->stream;
+    const mbf::StepEnds se = step_ends(b->tun, q, len, gr.r0, gr.r1 - gr.r0);
     if (ev0) BHIPCHK(b, hipEventRecord(ev0, st));
-    BHIPCHK(b, (launch_fields<T>(st, b->tun, vw, gw, it, ni, evm, b->d_queue, b->any_layer, b->tiles)));
+    BHIPCHK(b, (launch_fields<T>(st, b->tun, vw, gw, it, ni, se, evm, b->d_queue, b->any_layer, b->tiles)));
     if (ev1) BHIPCHK(b, hipEventRecord(ev1, st));
     const mbf::SimView<T>* views = reinterpret_cast<const mbf::SimView<T>*>(b->d_views) + gr.r0;
     const unsigned nm = (unsigned)(gr.r1 - gr.r0);
     if (gr.mur_tasks > 0) {
         const dim3 gm((unsigned)((gr.mur_sites + 255) / 256), (unsigned)gr.mur_tasks, nm);
-        hipLaunchKernelGGL(mbf::k_mur_batch<T>, gm, dim3(256), 0, st, views);
+        hipLaunchKernelGGL(mbf::k_mur_batch<T>, gm, dim3(256), 0, st, views, se.q);
     }
-    hipLaunchKernelGGL(mbf::k_end_step_batch<T>, dim3(nm), dim3(mbf::kEndThreads), 0, st, views);
+    if (ends_here(b->tun, q, len))
+        hipLaunchKernelGGL(mbf::k_end_step_batch<T>, dim3(nm), dim3(64, mbf::kEndThreads / 64), 0, st, views, se.q);
     BHIPCHK(b, hipGetLastError());
     return MBF_OK;
 }
 
-int batch_dispatch(mbf_batch* b, int gi, hipEvent_t ev0 = nullptr, hipEvent_t evm = nullptr,
+int batch_dispatch(mbf_batch* b, int gi, int64_t q, int64_t len, hipEvent_t ev0 = nullptr, hipEvent_t evm = nullptr,
                    hipEvent_t ev1 = nullptr) {
-    return b->precision == MBF_FP64 ? batch_launch_step<double>(b, gi, ev0, evm, ev1)
-                                    : batch_launch_step<float>(b, gi, ev0, evm, ev1);
+    return b->precision == MBF_FP64 ? batch_launch_step<double>(b, gi, q, len, ev0, evm, ev1)
+                                    : batch_launch_step<float>(b, gi, q, len, ev0, evm, ev1);
 }
 
 // Probe decimation shared by the members with probes (0: none has probes,
@@ -2535,7 +2565,7 @@ int batch_build_graph(mbf_batch* b, int64_t n) {
     int rc = MBF_OK;
     // the whole chunk for one group, then the next group
     for (int gi = 0; gi < (int)b->groups.size() && rc == MBF_OK; ++gi) {
-        for (int64_t q = 0; q < n && rc == MBF_OK; ++q) rc = batch_dispatch(b, gi);
+        for (int64_t q = 0; q < n && rc == MBF_OK; ++q) rc = batch_dispatch(b, gi, seq_step(q), seq_len(q, n));
         for (int r = b->groups[gi].r0; r < b->groups[gi].r1 && rc == MBF_OK; ++r)
             if (b->m[r]->n_probes > 0) {
                 rc = dispatch_dft(b->m[r], (int)n);
@@ -2586,17 +2616,22 @@ int run_batch(mbf_batch* b, int64_t nsteps, std::vector<hipEvent_t>* ev) {
             left -= chunk;
             continue;
         }
-        // a single step: every group once (timed steps run as one group)
+        // the steps that no member's spectrum splits, group by group (timed
+        // steps one by one, as one group)
+        int64_t len = ev ? 1 : std::min<int64_t>(left, mbf::kSeqSteps);
+        for (const mbf_handle* h : b->m)
+            if (h->n_probes > 0) len = std::min(len, h->decim - (h->step - h->flushed));
         if (ev) {
-            rc = batch_dispatch(b, -1, (*ev)[e], (*ev)[e + 1], (*ev)[e + 2]);
+            rc = batch_dispatch(b, -1, 0, 1, (*ev)[e], (*ev)[e + 1], (*ev)[e + 2]);
         } else {
-            for (int gi = 0; gi < (int)b->groups.size() && rc == MBF_OK; ++gi) rc = batch_dispatch(b, gi);
+            for (int gi = 0; gi < (int)b->groups.size() && rc == MBF_OK; ++gi)
+                for (int64_t q = 0; q < len && rc == MBF_OK; ++q) rc = batch_dispatch(b, gi, q, len);
         }
         if (rc) return rc;
         e += 3;
-        left -= 1;
+        left -= len;
         for (mbf_handle* h : b->m) {
-            h->step += 1;
+            h->step += len;
             if (h->n_probes == 0) {
                 h->flushed = h->step;
             } else if (h->step - h->flushed == h->decim) {

@@ -37,7 +37,7 @@ struct Ctl {                  // per-simulation control block (device memory)
     double loss;              // loss-box integral
     int32_t nonfinite;        // set once a step produced a non-finite energy
     int32_t pad;
-    double src_val;           // soft-source value added during the current step
+    double src_val;           // soft-source value added during step `step` (src_tab[0])
     int64_t tap_base;         // step of trajectory slot 0 while a trajectory is recorded
 };
 
@@ -73,6 +73,7 @@ struct SimView {
     // its centre), 1 the continuous wave switched on over src_tp
     int src_on, src_kind, src_comp, src_i, src_j, src_k;
     double src_amp, src_ws, src_tp, src_t0, dt;
+    double* src_tab;          // source values of steps ctl->step .. ctl->step + kSeqSteps - 1
     // loss box
     int box_on, box[6];
     // first-order Mur: task q (a, side, c) packed in bits 5q..5q+4 of mur_code
@@ -92,9 +93,9 @@ struct SimView {
     int lay_kz[2];            // planes lay_kz[0] <= k < lay_kz[1] have zero z parts
     // monitors
     Ctl* ctl;
-    double* e_part;           // per workgroup energy partial sums
-    double* l_part;           // per workgroup loss partial sums
-    int n_part;
+    double* e_part;           // energy partial sums of a step, two buffers by its parity, part_cap apart
+    double* l_part;           // loss partial sums, likewise
+    int n_part, part_cap;
     double* hist;
     int64_t hist_cap;
     int n_probes, n_freq, decim;
@@ -448,13 +449,132 @@ __device__ __forceinline__ void decode_item(const Geom& g, int w, int& bx, int& 
 // table out in dispatch order, XCD grouping included).  Energy and loss partials are indexed by the member's own
 // work item, so a member's sums match its solo run term for term.
 
-__device__ __forceinline__ void batch_item(const uint32_t* __restrict__ items, int nitems, int remap,
-                                           int& r, int& w) {
-    (void)nitems;
-    (void)remap;                       // the table is already in dispatch order
-    const uint32_t e = items[blockIdx.x];
+__device__ __forceinline__ void batch_item(const uint32_t* __restrict__ items, int ends, int& r, int& w) {
+    const uint32_t e = items[(int)blockIdx.x - ends];   // the table is in dispatch order
     r = (int)(e >> 24);
     w = (int)(e & 0xFFFFFFu);
+}
+
+// ------------------------------------------------------ row a7, step end
+// A sequence of steps (the steps of a captured graph, or those queued by one
+// call) ends each step in the next one's single pass or second pass (the
+// first keeps 55 VGPRs, which the sums would raise): workgroups of their own at
+// the front of that launch, one a member, sum the partials of
+// the step before and sample the probes while the others step the fields.  Only
+// the last step of a sequence has a launch to end it, which also advances
+// ctl->step and tabulates the source for the next sequence.  (On 32^3 that launch
+// took 2.9 of a step's 9.0 us, which now takes 6.1; on 192^3 with layers 6 of
+// 209, now 198.)
+constexpr int kSeqSteps = 32;   // steps of a sequence at most
+struct StepEnds {
+    int q;               // steps since the sequence began
+    int ends;            // workgroups at the front: a multiple of 8, so that the others keep their XCDs
+    int r0, members;     // members they serve
+};
+
+// Sum of the partials in a fixed order: each of 1024 threads (TH threads take
+// 1024 / TH turns) keeps eight independent accumulators over a fixed stride,
+// four at a time with UN loads in flight together, then a fixed tree over the
+// threads; every thread gets the sum.
+constexpr int kEndThreads = 1024;
+
+template <int TH, int UN>
+__device__ __forceinline__ double sum_partials(const double* __restrict__ p, int n, double* sh) {
+    const int t0 = (int)(threadIdx.x + 64u * threadIdx.y);
+    __syncthreads();                                  // earlier readers of sh are done
+    for (int t = t0; t < kEndThreads; t += TH) {
+        // accumulator r adds p[t + r K], p[t + (r + 8) K], ... in that order (K
+        // threads).  Past the end they read as +0, which changes no sum: an
+        // accumulator starts at +0 and so is never -0.
+        double x[2];
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            double a[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int q = t + 4 * hf * kEndThreads; q < n; q += 2 * UN * kEndThreads) {
+                double v[UN];
+#pragma unroll
+                for (int s = 0; s < UN; ++s) {
+                    const int e = q + ((s & 3) + 8 * (s >> 2)) * kEndThreads;
+                    v[s] = e < n ? gld(p + e) : 0.0;
+                }
+#pragma unroll
+                for (int s = 0; s < UN; ++s) a[s & 3] += v[s];
+            }
+            x[hf] = (a[0] + a[1]) + (a[2] + a[3]);
+        }
+        const double y = wave_sum(x[0] + x[1]);
+        if ((t & 63) == 0) sh[t >> 6] = y;
+    }
+    __syncthreads();
+    double r = 0.0;
+    for (int w = 0; w < kEndThreads / 64; ++w) r += sh[w];
+    return r;
+}
+
+// Sums, history and probe samples of step n, whose fields and partials are
+// complete (workgroups of TH threads in rows of 64).
+template <typename T, int TH, int UN>
+__device__ __forceinline__ void finish_step(const SimView<T>& v, int64_t n) {
+    __shared__ double sh[kEndThreads / 64];
+    const int t = (int)(threadIdx.x + 64u * threadIdx.y);
+    const int64_t pb = (n & 1) * (int64_t)v.part_cap;
+    const double W = sum_partials<TH, UN>(v.e_part + pb, v.n_part, sh);
+    const double L = v.box_on ? sum_partials<TH, UN>(v.l_part + pb, v.n_part, sh) : 0.0;
+    const Fields<T> f = bind_fields(v, (int)(n & 1));
+    for (int p = t; p < v.n_probes; p += TH) {
+        const int c = v.probe_comp[p];
+        const T* e = c == 0 ? f.en[0] : (c == 1 ? f.en[1] : f.en[2]);
+        v.ring[(int64_t)p * v.decim + (uint32_t)n % (uint32_t)v.decim] = e[v.probe_off[p]];   // n < 2^32
+    }
+    if (t == 0) {
+        if (!(W == W) || W - W != 0.0) v.ctl->nonfinite = 1;
+        if (n < v.hist_cap) v.hist[n] = W;
+        v.ctl->W_now = W;
+        v.ctl->W_int += W;
+        v.ctl->loss += L;
+    }
+}
+
+// Source values of the steps from n on, so that every step reads its own from
+// memory (`threads` threads, this one's index t).
+template <typename T>
+__device__ __forceinline__ void set_source(const SimView<T>& v, int64_t n, int t, int threads) {
+    for (int q = t; q < kSeqSteps; q += threads) {
+        const double x = v.src_on ? (double)source_value(v, n + q) : 0.0;
+        v.src_tab[q] = x;
+        if (q == 0) v.ctl->src_val = x;
+    }
+}
+
+// The front workgroups of step ctl->step + q: they end the step before, whose E
+// no workgroup of this step writes.
+template <typename T, int TH>
+__device__ __forceinline__ void front_group(const SimView<T>* __restrict__ views, StepEnds s) {
+    if ((int)blockIdx.x >= s.members || s.q == 0) return;
+    const SimView<T>& v = views[s.r0 + (int)blockIdx.x];
+    finish_step<T, TH, 4>(v, gld(&v.ctl->step) + s.q - 1);
+}
+
+// The launch that ends a sequence: its last step is ctl->step + q.
+template <typename T>
+__device__ __forceinline__ void end_step_body(const SimView<T>& v, int q) {
+    const int64_t n = gld(&v.ctl->step) + q;
+    finish_step<T, kEndThreads, 16>(v, n);
+    __syncthreads();                                  // every thread has read ctl->step
+    const int t = (int)(threadIdx.x + 64u * threadIdx.y);
+    if (t == 0) v.ctl->step = n + 1;
+    set_source(v, n + 1, t, kEndThreads);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kEndThreads) k_end_step(SimView<T> v, int q) {
+    end_step_body(v, q);
+}
+
+// Batched: one workgroup per member.
+template <typename T>
+__global__ void __launch_bounds__(kEndThreads) k_end_step_batch(const SimView<T>* __restrict__ views, int q) {
+    end_step_body(views[blockIdx.x], q);
 }
 
 // Energy density of cell (i, j) of the monitored plane from the cell's own
@@ -500,13 +620,13 @@ __device__ __forceinline__ void load_hplane(HPlane<T>& p, const Fields<T>& f, co
 // NT: H^{n+1/2} leaves by streaming stores (for grids far larger than the
 // caches, where the E pass reads it back from HBM anyway).
 template <typename T, int TY, bool NT>
-__device__ __forceinline__ void curl_h_body(const SimView<T>& v, const Geom& gm, int w) {
+__device__ __forceinline__ void curl_h_body(const SimView<T>& v, const Geom& gm, int w, int q) {
     __shared__ double sh[TY][4];
     int bx, by, bz;
     decode_item(gm, w, bx, by, bz);
     const int i = bx * 64 + threadIdx.x;
     const int j = by * TY + threadIdx.y;
-    const int64_t n = gld(&v.ctl->step);
+    const int64_t n = gld(&v.ctl->step) + q;
     const int par = (int)(n & 1);
     const Fields<T> f = bind_fields(v, par);
     T wsum = (T)0;
@@ -584,7 +704,7 @@ __device__ __forceinline__ void curl_h_body(const SimView<T>& v, const Geom& gm,
             P = Q;
         }
     }
-    tile_sums_rows<TY>(v, v.e_part, bx, by, bz, (double)wsum, sh);
+    tile_sums_rows<TY>(v, v.e_part + par * (int64_t)v.part_cap, bx, by, bz, (double)wsum, sh);
 }
 
 // The tables are separate no-alias read-only arguments, so the compiler may
@@ -592,10 +712,10 @@ __device__ __forceinline__ void curl_h_body(const SimView<T>& v, const Geom& gm,
 template <typename T, int TY, bool NT>
 __global__ void __launch_bounds__(64 * TY) k_curl_h_batch(const SimView<T>* __restrict__ views,
                                                 const Geom* __restrict__ geoms,
-                                                const uint32_t* __restrict__ items, int nitems, int remap) {
+                                                const uint32_t* __restrict__ items, int q) {
     int r, w;
-    batch_item(items, nitems, remap, r, w);
-    curl_h_body<T, TY, NT>(views[r], geoms[r], w);
+    batch_item(items, 0, r, w);
+    curl_h_body<T, TY, NT>(views[r], geoms[r], w, q);
 }
 
 // ---------------------------------------------------- rows a2, a3, a4, a5
@@ -675,12 +795,11 @@ __device__ __forceinline__ T* tap_slot(const SimView<T>& v, int64_t n) {
 
 // The soft source's value for component c at this site (zero elsewhere).
 template <typename T>
-__device__ __forceinline__ void source3(const SimView<T>& v, int i, int j, int k, int64_t n,
+__device__ __forceinline__ void source3(const SimView<T>& v, int i, int j, int k, int q,
                                         T& s0, T& s1, T& s2) {
     s0 = s1 = s2 = (T)0;
-    (void)n;
     if (v.src_on && i == v.src_i && j == v.src_j && k == v.src_k) {
-        const T sv = (T)gld(&v.ctl->src_val);
+        const T sv = (T)gld(v.src_tab + q);
         s0 = v.src_comp == 0 ? sv : (T)0;
         s1 = v.src_comp == 1 ? sv : (T)0;
         s2 = v.src_comp == 2 ? sv : (T)0;
@@ -724,7 +843,7 @@ __device__ __forceinline__ void load_plane(EPlane<T>& p, const Fields<T>& f, uin
 // faster where the work fills the chip (a 320^3 batch; there the first pass
 // also writes H with streaming stores, NT).
 template <typename T, int TY, bool SPLIT>
-__device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm, int w) {
+__device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm, int w, int q) {
     __shared__ double sh[TY][4];
     // the member's 1/eps_r table in LDS: one gather per plane fewer on the
     // vector memory path
@@ -735,7 +854,7 @@ __device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm,
     decode_item(gm, w, bx, by, bz);
     const int i = bx * 64 + threadIdx.x;
     const int j = by * TY + threadIdx.y;
-    const int64_t n = gld(&v.ctl->step);
+    const int64_t n = gld(&v.ctl->step) + q;
     const int par = (int)(n & 1);
     const Fields<T> f = bind_fields(v, par);
     T* const tslot = tap_slot(v, n);
@@ -793,7 +912,7 @@ __device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm,
                 noise3(v, cell, (uint32_t)n, xi);
             }
             T s0, s1, s2;
-            source3(v, i, j, k, n, s0, s1, s2);
+            source3(v, i, j, k, q, s0, s1, s2);
             // the z parts of this plane (0 without a layer and between the z
             // layers, where the column's coefficients taken before the march
             // apply)
@@ -842,7 +961,7 @@ __device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm,
             gi = gi_n;
         }
     }
-    if (v.box_on) tile_sums_rows<TY>(v, v.l_part, bx, by, bz, lsum, sh);
+    if (v.box_on) tile_sums_rows<TY>(v, v.l_part + par * (int64_t)v.part_cap, bx, by, bz, lsum, sh);
 }
 
 // The tables are separate no-alias read-only arguments, so the compiler may
@@ -850,10 +969,14 @@ __device__ __forceinline__ void curl_e_body(const SimView<T>& v, const Geom& gm,
 template <typename T, int TY, bool SPLIT>
 __global__ void __launch_bounds__(64 * TY) k_curl_e_batch(const SimView<T>* __restrict__ views,
                                                 const Geom* __restrict__ geoms,
-                                                const uint32_t* __restrict__ items, int nitems, int remap) {
+                                                const uint32_t* __restrict__ items, StepEnds s) {
+    if ((int)blockIdx.x < s.ends) {
+        front_group<T, 64 * TY>(views, s);
+        return;
+    }
     int r, w;
-    batch_item(items, nitems, remap, r, w);
-    curl_e_body<T, TY, SPLIT>(views[r], geoms[r], w);
+    batch_item(items, s.ends, r, w);
+    curl_e_body<T, TY, SPLIT>(views[r], geoms[r], w, s.q);
 }
 
 // ------------------------------------------------ fused step (a1 to a5)
@@ -1016,14 +1139,14 @@ __device__ __forceinline__ TileNear<T> tile_near(int lane, T hx, T hy, T hz, T e
 
 // LAY: some member of the launch has an absorbing layer.
 template <typename T, int NW, bool LAY>
-__device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom& gm, int w) {
+__device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom& gm, int w, int q) {
     constexpr uint32_t B = sizeof(T);
     const int lane = (int)threadIdx.x;
     const int bz = w / gm.per_seg;
     const int t = __builtin_amdgcn_readfirstlane((w - bz * gm.per_seg) * NW + (int)threadIdx.y);
     if (t >= gm.tiles_x * gm.tiles_y) return;
     const int i0 = t % gm.tiles_x * 16, j0 = t / gm.tiles_x * 4;
-    const int64_t n = gld(&v.ctl->step);
+    const int64_t n = gld(&v.ctl->step) + q;
     T* const tslot = tap_slot(v, n);
     T wsum = (T)0;
     double lsum = 0.0;
@@ -1159,7 +1282,7 @@ __device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom&
             noise3(v, cell, (uint32_t)n, xi);
         }
         T s0, s1, s2;
-        source3(v, i, j, k, n, s0, s1, s2);
+        source3(v, i, j, k, q, s0, s1, s2);
         T acc = (T)0;
         {
             const T en = bloch_site<T, LAY>(v, 0, ex, dcurl(nhz, nb.hz_y, nhy, hyp), ie, inx, g && inx, b, xi[0], s0, l0);
@@ -1194,8 +1317,9 @@ __device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom&
         s_n = s_nn;
     }
     const uint32_t slot = (uint32_t)(t + gm.tiles_x * gm.tiles_y * bz);
-    tile_sum_wave(v.e_part, slot, (double)wsum);
-    if (v.box_on) tile_sum_wave(v.l_part, slot, lsum);
+    const int64_t pb = (n & 1) * (int64_t)v.part_cap;
+    tile_sum_wave(v.e_part + pb, slot, (double)wsum);
+    if (v.box_on) tile_sum_wave(v.l_part + pb, slot, lsum);
 }
 
 // The tables are separate no-alias read-only arguments, so the compiler may
@@ -1203,10 +1327,14 @@ __device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom&
 template <typename T, int NW, bool LAY>
 __global__ void __launch_bounds__(64 * NW) k_step_fused_batch(const SimView<T>* __restrict__ views,
                                                 const Geom* __restrict__ geoms,
-                                                const uint32_t* __restrict__ items, int nitems, int remap) {
+                                                const uint32_t* __restrict__ items, StepEnds s) {
+    if ((int)blockIdx.x < s.ends) {
+        front_group<T, 64 * NW>(views, s);
+        return;
+    }
     int r, w;
-    batch_item(items, nitems, remap, r, w);
-    step_fused_body<T, NW, LAY>(views[r], geoms[r], w);
+    batch_item(items, s.ends, r, w);
+    step_fused_body<T, NW, LAY>(views[r], geoms[r], w, s.q);
 }
 
 
@@ -1235,7 +1363,7 @@ __global__ void __launch_bounds__(64 * TY) k_step_fused_persist(const SimView<T>
         if (p >= nitems) break;
         const uint32_t e = items[p];
         const int r = (int)(e >> 24), w = (int)(e & 0xFFFFFFu);
-        step_fused_body<T, TY, LAY>(views[r], geoms[r], w);
+        step_fused_body<T, TY, LAY>(views[r], geoms[r], w, 0);
     }
     if (lead && atomicAdd(queue + 8, 1u) == gridDim.x - 1u) {
         for (int q = 0; q < 9; ++q) atomicExch(queue + q, 0u);
@@ -1401,7 +1529,7 @@ __device__ __forceinline__ void step_lds_body(const SimView<T>& v, const Geom& g
                     noise3(v, cell, (uint32_t)n, xi);
                 }
                 T s0, s1, s2;
-                source3(v, i, j, k, n, s0, s1, s2);
+                source3(v, i, j, k, 0, s0, s1, s2);
                 T acc = (T)0;
                 {
                     const T curl = inx ? dcurl(nhz, hz_jm, nhy, hyp) : (T)0;
@@ -1442,17 +1570,17 @@ __device__ __forceinline__ void step_lds_body(const SimView<T>& v, const Geom& g
             if (k + 1 < kz1) gi_next = gain_index(v, bx, j, k + 1, act && m_next >= kGainId, true);
         }
     }
-    tile_sums_rows<TY>(v, v.e_part, bx, by, bz, (double)wsum, sh);
-    if (v.box_on) tile_sums_rows<TY>(v, v.l_part, bx, by, bz, lsum, sh);
+    const int64_t pb = (n & 1) * (int64_t)v.part_cap;
+    tile_sums_rows<TY>(v, v.e_part + pb, bx, by, bz, (double)wsum, sh);
+    if (v.box_on) tile_sums_rows<TY>(v, v.l_part + pb, bx, by, bz, lsum, sh);
 }
 
 template <typename T, int TY>
 __global__ void __launch_bounds__(64 * TY) k_step_lds_batch(const SimView<T>* __restrict__ views,
                                                           const Geom* __restrict__ geoms,
-                                                          const uint32_t* __restrict__ items, int nitems,
-                                                          int remap) {
+                                                          const uint32_t* __restrict__ items) {
     int r, w;
-    batch_item(items, nitems, remap, r, w);
+    batch_item(items, 0, r, w);
     step_lds_body<T, TY>(views[r], geoms[r], w);
 }
 
@@ -1470,7 +1598,7 @@ __device__ __forceinline__ int64_t sel3(int a, int64_t x0, int64_t x1, int64_t x
 }
 
 template <typename T>
-__device__ __forceinline__ void mur_body(const SimView<T>& v, int task) {
+__device__ __forceinline__ void mur_body(const SimView<T>& v, int task, int step) {
     if (task >= v.n_mur) return;
     const int code = (int)((v.mur_code >> (5 * task)) & 31u);
     const int a = code & 3, side = (code >> 2) & 1, c = (code >> 3) & 3;
@@ -1485,7 +1613,7 @@ __device__ __forceinline__ void mur_body(const SimView<T>& v, int task) {
     const bool on_t = (w == 0 || w == ntd);
     const bool t_is_mur = ((v.mur_axes >> t) & 1) != 0;
     if (on_t && (!t_is_mur || t > a)) return;
-    const int par = (int)(gld(&v.ctl->step) & 1);   // parity of the step being finished
+    const int par = (int)((gld(&v.ctl->step) + step) & 1);   // parity of the step being finished
     const Fields<T> f = bind_fields(v, par);
     const T* __restrict__ Ec = c == 0 ? f.e[0] : (c == 1 ? f.e[1] : f.e[2]);
     T* __restrict__ En = c == 0 ? f.en[0] : (c == 1 ? f.en[1] : f.en[2]);
@@ -1510,89 +1638,21 @@ __device__ __forceinline__ void mur_body(const SimView<T>& v, int task) {
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_mur(SimView<T> v) {
-    mur_body(v, (int)blockIdx.y);
+__global__ void __launch_bounds__(256) k_mur(SimView<T> v, int q) {
+    mur_body(v, (int)blockIdx.y, q);
 }
 
 // Batched: blockIdx.z is the member (members without Mur walls return).
 template <typename T>
-__global__ void __launch_bounds__(256) k_mur_batch(const SimView<T>* __restrict__ views) {
-    mur_body(views[blockIdx.z], (int)blockIdx.y);
-}
-
-// ------------------------------------------------------ row a7, step end
-// Sum of the per-workgroup partials in a fixed order: each thread keeps eight
-// independent accumulators over a fixed stride (so its loads are in flight
-// together), then a fixed tree over the threads; every thread gets the sum.
-constexpr int kEndThreads = 1024;
-
-__device__ __forceinline__ double sum_partials(const double* __restrict__ p, int n, double* sh) {
-    const int t = threadIdx.x;
-    double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    // accumulator r adds p[t + r K], p[t + (r + 8) K], ... in that order (K
-    // threads); 32 loads go out per round.  Past the end they read as +0,
-    // which changes no sum: an accumulator starts at +0 and so is never -0.
-    for (int q = t; q < n; q += 32 * kEndThreads) {
-        double v[32];
-#pragma unroll
-        for (int s = 0; s < 32; ++s) {
-            const int e = q + s * kEndThreads;
-            v[s] = e < n ? p[e] : 0.0;
-        }
-#pragma unroll
-        for (int s = 0; s < 32; ++s) a[s & 7] += v[s];
-    }
-    double x = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-    x = wave_sum(x);
-    if ((t & 63) == 0) sh[t >> 6] = x;
-    __syncthreads();
-    double r = 0.0;
-    for (int w = 0; w < kEndThreads / 64; ++w) r += sh[w];
-    return r;
-}
-
-template <typename T>
-__device__ __forceinline__ void end_step_body(const SimView<T>& v) {
-    __shared__ double sh[kEndThreads / 64];
-    const int t = threadIdx.x;
-    const int64_t n = gld(&v.ctl->step);
-    const double W = sum_partials(v.e_part, v.n_part, sh);
-    __syncthreads();
-    const double L = v.box_on ? sum_partials(v.l_part, v.n_part, sh) : 0.0;
-    const Fields<T> f = bind_fields(v, (int)(n & 1));
-    for (int p = t; p < v.n_probes; p += kEndThreads) {
-        const int c = v.probe_comp[p];
-        const T* e = c == 0 ? f.en[0] : (c == 1 ? f.en[1] : f.en[2]);
-        v.ring[(int64_t)p * v.decim + (n % v.decim)] = e[v.probe_off[p]];
-    }
-    if (t == 0) {
-        if (!(W == W) || W - W != 0.0) v.ctl->nonfinite = 1;
-        if (n < v.hist_cap) v.hist[n] = W;
-        v.ctl->W_now = W;
-        v.ctl->W_int += W;
-        v.ctl->loss += L;
-        v.ctl->step = n + 1;
-        v.ctl->src_val = v.src_on ? (double)source_value(v, n + 1) : 0.0;
-    }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(kEndThreads) k_end_step(SimView<T> v) {
-    end_step_body(v);
-}
-
-// Batched: one workgroup per member.
-template <typename T>
-__global__ void __launch_bounds__(kEndThreads) k_end_step_batch(const SimView<T>* __restrict__ views) {
-    end_step_body(views[blockIdx.x]);
+__global__ void __launch_bounds__(256) k_mur_batch(const SimView<T>* __restrict__ views, int q) {
+    mur_body(views[blockIdx.z], (int)blockIdx.y, q);
 }
 
 // Source value of the current step (after the pump, a checkpoint load or a
 // change of source), so that every step reads it from the control block.
 template <typename T>
 __global__ void k_source_init(SimView<T> v) {
-    if (threadIdx.x == 0 && blockIdx.x == 0)
-        v.ctl->src_val = v.src_on ? (double)source_value(v, v.ctl->step) : 0.0;
+    set_source(v, v.ctl->step, (int)threadIdx.x, 64);
 }
 
 // Fold `count` buffered probe samples into the FP64 spectrum; the samples
