@@ -1710,8 +1710,8 @@ int spec_stats_device(mbf_handle* h, const double* dspec, int np, int nf, const 
     if (hipMalloc(&pw, sizeof(double) * (size_t)nf) != hipSuccess ||
         hipMalloc(&dout, sizeof(mbf_spec_stats)) != hipSuccess)
         return fail(h, MBF_ENOMEM, "device allocation for the spectral statistics failed");
-    hipLaunchKernelGGL(mbf::k_spec_power, dim3((unsigned)((nf + 63) / 64)), dim3(64), 0, st, dspec, np, nf, pw);
-    hipLaunchKernelGGL(mbf::k_spec_stats, dim3(1), dim3(mbf::kStatThreads), 0, st, pw, nf, domega, level, dout);
+    mbf::launch_spec_power(st, dspec, np, nf, pw);
+    mbf::launch_spec_stats(st, pw, nf, domega, level, dout);
     HIPCHK(h, hipGetLastError());
     HIPCHK(h, hipMemcpyAsync(out, dout, sizeof(mbf_spec_stats), hipMemcpyDeviceToHost, st));
     HIPCHK(h, hipStreamSynchronize(st));
@@ -1766,9 +1766,8 @@ int spec_peaks_device(mbf_handle* h, const double* dspec, int np, int nf, double
     if (hipMalloc(&pw, sizeof(double) * (size_t)nf) != hipSuccess ||
         hipMalloc(&dout, sizeof(int32_t) * (size_t)(max_peaks + 1)) != hipSuccess)
         return fail(h, MBF_ENOMEM, "device allocation for the spectral peaks failed");
-    hipLaunchKernelGGL(mbf::k_spec_power, dim3((unsigned)((nf + 63) / 64)), dim3(64), 0, st, dspec, np, nf, pw);
-    hipLaunchKernelGGL(mbf::k_spec_peaks, dim3(1), dim3(mbf::kStatThreads), 0, st, pw, nf, min_rel, max_peaks,
-                       dout + 1, dout);
+    mbf::launch_spec_power(st, dspec, np, nf, pw);
+    mbf::launch_spec_peaks(st, pw, nf, min_rel, max_peaks, dout + 1, dout);
     HIPCHK(h, hipGetLastError());
     std::vector<int32_t> host((size_t)max_peaks + 1);
     HIPCHK(h, hipMemcpyAsync(host.data(), dout, sizeof(int32_t) * host.size(), hipMemcpyDeviceToHost, st));
@@ -3250,9 +3249,8 @@ int mbf_spectral_stats_noalloc(const double* spec, int n_probes, int n_freq, con
     const int rc = scratch_address(&pw);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(mbf::k_spec_power, dim3((unsigned)((n_freq + 63) / 64)), dim3(64), 0, st, spec, n_probes,
-                       n_freq, pw);
-    hipLaunchKernelGGL(mbf::k_spec_stats, dim3(1), dim3(mbf::kStatThreads), 0, st, pw, n_freq, omega, level, out);
+    mbf::launch_spec_power(st, spec, n_probes, n_freq, pw);
+    mbf::launch_spec_stats(st, pw, n_freq, omega, level, out);
     HIPCHK(nullptr, hipGetLastError());
     return MBF_OK;
 }

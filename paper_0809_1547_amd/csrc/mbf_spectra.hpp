@@ -41,36 +41,62 @@ __device__ __forceinline__ void stat_max(double& v, int& k, double v2, int k2) {
     }
 }
 
-// S_k = sum_p |F_{p,k}|^2, one thread per bin (a wave reads 64 consecutive
-// complex values of one probe at a time); spec holds np x nf complex values,
-// re and im interleaved, probe-major.  The probes are added in index order;
-// the loads of eight probes go out before their sums.
-__global__ void __launch_bounds__(64) k_spec_power(const double* __restrict__ spec, int np, int nf,
-                                                   double* __restrict__ pw) {
-    const int k = (int)(blockIdx.x * 64 + threadIdx.x);
-    if (k >= nf) return;
+// S_k = sum_p |F_{p,k}|^2; spec holds np x nf complex values, re and im
+// interleaved, probe-major.  A workgroup takes 16 bins and 256 probes at a time:
+// every thread forms the squares of four probes, and 16 threads add the probes
+// in index order from LDS.  Bound by latency: one thread a bin with eight loads
+// in flight took 32 rounds of loads for 256 probes, 10.3 us at 874 bins; now
+// one round, 4.3 us.
+constexpr int kPowerBins = 16, kPowerProbes = 256, kPowerThreads = 1024;
+
+__global__ void __launch_bounds__(kPowerThreads) k_spec_power(const double* __restrict__ spec, int np, int nf,
+                                                              double* __restrict__ pw) {
+    __shared__ double sq[kPowerProbes][kPowerBins];
+    constexpr int rows = kPowerThreads / kPowerBins;
+    const int b = (int)threadIdx.x % kPowerBins, row = (int)threadIdx.x / kPowerBins;
+    const int k = (int)blockIdx.x * kPowerBins + b;
     const double2* __restrict__ f = reinterpret_cast<const double2*>(spec);
     double s = 0.0;
-    int p = 0;
-    for (; p + 8 <= np; p += 8) {
-        double2 v[8];
+    for (int p0 = 0; p0 < np; p0 += kPowerProbes) {
+        double2 v[kPowerProbes / rows];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = f[(int64_t)(p + q) * nf + k];
+        for (int q = 0; q < kPowerProbes / rows; ++q) {
+            const int p = p0 + row + q * rows;
+            v[q] = p < np && k < nf ? f[(int64_t)p * nf + k] : make_double2(0.0, 0.0);
+        }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) s += v[q].x * v[q].x + v[q].y * v[q].y;
+        for (int q = 0; q < kPowerProbes / rows; ++q) sq[row + q * rows][b] = v[q].x * v[q].x + v[q].y * v[q].y;
+        __syncthreads();
+        if (row == 0) {
+            const int n = min(np - p0, kPowerProbes);
+#pragma unroll 16
+            for (int q = 0; q < n; ++q) s += sq[q][b];
+        }
+        __syncthreads();
     }
-    for (; p < np; ++p) {
-        const double2 v = f[(int64_t)p * nf + k];
-        s += v.x * v.x + v.y * v.y;
-    }
-    pw[k] = s;
+    if (row == 0 && k < nf) pw[k] = s;
 }
 
-// One workgroup per spectrum: pw holds S (nf values, from k_spec_power),
-// out receives the statistics.
-__global__ void __launch_bounds__(kStatThreads) k_spec_stats(const double* __restrict__ pw, int nf,
+// Spectra of up to this many bins are held in LDS (statistics) or in registers
+// (peaks) from pass to pass; longer ones are read again.
+constexpr int kSpecHeld = 4096;
+
+// One workgroup per spectrum: pw_in holds S (nf values, from k_spec_power),
+// out receives the statistics.  HELD: nf <= kSpecHeld.  (The walk to the fit
+// window's ends waits for each value: 13 us from memory at 874 bins,
+// 10.2 from LDS with the eight sums taken
+// together.)
+template <bool HELD>
+__global__ void __launch_bounds__(kStatThreads) k_spec_stats(const double* __restrict__ pw_in, int nf,
                                                             const double* __restrict__ omega, double level,
                                                             mbf_spec_stats* out) {
+    __shared__ double s_pw[HELD ? kSpecHeld : 1];
+    __shared__ double sh8[8][kStatThreads / 64];
+    const double* const pw = HELD ? s_pw : pw_in;
+    if constexpr (HELD) {
+        for (int k = (int)threadIdx.x; k < nf; k += kStatThreads) s_pw[k] = pw_in[k];
+        __syncthreads();
+    }
     __shared__ double sh[kStatThreads / 64];
     __shared__ double shv[kStatThreads / 64];
     __shared__ int shk[kStatThreads / 64];
@@ -140,9 +166,28 @@ __global__ void __launch_bounds__(kStatThreads) k_spec_stats(const double* __res
             r1 += w * (x * y);
             r2 += w * (x2 * y);
         }
-        a0 = stat_sum(a0, sh); a1 = stat_sum(a1, sh); a2 = stat_sum(a2, sh);
-        a3 = stat_sum(a3, sh); a4 = stat_sum(a4, sh);
-        r0 = stat_sum(r0, sh); r1 = stat_sum(r1, sh); r2 = stat_sum(r2, sh);
+        // the eight sums together (stat_sum's order): one pair of barriers, and
+        // their exchanges between lanes overlap
+        double v[8] = {a0, a1, a2, a3, a4, r0, r1, r2};
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] += __shfl_xor(v[q], o, 64);
+        }
+        __syncthreads();
+        if ((t & 63) == 0) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) sh8[q][t >> 6] = v[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            v[q] = 0.0;
+#pragma unroll
+            for (int w = 0; w < kStatThreads / 64; ++w) v[q] += sh8[q][w];
+        }
+        a0 = v[0]; a1 = v[1]; a2 = v[2]; a3 = v[3]; a4 = v[4];
+        r0 = v[5]; r1 = v[6]; r2 = v[7];
     }
     if (t != 0) return;
     mbf_spec_stats o{};
@@ -179,29 +224,87 @@ __global__ void __launch_bounds__(kStatThreads) k_spec_stats(const double* __res
 // S_k > 0, S_k >= min_rel * max S, S_{k-1} < S_k >= S_{k+1} (an edge bin
 // compares with its one neighbour; a flat top counts once, at its first bin),
 // listed by decreasing S_k (equal values: lower k first), at most max_peaks.
-// One workgroup; round r takes the largest candidate below the previous one
-// in that order.
+// One workgroup.  HELD (nf <= kSpecHeld) with at most kPeakRanked candidates:
+// the candidates go to LDS and each finds its own place by counting those that
+// come before it.  Otherwise round r takes the largest candidate below the
+// previous one, a reduction over the workgroup each time (874 bins, eight peaks:
+// 18.6 us in rounds, 5.5 by counting).
+constexpr int kPeakRanked = 512;
+
+template <bool HELD>
 __global__ void __launch_bounds__(kStatThreads) k_spec_peaks(const double* __restrict__ pw, int nf, double min_rel,
                                                             int max_peaks, int32_t* __restrict__ bins,
                                                             int32_t* __restrict__ count) {
-    __shared__ double sh[kStatThreads / 64];
-    __shared__ double shv[kStatThreads / 64];
-    __shared__ int shk[kStatThreads / 64];
+    constexpr int R = HELD ? kSpecHeld / kStatThreads : 1;
+    __shared__ double shv[2][kStatThreads / 64];
+    __shared__ int shk[2][kStatThreads / 64];
     const int t = (int)threadIdx.x;
+    int buf = 0;                                      // two buffers: one barrier a maximum
+    // largest (value, bin) of the workgroup, to every thread
+    const auto group_max = [&](double& v, int& k) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const double v2 = __shfl_xor(v, o, 64);
+            const int k2 = __shfl_xor(k, o, 64);
+            stat_max(v, k, v2, k2);
+        }
+        if ((t & 63) == 0) {
+            shv[buf][t >> 6] = v;
+            shk[buf][t >> 6] = k;
+        }
+        __syncthreads();
+        v = shv[buf][0];
+        k = shk[buf][0];
+        for (int w = 1; w < kStatThreads / 64; ++w) stat_max(v, k, shv[buf][w], shk[buf][w]);
+        buf ^= 1;
+    };
+    double c[R];                                      // held: S
     double top = -1.0;
     int tk = nf;
-    for (int k = t; k < nf; k += kStatThreads) stat_max(top, tk, pw[k], k);
+    if constexpr (HELD) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const double v2 = __shfl_xor(top, o, 64);
-        const int k2 = __shfl_xor(tk, o, 64);
-        stat_max(top, tk, v2, k2);
+        for (int q = 0; q < R; ++q) {
+            const int k = t + q * kStatThreads;
+            c[q] = k < nf ? pw[k] : -1.0;
+            if (k < nf) stat_max(top, tk, c[q], k);
+        }
+    } else {
+        for (int k = t; k < nf; k += kStatThreads) stat_max(top, tk, pw[k], k);
     }
-    if ((t & 63) == 0) shv[t >> 6] = top;
-    (void)stat_sum(0.0, sh);                          // barrier: shv published
-    double smax = shv[0];
-    for (int w = 1; w < kStatThreads / 64; ++w) smax = fmax(smax, shv[w]);
-    const double thr = min_rel * smax;
+    group_max(top, tk);
+    const double thr = min_rel * top;
+    const auto is_peak = [&](double v, int k) {
+        return v > 0.0 && v >= thr && (k == 0 || pw[k - 1] < v) && (k == nf - 1 || v >= pw[k + 1]);
+    };
+    if constexpr (HELD) {
+        __shared__ double cv[kPeakRanked];
+        __shared__ int ck[kPeakRanked], n_cand;
+        if (t == 0) n_cand = 0;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int k = t + q * kStatThreads;
+            if (q * kStatThreads >= nf || !(k < nf && is_peak(c[q], k))) continue;
+            const int slot = atomicAdd(&n_cand, 1);   // in no order: the places do not depend on it
+            if (slot < kPeakRanked) {
+                cv[slot] = c[q];
+                ck[slot] = k;
+            }
+        }
+        __syncthreads();
+        const int n = n_cand;
+        if (n <= kPeakRanked) {
+            for (int a = t; a < n; a += kStatThreads) {
+                const double v = cv[a];
+                const int k = ck[a];
+                int place = 0;
+                for (int o = 0; o < n; ++o) place += cv[o] > v || (cv[o] == v && ck[o] < k);
+                if (place < max_peaks) bins[place] = k;
+            }
+            if (t == 0) *count = min(n, max_peaks);
+            return;
+        }
+    }
     double pv = INFINITY;                             // previous pick (value, bin)
     int pk = -1;
     int found = 0;
@@ -210,25 +313,10 @@ __global__ void __launch_bounds__(kStatThreads) k_spec_peaks(const double* __res
         int bk = nf;
         for (int k = t; k < nf; k += kStatThreads) {
             const double v = pw[k];
-            const bool is_peak = v > 0.0 && v >= thr && (k == 0 || pw[k - 1] < v) && (k == nf - 1 || v >= pw[k + 1]);
             const bool below = v < pv || (v == pv && k > pk);
-            if (is_peak && below) stat_max(best, bk, v, k);
+            if (is_peak(v, k) && below) stat_max(best, bk, v, k);
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const double v2 = __shfl_xor(best, o, 64);
-            const int k2 = __shfl_xor(bk, o, 64);
-            stat_max(best, bk, v2, k2);
-        }
-        __syncthreads();                              // readers of the previous round are done
-        if ((t & 63) == 0) {
-            shv[t >> 6] = best;
-            shk[t >> 6] = bk;
-        }
-        __syncthreads();
-        best = shv[0];
-        bk = shk[0];
-        for (int w = 1; w < kStatThreads / 64; ++w) stat_max(best, bk, shv[w], shk[w]);
+        group_max(best, bk);
         if (best < 0.0) break;                        // uniform: no candidate left
         if (t == 0) bins[r] = bk;
         pv = best;
@@ -236,6 +324,25 @@ __global__ void __launch_bounds__(kStatThreads) k_spec_peaks(const double* __res
         found = r + 1;
     }
     if (t == 0) *count = found;
+}
+
+inline void launch_spec_power(hipStream_t st, const double* spec, int np, int nf, double* pw) {
+    hipLaunchKernelGGL(k_spec_power, dim3((unsigned)((nf - 1) / kPowerBins + 1)), dim3(kPowerThreads), 0, st,
+                       spec, np, nf, pw);
+}
+inline void launch_spec_stats(hipStream_t st, const double* pw, int nf, const double* omega, double level,
+                              mbf_spec_stats* out) {
+    if (nf <= kSpecHeld)
+        hipLaunchKernelGGL(k_spec_stats<true>, dim3(1), dim3(kStatThreads), 0, st, pw, nf, omega, level, out);
+    else
+        hipLaunchKernelGGL(k_spec_stats<false>, dim3(1), dim3(kStatThreads), 0, st, pw, nf, omega, level, out);
+}
+inline void launch_spec_peaks(hipStream_t st, const double* pw, int nf, double min_rel, int max_peaks, int32_t* bins,
+                              int32_t* count) {
+    if (nf <= kSpecHeld)
+        hipLaunchKernelGGL(k_spec_peaks<true>, dim3(1), dim3(kStatThreads), 0, st, pw, nf, min_rel, max_peaks, bins, count);
+    else
+        hipLaunchKernelGGL(k_spec_peaks<false>, dim3(1), dim3(kStatThreads), 0, st, pw, nf, min_rel, max_peaks, bins, count);
 }
 
 // ---------------------------------------------------------------- threshold
