@@ -338,11 +338,13 @@ int mbf_write_field(mbf_handle* h, int field_id, const void* src, int mem_kind);
  * z segment) work items; 2 (default) whole z-segment layers dealt to the XCDs
  * in turn, so neighbouring tiles share an L2 and the XCDs stream one window of
  * planes together.  tile_y must be 2, 4, 8 or 16.
- *   MBF_VARIANT_TWO_PASS: a1 in one kernel, a2-a5 in a second.  While the
- *     state of the launch (E, H, Bloch state, material) stays in the 256 MB
- *     last-level cache (at most 250 MB in all; tile_y 4 and up) the kernel of
- *     MBF_VARIANT_FUSED runs the step instead, with the same fields and
- *     monitors bit for bit.
+ *   MBF_VARIANT_TWO_PASS: a1 in one kernel, a2-a5 in a second.  With
+ *     tile_y 4 and up the kernel of MBF_VARIANT_FUSED runs the step instead
+ *     while the state of the launch (E, H, Bloch state, material) stays in the
+ *     256 MB last-level cache, in FP64, and in FP32 where rows of 64 would leave
+ *     a fifth of their lanes empty and 48 nx ny is at most 640 KB; the passes of
+ *     MBF_VARIANT_TWO_PASS_SPLIT run it from 300 MB on.  The fields and monitors
+ *     are the same bit for bit.
  *   MBF_VARIANT_TWO_PASS_SPLIT: the same two passes; the second prefetches
  *     only the dense fields of the next plane and loads the Bloch state at the
  *     start of each plane, and the first writes H with streaming (non-

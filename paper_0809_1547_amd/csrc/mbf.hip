@@ -369,22 +369,57 @@ double state_bytes(const mbf_handle* h) {
     return (double)h->nsite * (12.0 * h->esz + 1.0) + 15.0 * (double)h->glen * h->esz;
 }
 
-// Whether a launch under schedule t over members of `bytes` state in all runs
-// the tile kernel (one pass): the fused variants do, and so does the two-pass
-// schedule while the state stays in the 256 MB last-level cache (its fields
-// and monitors are the same bit for bit).  Per step, two passes and one, the
-// best segment length of each (us): FP32 32^3 13.2 and 9.0, 64^3 15.8 and 13.5,
-// 96^3 34.6 and 26.3, 128^3 (200 MB) 57.9 and 49.1, 136^3 (240 MB) 72.1 and
-// 58.6; FP64 96^3 63.3 and 47.9, 112^3 (250 MB) 85.8 and 68.4.  Beyond the
-// cache the tiles' half lines are read and written more than once and the two
-// passes stream faster (144^3, 280 MB: 91.6 and 88.9, with layers 96.5 and
-// 96.9; 152^3 100.5 and 112.8, 160^3 117.3 and 130.8).
-constexpr double kCacheBytes = 250e6;
-bool tile_schedule(const mbf_tuning& t, double bytes) {
-    return t.variant == MBF_VARIANT_FUSED || t.variant == MBF_VARIANT_FUSED_PERSISTENT ||
-           (t.variant == MBF_VARIANT_TWO_PASS && t.tile_y >= 4 && bytes <= kCacheBytes);
+// What a launch's kernel goes by: the members' state in bytes, their cells and
+// the lanes that rows of 64 give them, the largest plane of E and H (both
+// buffers) in bytes.
+struct LaunchShape {
+    double bytes = 0.0, cells = 0.0, lanes = 0.0, plane = 0.0;
+    bool fp64 = false;
+    void add(const mbf_handle* h) {
+        const mbf_config& c = h->cfg;
+        bytes += state_bytes(h);
+        cells += (double)c.nx * c.ny * c.nz;
+        lanes += (double)((c.nx + 63) / 64 * 64) * c.ny * c.nz;
+        plane = std::max(plane, 12.0 * h->esz * (double)c.nx * c.ny);
+        fp64 = c.precision == MBF_FP64;
+    }
+};
+
+// The kernels of a launch: the tile kernel (one pass), or two passes, split
+// (TWO_PASS_SPLIT's) or not.  All give the same fields and monitors bit for
+// bit, so that the two-pass schedule (tile_y 4 and up for tiles) takes the
+// fastest; steps in us, the same segments on both sides:
+//  - one pass while the state stays in the 256 MB last-level cache: FP32 32^3
+//    13.2 for two passes and 9.0, 96^3 34.6 and 26.3, 136^3 (240 MB) 72.1 and
+//    58.6; FP64 96^3 63.3 and 47.9;
+//  - one pass in FP64, whose rows of 16 fill their lines: 16 x 64^3 247 and 231,
+//    6 x 96^3 342 and 289, 152^3 (604 MB) 224 and 208;
+//  - one pass in FP32 where rows of 64 leave a fifth of their lanes empty and a
+//    plane is small enough (640 KB) that a tile finds the lines it shares with
+//    its neighbours in the XCD's L2: 160 x 32^3 179 and 163, 64 x 48^3 254 and
+//    230, 24 x 72^3 336 and 301, 10 x 96^3 269 and 260; else two passes
+//    stream faster (16 x 64^3 115 and 131, 8 x 104^3 305 and 306, 4 x 128^3 239
+//    and 259, 152^3 98 and 112);
+//  - two passes split from 300 MB on: 6 x 112^3 286 whole and 265 split, 152^3
+//    (302 MB) 102 and 98, 16 x 64^3 117 and 115; 144^3 (257 MB) 86 and 89.
+constexpr double kCacheBytes = 250e6, kSplitBytes = 300e6, kTilePlane = 640e3, kRowFill = 0.8;
+struct StepKernels {
+    bool tiles, split;
+};
+StepKernels step_kernels(const mbf_tuning& t, const LaunchShape& s) {
+    if (t.variant == MBF_VARIANT_FUSED || t.variant == MBF_VARIANT_FUSED_PERSISTENT) return {true, false};
+    if (t.variant != MBF_VARIANT_TWO_PASS) return {false, t.variant == MBF_VARIANT_TWO_PASS_SPLIT};
+    if (t.tile_y >= 4 &&
+        (s.fp64 || s.bytes <= kCacheBytes || (s.cells <= kRowFill * s.lanes && s.plane <= kTilePlane)))
+        return {true, false};
+    return {false, s.bytes > kSplitBytes};
 }
-bool uses_tiles(const mbf_handle* h) { return tile_schedule(h->tun, state_bytes(h)); }
+StepKernels step_kernels(const mbf_handle* h) {
+    LaunchShape s;
+    s.add(h);
+    return step_kernels(h->tun, s);
+}
+bool uses_tiles(const mbf_handle* h) { return step_kernels(h).tiles; }
 
 // Work-item geometry of a handle's grid under schedule t (a batch steps its
 // members under the batch's schedule, whatever the members' own): blocks of
@@ -537,12 +572,12 @@ bool ends_here(const mbf_tuning& t, int64_t q, int64_t len) { return q == len - 
 // work table it[0..ni) of the views vw and geometries gw; evm (optional) is
 // recorded between the two passes; queue holds the persistent variant's
 // counters (zero between launches); se: the step's place in its sequence; lay:
-// some member has an absorbing layer; tiles: the table is the tile kernel's.
+// some member has an absorbing layer; kn: the kernels that the table is for.
 template <typename T>
 hipError_t launch_fields(hipStream_t st, const mbf_tuning& tun, const mbf::SimView<T>* vw, const mbf::Geom* gw,
-                         const uint32_t* it, int ni, mbf::StepEnds se, hipEvent_t evm, uint32_t* queue, bool lay, bool tiles) {
+                         const uint32_t* it, int ni, mbf::StepEnds se, hipEvent_t evm, uint32_t* queue, bool lay, StepKernels kn) {
     const int var = tun.variant;
-    if (tiles || var == MBF_VARIANT_FUSED_LDS) {
+    if (kn.tiles || var == MBF_VARIANT_FUSED_LDS) {
         if (var == MBF_VARIANT_FUSED_PERSISTENT && !queue) return hipErrorInvalidValue;
         switch (tun.tile_y * 2 + (lay ? 1 : 0)) {
             case 4: launch_one_pass<T, 2, false>(st, var, vw, gw, it, ni, se, queue); break;
@@ -556,7 +591,7 @@ hipError_t launch_fields(hipStream_t st, const mbf_tuning& tun, const mbf::SimVi
         }
         return evm ? hipEventRecord(evm, st) : hipSuccess;
     }
-    if (var == MBF_VARIANT_TWO_PASS_SPLIT) return launch_two_pass<T, true>(st, tun.tile_y, vw, gw, it, ni, se, evm);
+    if (kn.split) return launch_two_pass<T, true>(st, tun.tile_y, vw, gw, it, ni, se, evm);
     return launch_two_pass<T, false>(st, tun.tile_y, vw, gw, it, ni, se, evm);
 }
 
@@ -621,7 +656,7 @@ int launch_step(mbf_handle* h, int64_t q, int64_t len, hipEvent_t ev0, hipEvent_
     const mbf::StepEnds se = step_ends(h->tun, q, len, 0, 1);
     if (ev0) HIPCHK(h, hipEventRecord(ev0, h->stream));
     HIPCHK(h, (launch_fields<T>(h->stream, h->tun, reinterpret_cast<const mbf::SimView<T>*>(h->d_view),
-                                h->d_geom, h->d_items, gm.nblk, se, evm, h->d_queue, h->has_layer, uses_tiles(h))));
+                                h->d_geom, h->d_items, gm.nblk, se, evm, h->d_queue, h->has_layer, step_kernels(h))));
     if (ev1) HIPCHK(h, hipEventRecord(ev1, h->stream));
     if (h->mur_tasks > 0) {
         const int nmax = std::max({h->cfg.nx, h->cfg.ny, h->cfg.nz}) + 1;
@@ -2390,7 +2425,7 @@ struct mbf_batch {
     std::vector<Group> groups;
     Group all{0, 0, 0, 0, 0, 0};  // every member as one group (timed steps)
     bool any_layer = false;       // some member has an absorbing layer
-    bool tiles = false;           // the tables are the tile kernel's
+    StepKernels kn{false, false}; // the kernels that the tables are for
     std::vector<uint64_t> seen;   // member versions the device tables describe
     bool tables = false;
     hipGraphExec_t gexec = nullptr;
@@ -2425,20 +2460,23 @@ void batch_free_tables(mbf_batch* b) {
     b->tables = false;
 }
 
-// Whether the batch's schedule runs the tile kernel: the rule goes by the
-// largest group of members, since a group runs a whole chunk of steps before
-// the next.
-bool batch_uses_tiles(const mbf_batch* b) {
+// The kernels of the batch's schedule: the rule goes by the largest group of
+// members, since a group runs a whole chunk of steps before the next.
+StepKernels step_kernels(const mbf_batch* b) {
     const double budget = (double)b->tun.group_mb * 1048576.0;
-    double gbytes = 0.0, gstate = 0.0, largest = 0.0;
+    double gbytes = 0.0;
+    LaunchShape group, largest;
     for (const mbf_handle* h : b->m) {
         const double mb = (double)snap_bytes(h);
-        if (budget > 0.0 && gbytes > 0.0 && gbytes + mb > budget) gbytes = gstate = 0.0;
+        if (budget > 0.0 && gbytes > 0.0 && gbytes + mb > budget) {
+            gbytes = 0.0;
+            group = {};
+        }
         gbytes += mb;
-        gstate += state_bytes(h);
-        largest = std::max(largest, gstate);
+        group.add(h);
+        if (group.bytes > largest.bytes) largest = group;
     }
-    return tile_schedule(b->tun, largest);
+    return step_kernels(b->tun, largest);
 }
 
 // Rebuild the device views, geometries and work table when a member changed.
@@ -2458,13 +2496,13 @@ int batch_tables(mbf_batch* b) {
     b->any_layer = false;
     for (const mbf_handle* h : b->m) b->any_layer = b->any_layer || h->has_layer;
     const double budget = (double)b->tun.group_mb * 1048576.0;
-    b->tiles = batch_uses_tiles(b);
+    b->kn = step_kernels(b);
     double gbytes = 0.0;
     for (int r = 0; r < R; ++r) {
         mbf_handle* h = b->m[r];
-        geoms[r] = step_geom(h, b->tun, b->tiles);
+        geoms[r] = step_geom(h, b->tun, b->kn.tiles);
         views[r] = view<T>(h);
-        views[r].n_part = step_parts(h, b->tun, b->tiles);
+        views[r].n_part = step_parts(h, b->tun, b->kn.tiles);
         if (geoms[r].nblk >= (1 << 24)) return bfail(b, MBF_EINVAL, "member grid has too many work items");
         // a new group when this member would overflow the budget
         const double mb = (double)snap_bytes(h);
@@ -2525,7 +2563,7 @@ int batch_launch_step(mbf_batch* b, int gi, int64_t q, int64_t len, hipEvent_t e
     hipStream_t st = b->stream;
     const mbf::StepEnds se = step_ends(b->tun, q, len, gr.r0, gr.r1 - gr.r0);
     if (ev0) BHIPCHK(b, hipEventRecord(ev0, st));
-    BHIPCHK(b, (launch_fields<T>(st, b->tun, vw, gw, it, ni, se, evm, b->d_queue, b->any_layer, b->tiles)));
+    BHIPCHK(b, (launch_fields<T>(st, b->tun, vw, gw, it, ni, se, evm, b->d_queue, b->any_layer, b->kn)));
     if (ev1) BHIPCHK(b, hipEventRecord(ev1, st));
     const mbf::SimView<T>* views = reinterpret_cast<const mbf::SimView<T>*>(b->d_views) + gr.r0;
     const unsigned nm = (unsigned)(gr.r1 - gr.r0);
@@ -2916,7 +2954,7 @@ int mbf_batch_autotune(mbf_batch* b, int budget_ms, mbf_tuning* chosen) {
 int mbf_batch_step_bytes(const mbf_batch* b, double* bytes) {
     if (!b || !bytes) return bfail(nullptr, MBF_EINVAL, "null argument");
     bytes[0] = bytes[1] = bytes[2] = 0.0;
-    const bool one_pass = b->tun.variant == MBF_VARIANT_FUSED_LDS || batch_uses_tiles(b);
+    const bool one_pass = b->tun.variant == MBF_VARIANT_FUSED_LDS || step_kernels(b).tiles;
     for (const mbf_handle* h : b->m) {
         double x[3];
         member_step_bytes(h, one_pass, x);

@@ -66,3 +66,28 @@ def test_two_pass_schedule_leaves_the_tile_kernel_beyond_the_cache():
         sim.step(2)
         sim.sync()
         sim.close()
+
+
+# beyond the last-level cache: FP64 (one kernel), FP32 rows that fill 72 of 128
+# lanes (one), rows that fill all of theirs (two, split from 300 MB on), a plane
+# above 640 KB (two)
+@pytest.mark.parametrize("n,precision,one", [((112, 116, 114), "fp64", True), ((72, 70, 1040), "fp32", True),
+                                             ((64, 62, 1700), "fp32", False), ((140, 126, 290), "fp32", False)])
+def test_two_pass_schedule_beyond_the_cache(n, precision, one):
+    from paper_0809_1547_amd import mbf
+    eps = np.full(n[::-1], 2.25, dtype=np.float32)
+    gain = np.zeros(n[::-1], dtype=np.uint8)
+    gain[:, :, 5:33] = 1
+    res = []
+    for variant in ("two_pass", "two_pass_split"):
+        sim = mbf.Sim(n, boundary="absorb", precision=precision, seed=3, E_sp=1e-2, energy_history=33)
+        sim.set_tuning(variant, tile_y=4, zseg=4)
+        sim.set_material(eps, gain)
+        sim.set_pump(2e24)
+        sim.set_loss_box((3, 3, 3), (60, 50, 100))
+        assert (sim.step_bytes()[2] == 0.0) == (one and variant == "two_pass")
+        sim.step(33)
+        res.append([sim.field(q) for q in (0, 1, 2, 3, 4, 5, 6, 13, 20)] + [sim.energy_history(), np.array(sim.loss())])
+        sim.close()
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
