@@ -405,6 +405,7 @@ struct LaunchShape {
 constexpr double kCacheBytes = 250e6, kSplitBytes = 300e6, kTilePlane = 640e3, kRowFill = 0.8;
 struct StepKernels {
     bool tiles, split;
+    bool multi = false;       // some march of the tile kernel is of several segments
 };
 StepKernels step_kernels(const mbf_tuning& t, const LaunchShape& s) {
     if (t.variant == MBF_VARIANT_FUSED || t.variant == MBF_VARIANT_FUSED_PERSISTENT) return {true, false};
@@ -421,6 +422,15 @@ StepKernels step_kernels(const mbf_handle* h) {
 }
 bool uses_tiles(const mbf_handle* h) { return step_kernels(h).tiles; }
 
+// The tile kernel marches over up to kMarch planes, a whole number of the
+// schedule's segments, while the grid still makes kMarchWaves waves (two a
+// SIMD): it forms the H of the plane below its march again, and the sums stay
+// the segments'.  Per step in us at 1, 2 and 4 planes: 64^3 (4096 waves at one
+// plane) 10.9, 10.3 and 12.6, FP64 24.7, 20.8 and 23.5; 48^3 with layers (1728)
+// 8.9, 10.2; 96^3 (13824) 26.4, 22.4 and 23.3, FP64 55.9, 48.9 and 47.9.
+constexpr int kMarch = 4;
+constexpr int64_t kMarchWaves = 1800;
+
 // Work-item geometry of a handle's grid under schedule t (a batch steps its
 // members under the batch's schedule, whatever the members' own): blocks of
 // 64 x tile_y columns, or the tile kernel's 16 x 4 tiles, tile_y a workgroup.
@@ -430,7 +440,12 @@ mbf::Geom step_geom(const mbf_handle* h, const mbf_tuning& t, bool tiles) {
     g.tiles_x = tiles ? (h->cfg.nx + 15) / 16 : (h->cfg.nx + 63) / 64;
     g.tiles_y = tiles ? (h->cfg.ny + 3) / 4 : (h->cfg.ny + ty - 1) / ty;
     g.zseg = step_zseg(h, t);
-    g.segs = (h->cfg.nz + g.zseg - 1) / g.zseg;
+    g.march = g.zseg;
+    if (tiles)
+        while (2 * g.march <= kMarch && (int64_t)g.tiles_x * g.tiles_y * ((h->cfg.nz + 2 * g.march - 1) / (2 * g.march)) >= kMarchWaves)
+            g.march *= 2;
+    g.march_segs = g.march / g.zseg;
+    g.segs = (h->cfg.nz + g.march - 1) / g.march;
     g.per_seg = tiles ? (g.tiles_x * g.tiles_y + ty - 1) / ty : g.tiles_x * g.tiles_y;
     g.nblk = g.per_seg * g.segs;
     g.xcd_remap = t.xcd_remap;
@@ -539,15 +554,17 @@ int persist_grid(int ni) {
 // The single-pass kernels at NW (waves per workgroup, or rows of a tile).
 template <typename T, int NW, bool LAY>
 void launch_one_pass(hipStream_t st, int variant, const mbf::SimView<T>* vw, const mbf::Geom* gw, const uint32_t* it,
-                     int ni, mbf::StepEnds se, uint32_t* queue) {
+                     int ni, mbf::StepEnds se, uint32_t* queue, bool multi) {
     const dim3 g((unsigned)ni), b(64, NW);
     if (variant == MBF_VARIANT_FUSED_PERSISTENT)
         hipLaunchKernelGGL((mbf::k_step_fused_persist<T, NW, LAY>), dim3((unsigned)persist_grid<T, NW, LAY>(ni)), b, 0,
                            st, vw, gw, it, ni, queue);
     else if (variant == MBF_VARIANT_FUSED_LDS)
         hipLaunchKernelGGL((mbf::k_step_lds_batch<T, NW>), g, b, 0, st, vw, gw, it);
+    else if (multi)
+        hipLaunchKernelGGL((mbf::k_step_fused_batch<T, NW, LAY, true>), dim3((unsigned)(ni + se.ends)), b, 0, st, vw, gw, it, se);
     else
-        hipLaunchKernelGGL((mbf::k_step_fused_batch<T, NW, LAY>), dim3((unsigned)(ni + se.ends)), b, 0, st, vw, gw, it, se);
+        hipLaunchKernelGGL((mbf::k_step_fused_batch<T, NW, LAY, false>), dim3((unsigned)(ni + se.ends)), b, 0, st, vw, gw, it, se);
 }
 
 // Whether a schedule's kernels end the step before in the next step's launch;
@@ -580,14 +597,14 @@ hipError_t launch_fields(hipStream_t st, const mbf_tuning& tun, const mbf::SimVi
     if (kn.tiles || var == MBF_VARIANT_FUSED_LDS) {
         if (var == MBF_VARIANT_FUSED_PERSISTENT && !queue) return hipErrorInvalidValue;
         switch (tun.tile_y * 2 + (lay ? 1 : 0)) {
-            case 4: launch_one_pass<T, 2, false>(st, var, vw, gw, it, ni, se, queue); break;
-            case 5: launch_one_pass<T, 2, true>(st, var, vw, gw, it, ni, se, queue); break;
-            case 8: launch_one_pass<T, 4, false>(st, var, vw, gw, it, ni, se, queue); break;
-            case 9: launch_one_pass<T, 4, true>(st, var, vw, gw, it, ni, se, queue); break;
-            case 32: launch_one_pass<T, 16, false>(st, var, vw, gw, it, ni, se, queue); break;
-            case 33: launch_one_pass<T, 16, true>(st, var, vw, gw, it, ni, se, queue); break;
-            case 16: launch_one_pass<T, 8, false>(st, var, vw, gw, it, ni, se, queue); break;
-            default: launch_one_pass<T, 8, true>(st, var, vw, gw, it, ni, se, queue); break;
+            case 4: launch_one_pass<T, 2, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            case 5: launch_one_pass<T, 2, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            case 8: launch_one_pass<T, 4, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            case 9: launch_one_pass<T, 4, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            case 32: launch_one_pass<T, 16, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            case 33: launch_one_pass<T, 16, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            case 16: launch_one_pass<T, 8, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            default: launch_one_pass<T, 8, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
         }
         return evm ? hipEventRecord(evm, st) : hipSuccess;
     }
@@ -654,9 +671,11 @@ int launch_step(mbf_handle* h, int64_t q, int64_t len, hipEvent_t ev0, hipEvent_
     mbf::SimView<T> v = view<T>(h);
     v.n_part = step_parts(h, h->tun, uses_tiles(h));
     const mbf::StepEnds se = step_ends(h->tun, q, len, 0, 1);
+    StepKernels kn = step_kernels(h);
+    kn.multi = gm.march_segs > 1;
     if (ev0) HIPCHK(h, hipEventRecord(ev0, h->stream));
     HIPCHK(h, (launch_fields<T>(h->stream, h->tun, reinterpret_cast<const mbf::SimView<T>*>(h->d_view),
-                                h->d_geom, h->d_items, gm.nblk, se, evm, h->d_queue, h->has_layer, step_kernels(h))));
+                                h->d_geom, h->d_items, gm.nblk, se, evm, h->d_queue, h->has_layer, kn)));
     if (ev1) HIPCHK(h, hipEventRecord(ev1, h->stream));
     if (h->mur_tasks > 0) {
         const int nmax = std::max({h->cfg.nx, h->cfg.ny, h->cfg.nz}) + 1;
@@ -2501,6 +2520,7 @@ int batch_tables(mbf_batch* b) {
     for (int r = 0; r < R; ++r) {
         mbf_handle* h = b->m[r];
         geoms[r] = step_geom(h, b->tun, b->kn.tiles);
+        b->kn.multi = b->kn.multi || geoms[r].march_segs > 1;
         views[r] = view<T>(h);
         views[r].n_part = step_parts(h, b->tun, b->kn.tiles);
         if (geoms[r].nblk >= (1 << 24)) return bfail(b, MBF_EINVAL, "member grid has too many work items");

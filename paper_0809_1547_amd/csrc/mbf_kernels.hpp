@@ -418,7 +418,8 @@ __device__ __forceinline__ T source_value(const SimView<T>& v, int64_t n) {
 // z segments of zseg planes, one workgroup each, on a 1-D grid of nblk.
 struct Geom {
     int tiles_x, tiles_y, segs, zseg, nblk, xcd_remap;
-    int per_seg;              // workgroups per z segment
+    int per_seg;              // workgroups per z segment (tile kernel: per march)
+    int march, march_segs;    // tile kernel: planes and segments of a work item (segs counts work items along z)
 };
 
 // Workgroups are dealt to the 8 XCDs in turn (id mod 8); with remapping, XCD
@@ -1137,8 +1138,10 @@ __device__ __forceinline__ TileNear<T> tile_near(int lane, T hx, T hy, T hz, T e
     return r;
 }
 
-// LAY: some member of the launch has an absorbing layer.
-template <typename T, int NW, bool LAY>
+// LAY: some member of the launch has an absorbing layer; MULTI: some member's
+// march is of several segments (the test for a segment's end costs 1% of a
+// small step, so others go without).
+template <typename T, int NW, bool LAY, bool MULTI>
 __device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom& gm, int w, int q) {
     constexpr uint32_t B = sizeof(T);
     const int lane = (int)threadIdx.x;
@@ -1150,7 +1153,7 @@ __device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom&
     T* const tslot = tap_slot(v, n);
     T wsum = (T)0;
     double lsum = 0.0;
-    const int kz0 = bz * gm.zseg, kz1 = min(kz0 + gm.zseg, v.nz);
+    const int kz0 = bz * gm.march, kz1 = min(kz0 + gm.march, v.nz);
     const Fields<T> f = bind_fields(v, (int)(n & 1));
     const GlobalBytes F = (GlobalBytes)(char*)v.E[0][0];
     TileOffs o;
@@ -1217,6 +1220,13 @@ __device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom&
     load_tile(D, F, o, x * B, e, tl.on);
     gi = gain_index16(gi, act && m >= kGainId, lane);
     EpsPair<T> mp = load_eps(v, m), mp_n{(T)1, (T)1};
+    const int64_t pb = (n & 1) * (int64_t)v.part_cap;
+    [[maybe_unused]] int seg_end = kz0 + gm.zseg;
+    uint32_t slot = (uint32_t)(t + gm.tiles_x * gm.tiles_y * (bz * gm.march_segs));
+    const auto put_sums = [&]() {
+        tile_sum_wave(v.e_part + pb, slot, (double)wsum);
+        if (v.box_on) tile_sum_wave(v.l_part + pb, slot, lsum);
+    };
     for (int k = kz0; k < kz1; ++k, x += (uint32_t)v.sxy, seg += pseg) {
         const bool g = act && m >= kGainId;
         const bool inx = (j >= 1 && k >= 1), iny = (i >= 1 && k >= 1), inz = (i >= 1 && j >= 1);
@@ -1315,16 +1325,22 @@ __device__ __forceinline__ void step_fused_body(const SimView<T>& v, const Geom&
         mp = mp_n;
         if (k + 1 < kz1) gi = gain_index16(s_n, act && m >= kGainId, lane);
         s_n = s_nn;
+        if constexpr (MULTI) {
+            if (k + 1 == seg_end && k + 1 < kz1) {    // a segment's sums; the march goes on
+                put_sums();
+                wsum = (T)0;
+                lsum = 0.0;
+                slot += (uint32_t)(gm.tiles_x * gm.tiles_y);
+                seg_end += gm.zseg;
+            }
+        }
     }
-    const uint32_t slot = (uint32_t)(t + gm.tiles_x * gm.tiles_y * bz);
-    const int64_t pb = (n & 1) * (int64_t)v.part_cap;
-    tile_sum_wave(v.e_part + pb, slot, (double)wsum);
-    if (v.box_on) tile_sum_wave(v.l_part + pb, slot, lsum);
+    put_sums();
 }
 
 // The tables are separate no-alias read-only arguments, so the compiler may
 // keep the member's view in scalar registers across the kernel's stores.
-template <typename T, int NW, bool LAY>
+template <typename T, int NW, bool LAY, bool MULTI>
 __global__ void __launch_bounds__(64 * NW) k_step_fused_batch(const SimView<T>* __restrict__ views,
                                                 const Geom* __restrict__ geoms,
                                                 const uint32_t* __restrict__ items, StepEnds s) {
@@ -1334,7 +1350,7 @@ __global__ void __launch_bounds__(64 * NW) k_step_fused_batch(const SimView<T>* 
     }
     int r, w;
     batch_item(items, s.ends, r, w);
-    step_fused_body<T, NW, LAY>(views[r], geoms[r], w, s.q);
+    step_fused_body<T, NW, LAY, MULTI>(views[r], geoms[r], w, s.q);
 }
 
 
@@ -1363,7 +1379,7 @@ __global__ void __launch_bounds__(64 * TY) k_step_fused_persist(const SimView<T>
         if (p >= nitems) break;
         const uint32_t e = items[p];
         const int r = (int)(e >> 24), w = (int)(e & 0xFFFFFFu);
-        step_fused_body<T, TY, LAY>(views[r], geoms[r], w, 0);
+        step_fused_body<T, TY, LAY, true>(views[r], geoms[r], w, 0);
     }
     if (lead && atomicAdd(queue + 8, 1u) == gridDim.x - 1u) {
         for (int q = 0; q < 9; ++q) atomicExch(queue + q, 0u);

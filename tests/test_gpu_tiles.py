@@ -91,3 +91,15 @@ def test_two_pass_schedule_beyond_the_cache(n, precision, one):
         sim.close()
     for a, b in zip(*res):
         assert np.array_equal(a, b)
+
+
+# marches of several segments (grids that make 1800 waves at two and four planes,
+# a last march and a last segment cut short): the sums stay the segments'
+@pytest.mark.parametrize("n,precision", [((64, 48, 80), "fp64"), ((64, 64, 63), "fp32"), ((130, 90, 37), "fp32")])
+@pytest.mark.parametrize("zseg", [1, 2, 3])
+def test_marches_keep_the_segments_sums(n, precision, zseg):
+    ref, ref_sums, _ = _run(n, "absorb", precision, "two_pass_split", 4, zseg, steps=9)
+    got, sums, one = _run(n, "absorb", precision, "two_pass", 4, zseg, steps=9)
+    assert one
+    for a, b in zip(ref + ref_sums, got + sums):
+        assert np.array_equal(a, b)
