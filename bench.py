@@ -681,7 +681,8 @@ def main():
     # around them on the batch's stream
     kern_ms, launches = batch.step_timed(min(args.steps, 64))
     alg = batch.step_bytes()
-    two_pass = tuning["variant"].startswith("two_pass")
+    # (the two-pass schedule runs one kernel where that is faster: no bytes for a second)
+    two_pass = tuning["variant"].startswith("two_pass") and alg[2] > 0.0
     # the dominant kernel: the fused step kernel, or the longer of the two passes
     q = 1 if two_pass and kern_ms[1] >= kern_ms[0] else 0
     kname = ("k_curl_e_batch" if q else "k_curl_h_batch") if two_pass else "k_step_fused_batch"
