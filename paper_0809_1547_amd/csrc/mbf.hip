@@ -63,7 +63,7 @@ struct mbf_handle {
     uint8_t* mat = nullptr;
     void* lut = nullptr;      // inv_eps[256], eps[256], mur[256], (eps, inv_eps)[256] in the field type
     mbf::Ctl* ctl = nullptr;
-    double* src_tab = nullptr;   // source values of the next steps
+    double* src_tab = nullptr;   // source values of the next steps, then the unit sums of two steps
     double* e_part = nullptr;
     double* l_part = nullptr;
     int n_part = 0;
@@ -312,6 +312,7 @@ mbf::SimView<T> view(mbf_handle* h) {
     v.realization = h->cfg.realization;
     v.src_on = h->src_on;
     v.src_tab = h->src_tab;
+    v.end_sums = h->src_tab + mbf::kSeqSteps;
     v.src_comp = h->src_comp;
     v.src_i = h->src_i; v.src_j = h->src_j; v.src_k = h->src_k;
     v.src_kind = h->src_kind;
@@ -573,10 +574,25 @@ void launch_one_pass(hipStream_t st, int variant, const mbf::SimView<T>* vw, con
 bool defers_ends(const mbf_tuning& t) {
     return t.variant != MBF_VARIANT_FUSED_PERSISTENT && t.variant != MBF_VARIANT_FUSED_LDS;
 }
-// Step q of a sequence of len steps of members [r0, r0 + m).
-mbf::StepEnds step_ends(const mbf_tuning& t, int64_t q, int64_t len, int r0, int m) {
-    if (len <= 1 || !defers_ends(t)) return {0, 0, r0, m};
-    return {(int)q, (m + 7) / 8 * 8, r0, m};
+// A step's sums by units (StepEnds) where one workgroup would outlast the
+// kernel that runs beside it: at the front of a launch from kFrontParts partials
+// a member on, counted for workgroups of 1024 threads (smaller ones take more
+// turns).  Steps in us with a loss box, variant / rows / planes, one workgroup
+// and units: 256^3 two_pass/2/1 (524288 partials) 1409 and 502, 192^3
+// two_pass_split/4/2 (55296) 207.5 and 197.6, 64^3 two_pass_split/4/1 (4096)
+// 15.1 and 13.5, 48^3 two_pass/2/2 (1728) 17.2 and 12.2.  Fewer partials stay
+// with one workgroup, since the units of many small members take room: 64 x
+// 32^3 two_pass/4 (512 each) 78.2 and 86.8 without a box.  In a launch of its own the units
+// cost one launch more (2 us), the sums of kAloneParts as much.
+constexpr int64_t kFrontParts = 4096, kAloneParts = 32768;
+// Step q of a sequence of len steps of members [r0, r0 + m), of at most `parts`
+// partials each; box: some member has a loss box.
+mbf::StepEnds step_ends(const mbf_tuning& t, int64_t q, int64_t len, int r0, int m, int parts, bool box) {
+    const bool deferred = len > 1 && defers_ends(t);
+    const bool many = deferred ? (int64_t)parts * (16 / t.tile_y) > kFrontParts : parts > kAloneParts;
+    const int units = many ? (box ? mbf::kEndUnits : mbf::kEndWaves) : 0;
+    if (!deferred) return {0, 0, r0, m, units};
+    return {(int)q, (m * (many ? units / t.tile_y : 1) + 7) / 8 * 8, r0, m, units};
 }
 // n steps as sequences of kSeqSteps: the place of step s in its sequence, and
 // that sequence's length.
@@ -670,7 +686,7 @@ int launch_step(mbf_handle* h, int64_t q, int64_t len, hipEvent_t ev0, hipEvent_
     if (rc) return rc;
     mbf::SimView<T> v = view<T>(h);
     v.n_part = step_parts(h, h->tun, uses_tiles(h));
-    const mbf::StepEnds se = step_ends(h->tun, q, len, 0, 1);
+    const mbf::StepEnds se = step_ends(h->tun, q, len, 0, 1, v.n_part, h->box_on);
     StepKernels kn = step_kernels(h);
     kn.multi = gm.march_segs > 1;
     if (ev0) HIPCHK(h, hipEventRecord(ev0, h->stream));
@@ -683,8 +699,12 @@ int launch_step(mbf_handle* h, int64_t q, int64_t len, hipEvent_t ev0, hipEvent_
         dim3 gmur((unsigned)((sites + 255) / 256), (unsigned)h->mur_tasks, 1);
         hipLaunchKernelGGL(mbf::k_mur<T>, gmur, dim3(256), 0, h->stream, v, se.q);
     }
-    if (ends_here(h->tun, q, len))
-        hipLaunchKernelGGL(mbf::k_end_step<T>, dim3(1), dim3(64, mbf::kEndThreads / 64), 0, h->stream, v, se.q);
+    if (ends_here(h->tun, q, len)) {
+        if (se.units > 0)
+            hipLaunchKernelGGL(mbf::k_end_units<T>, dim3((unsigned)se.units), dim3(64), 0, h->stream,
+                               reinterpret_cast<const mbf::SimView<T>*>(h->d_view), se.q);
+        hipLaunchKernelGGL(mbf::k_end_step<T>, dim3(1), dim3(64, mbf::kEndWaves), 0, h->stream, v, se.q, se.units > 0);
+    }
     HIPCHK(h, hipGetLastError());
     return MBF_OK;
 }
@@ -1116,7 +1136,7 @@ int mbf_create(const mbf_config* cfg, void* stream, mbf_handle** out) {
         hipMalloc(&h->mat, (size_t)h->nsite) != hipSuccess ||
         hipMalloc(&h->lut, 5 * mbf::kMaxMat * h->esz) != hipSuccess ||
         hipMalloc(&h->ctl, sizeof(mbf::Ctl)) != hipSuccess ||
-        hipMalloc(&h->src_tab, sizeof(double) * mbf::kSeqSteps) != hipSuccess)
+        hipMalloc(&h->src_tab, sizeof(double) * (mbf::kSeqSteps + 2 * mbf::kEndUnits)) != hipSuccess)
         return bail(MBF_ENOMEM, "device allocation failed");
     // enough partial-sum slots for every schedule (one per 16 x 2 tile and
     // plane), for a step and the one that ends it
@@ -2444,6 +2464,8 @@ struct mbf_batch {
     std::vector<Group> groups;
     Group all{0, 0, 0, 0, 0, 0};  // every member as one group (timed steps)
     bool any_layer = false;       // some member has an absorbing layer
+    bool any_box = false;         // some member has a loss box
+    int parts = 0;                // most partials of a member
     StepKernels kn{false, false}; // the kernels that the tables are for
     std::vector<uint64_t> seen;   // member versions the device tables describe
     bool tables = false;
@@ -2512,8 +2534,12 @@ int batch_tables(mbf_batch* b) {
     std::vector<mbf::Geom> geoms(R);
     std::vector<uint32_t> items;
     b->groups.clear();
-    b->any_layer = false;
-    for (const mbf_handle* h : b->m) b->any_layer = b->any_layer || h->has_layer;
+    b->any_layer = b->any_box = false;
+    b->parts = 0;
+    for (const mbf_handle* h : b->m) {
+        b->any_layer = b->any_layer || h->has_layer;
+        b->any_box = b->any_box || h->box_on;
+    }
     const double budget = (double)b->tun.group_mb * 1048576.0;
     b->kn = step_kernels(b);
     double gbytes = 0.0;
@@ -2523,6 +2549,7 @@ int batch_tables(mbf_batch* b) {
         b->kn.multi = b->kn.multi || geoms[r].march_segs > 1;
         views[r] = view<T>(h);
         views[r].n_part = step_parts(h, b->tun, b->kn.tiles);
+        b->parts = std::max(b->parts, views[r].n_part);
         if (geoms[r].nblk >= (1 << 24)) return bfail(b, MBF_EINVAL, "member grid has too many work items");
         // a new group when this member would overflow the budget
         const double mb = (double)snap_bytes(h);
@@ -2581,7 +2608,7 @@ int batch_launch_step(mbf_batch* b, int gi, int64_t q, int64_t len, hipEvent_t e
     const uint32_t* it = b->d_items + gr.i0;
     const int ni = gr.i1 - gr.i0;
     hipStream_t st = b->stream;
-    const mbf::StepEnds se = step_ends(b->tun, q, len, gr.r0, gr.r1 - gr.r0);
+    const mbf::StepEnds se = step_ends(b->tun, q, len, gr.r0, gr.r1 - gr.r0, b->parts, b->any_box);
     if (ev0) BHIPCHK(b, hipEventRecord(ev0, st));
     BHIPCHK(b, (launch_fields<T>(st, b->tun, vw, gw, it, ni, se, evm, b->d_queue, b->any_layer, b->kn)));
     if (ev1) BHIPCHK(b, hipEventRecord(ev1, st));
@@ -2591,8 +2618,11 @@ int batch_launch_step(mbf_batch* b, int gi, int64_t q, int64_t len, hipEvent_t e
         const dim3 gm((unsigned)((gr.mur_sites + 255) / 256), (unsigned)gr.mur_tasks, nm);
         hipLaunchKernelGGL(mbf::k_mur_batch<T>, gm, dim3(256), 0, st, views, se.q);
     }
-    if (ends_here(b->tun, q, len))
-        hipLaunchKernelGGL(mbf::k_end_step_batch<T>, dim3(nm), dim3(64, mbf::kEndThreads / 64), 0, st, views, se.q);
+    if (ends_here(b->tun, q, len)) {
+        if (se.units > 0)
+            hipLaunchKernelGGL(mbf::k_end_units<T>, dim3((unsigned)se.units, nm), dim3(64), 0, st, views, se.q);
+        hipLaunchKernelGGL(mbf::k_end_step_batch<T>, dim3(nm), dim3(64, mbf::kEndWaves), 0, st, views, se.q, se.units > 0);
+    }
     BHIPCHK(b, hipGetLastError());
     return MBF_OK;
 }

@@ -74,6 +74,7 @@ struct SimView {
     int src_on, src_kind, src_comp, src_i, src_j, src_k;
     double src_amp, src_ws, src_tp, src_t0, dt;
     double* src_tab;          // source values of steps ctl->step .. ctl->step + kSeqSteps - 1
+    double* end_sums;         // kEndUnits sums a step, two buffers by its parity (steps of many partials)
     // loss box
     int box_on, box[6];
     // first-order Mur: task q (a, side, c) packed in bits 5q..5q+4 of mur_code
@@ -459,18 +460,24 @@ __device__ __forceinline__ void batch_item(const uint32_t* __restrict__ items, i
 // ------------------------------------------------------ row a7, step end
 // A sequence of steps (the steps of a captured graph, or those queued by one
 // call) ends each step in the next one's single pass or second pass (the
-// first keeps 55 VGPRs, which the sums would raise): workgroups of their own at
-// the front of that launch, one a member, sum the partials of
-// the step before and sample the probes while the others step the fields.  Only
-// the last step of a sequence has a launch to end it, which also advances
-// ctl->step and tabulates the source for the next sequence.  (On 32^3 that launch
-// took 2.9 of a step's 9.0 us, which now takes 6.1; on 192^3 with layers 6 of
-// 209, now 198.)
+// first keeps 55 VGPRs, which the sums would raise): workgroups at the front of
+// that launch sum the partials of the step before and sample the probes while
+// the others step the fields.  Only the last step of a sequence has launches to
+// end it, which also advance ctl->step and tabulate the source for the next
+// sequence.  (On 32^3 such a launch took 2.9 of a step's 9.0 us, which now takes
+// 6.1; on 192^3 with layers 6 of 209, now 198.)
+//
+// One workgroup a member sums few partials.  Many (narrow workgroups, short
+// segments: 16 x 2 columns and one plane make a million on 320^3) would keep it
+// longer than the step lasts: 2.8 ms where the step takes 1.15.  Then each of the
+// sum's 16 waves (kEndThreads / 64) is a wave of its own, and the 16 sums that
+// they leave are added one launch later.
 constexpr int kSeqSteps = 32;   // steps of a sequence at most
 struct StepEnds {
     int q;               // steps since the sequence began
     int ends;            // workgroups at the front: a multiple of 8, so that the others keep their XCDs
     int r0, members;     // members they serve
+    int units;           // waves that sum a member's partials, one unit each (0: a workgroup sums them all)
 };
 
 // Sum of the partials in a fixed order: each of 1024 threads (TH threads take
@@ -478,6 +485,8 @@ struct StepEnds {
 // four at a time with UN loads in flight together, then a fixed tree over the
 // threads; every thread gets the sum.
 constexpr int kEndThreads = 1024;
+constexpr int kEndWaves = kEndThreads / 64;
+constexpr int kEndUnits = 2 * kEndWaves;   // the waves of the energy's sum, then of the loss's
 
 template <int TH, int UN>
 __device__ __forceinline__ double sum_partials(const double* __restrict__ p, int n, double* sh) {
@@ -508,32 +517,90 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ p, int
     }
     __syncthreads();
     double r = 0.0;
-    for (int w = 0; w < kEndThreads / 64; ++w) r += sh[w];
+    for (int w = 0; w < kEndWaves; ++w) r += sh[w];
     return r;
 }
 
-// Sums, history and probe samples of step n, whose fields and partials are
-// complete (workgroups of TH threads in rows of 64).
-template <typename T, int TH, int UN>
-__device__ __forceinline__ void finish_step(const SimView<T>& v, int64_t n) {
-    __shared__ double sh[kEndThreads / 64];
-    const int t = (int)(threadIdx.x + 64u * threadIdx.y);
-    const int64_t pb = (n & 1) * (int64_t)v.part_cap;
-    const double W = sum_partials<TH, UN>(v.e_part + pb, v.n_part, sh);
-    const double L = v.box_on ? sum_partials<TH, UN>(v.l_part + pb, v.n_part, sh) : 0.0;
+// The sum of wave `w` of the kEndThreads threads above, by one wave: lane t
+// keeps the eight accumulators of thread 64 w + t, UN rounds of loads for each
+// in flight.
+template <int UN>
+__device__ __forceinline__ double sum_unit(const double* __restrict__ p, int n, int w) {
+    const int t = 64 * w + (int)threadIdx.x;
+    double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int q = t; q < n; q += 8 * UN * kEndThreads) {
+        double v[8 * UN];
+#pragma unroll
+        for (int s = 0; s < 8 * UN; ++s) {
+            const int e = q + s * kEndThreads;
+            v[s] = e < n ? gld(p + e) : 0.0;
+        }
+#pragma unroll
+        for (int s = 0; s < 8 * UN; ++s) a[s & 7] += v[s];
+    }
+    return wave_sum(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
+}
+
+// Probe samples of step n, whose fields are complete (thread t of TH).
+template <typename T, int TH>
+__device__ __forceinline__ void sample_probes(const SimView<T>& v, int64_t n, int t) {
     const Fields<T> f = bind_fields(v, (int)(n & 1));
     for (int p = t; p < v.n_probes; p += TH) {
         const int c = v.probe_comp[p];
         const T* e = c == 0 ? f.en[0] : (c == 1 ? f.en[1] : f.en[2]);
         v.ring[(int64_t)p * v.decim + (uint32_t)n % (uint32_t)v.decim] = e[v.probe_off[p]];   // n < 2^32
     }
-    if (t == 0) {
-        if (!(W == W) || W - W != 0.0) v.ctl->nonfinite = 1;
-        if (n < v.hist_cap) v.hist[n] = W;
-        v.ctl->W_now = W;
-        v.ctl->W_int += W;
-        v.ctl->loss += L;
+}
+
+// Energy W and loss L of step n into the monitors (one thread).
+template <typename T>
+__device__ __forceinline__ void note_step(const SimView<T>& v, int64_t n, double W, double L) {
+    if (!(W == W) || W - W != 0.0) v.ctl->nonfinite = 1;
+    if (n < v.hist_cap) v.hist[n] = W;
+    v.ctl->W_now = W;
+    v.ctl->W_int += W;
+    v.ctl->loss += L;
+}
+
+// Sums, history and probe samples of step n, whose fields and partials are
+// complete (workgroups of TH threads in rows of 64).
+template <typename T, int TH, int UN>
+__device__ __forceinline__ void finish_step(const SimView<T>& v, int64_t n) {
+    __shared__ double sh[kEndWaves];
+    const int t = (int)(threadIdx.x + 64u * threadIdx.y);
+    const int64_t pb = (n & 1) * (int64_t)v.part_cap;
+    const double W = sum_partials<TH, UN>(v.e_part + pb, v.n_part, sh);
+    const double L = v.box_on ? sum_partials<TH, UN>(v.l_part + pb, v.n_part, sh) : 0.0;
+    sample_probes<T, TH>(v, n, t);
+    if (t == 0) note_step(v, n, W, L);
+}
+
+// The monitors of step n from the unit sums of an earlier launch (one thread).
+template <typename T>
+__device__ __forceinline__ void note_units(const SimView<T>& v, int64_t n) {
+    const double* const u = v.end_sums + (n & 1) * kEndUnits;
+    double W = 0.0, L = 0.0;
+    for (int w = 0; w < kEndWaves; ++w) W += gld(u + w);
+    if (v.box_on)
+        for (int w = 0; w < kEndWaves; ++w) L += gld(u + kEndWaves + w);
+    note_step(v, n, W, L);
+}
+
+// Step n by units: workgroup `blk` of the member's takes TH / 64 of them; the
+// first also samples the probes and, with `before`, notes step n - 1, whose
+// units the launch before has summed.
+template <typename T, int TH, int UN>
+__device__ __forceinline__ void end_units(const SimView<T>& v, int64_t n, int blk, bool before) {
+    const int unit = blk * (TH / 64) + (int)threadIdx.y;
+    if (unit < kEndWaves || (unit < kEndUnits && v.box_on)) {
+        const double* const p = (unit < kEndWaves ? v.e_part : v.l_part) + (n & 1) * (int64_t)v.part_cap;
+        const double y = sum_unit<UN>(p, v.n_part, unit & (kEndWaves - 1));
+        if (threadIdx.x == 0) v.end_sums[(n & 1) * kEndUnits + unit] = y;
     }
+    if (blk != 0) return;
+    const int t = (int)(threadIdx.x + 64u * threadIdx.y);
+    sample_probes<T, TH>(v, n, t);
+    if (before && t == 0) note_units(v, n - 1);
 }
 
 // Source values of the steps from n on, so that every step reads its own from
@@ -551,31 +618,46 @@ __device__ __forceinline__ void set_source(const SimView<T>& v, int64_t n, int t
 // no workgroup of this step writes.
 template <typename T, int TH>
 __device__ __forceinline__ void front_group(const SimView<T>* __restrict__ views, StepEnds s) {
-    if ((int)blockIdx.x >= s.members || s.q == 0) return;
-    const SimView<T>& v = views[s.r0 + (int)blockIdx.x];
-    finish_step<T, TH, 4>(v, gld(&v.ctl->step) + s.q - 1);
+    if (s.q == 0) return;
+    const int per = s.units == 0 ? 1 : s.units / (TH / 64);   // workgroups a member
+    const int m = (int)blockIdx.x / per;
+    if (m >= s.members) return;
+    const SimView<T>& v = views[s.r0 + m];
+    const int64_t n = gld(&v.ctl->step) + s.q - 1;
+    if (s.units == 0) finish_step<T, TH, 4>(v, n);
+    else end_units<T, TH, 1>(v, n, (int)blockIdx.x - m * per, s.q >= 2);
 }
 
-// The launch that ends a sequence: its last step is ctl->step + q.
+// The end of a sequence, whose last step is ctl->step + q: by one workgroup,
+// or (units) after a launch of k_end_units, which has summed the units.
 template <typename T>
-__device__ __forceinline__ void end_step_body(const SimView<T>& v, int q) {
+__device__ __forceinline__ void end_step_body(const SimView<T>& v, int q, bool units) {
     const int64_t n = gld(&v.ctl->step) + q;
-    finish_step<T, kEndThreads, 16>(v, n);
-    __syncthreads();                                  // every thread has read ctl->step
     const int t = (int)(threadIdx.x + 64u * threadIdx.y);
+    if (!units) finish_step<T, kEndThreads, 16>(v, n);
+    else if (t == 0) note_units(v, n);
+    __syncthreads();                                  // every thread has read ctl->step
     if (t == 0) v.ctl->step = n + 1;
     set_source(v, n + 1, t, kEndThreads);
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kEndThreads) k_end_step(SimView<T> v, int q) {
-    end_step_body(v, q);
+__global__ void __launch_bounds__(kEndThreads) k_end_step(SimView<T> v, int q, bool units) {
+    end_step_body(v, q, units);
 }
 
 // Batched: one workgroup per member.
 template <typename T>
-__global__ void __launch_bounds__(kEndThreads) k_end_step_batch(const SimView<T>* __restrict__ views, int q) {
-    end_step_body(views[blockIdx.x], q);
+__global__ void __launch_bounds__(kEndThreads) k_end_step_batch(const SimView<T>* __restrict__ views, int q, bool units) {
+    end_step_body(views[blockIdx.x], q, units);
+}
+
+// The units of a sequence's last step, one wave each (blockIdx.x), of member
+// blockIdx.y.
+template <typename T>
+__global__ void __launch_bounds__(64) k_end_units(const SimView<T>* __restrict__ views, int q) {
+    const SimView<T>& v = views[blockIdx.y];
+    end_units<T, 64, 4>(v, gld(&v.ctl->step) + q, (int)blockIdx.x, q >= 1);
 }
 
 // Energy density of cell (i, j) of the monitored plane from the cell's own
