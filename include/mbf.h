@@ -354,7 +354,7 @@ int mbf_write_field(mbf_handle* h, int field_id, const void* src, int mem_kind);
  *   MBF_VARIANT_FUSED: rows a1-a5 in one z-marching kernel in which every
  *     wave owns a tile of 16 x 4 columns and forms again the few H^{n+1/2}
  *     values of the neighbouring row, column and plane that it needs (waves
- *     exchange no field values); a workgroup is tile_y such tiles.
+ *     exchange no field values); a workgroup is tile_y such tiles (16: 8).
  *   MBF_VARIANT_FUSED_LDS: rows a1-a5 in one z-marching kernel whose waves
  *     advance plane by plane together (one barrier per plane) and hand the
  *     H^{n+1/2} of their rows to the neighbouring row's E update through

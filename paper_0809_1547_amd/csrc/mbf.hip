@@ -432,12 +432,18 @@ bool uses_tiles(const mbf_handle* h) { return step_kernels(h).tiles; }
 constexpr int kMarch = 4;
 constexpr int64_t kMarchWaves = 1800;
 
+// Waves of a workgroup of the step kernels under schedule t: a row each, or a
+// tile each.  Tiles share nothing, and sixteen waves would have to do with 128
+// registers where the FP64 tile kernel takes 210: a step of FP64 64^3 59 us at
+// sixteen and 20.2 at eight, 160^3 680 and 261 (FP32 192^3 252 and 227).
+int step_waves(const mbf_tuning& t, bool tiles) { return tiles ? std::min(t.tile_y, 8) : t.tile_y; }
+
 // Work-item geometry of a handle's grid under schedule t (a batch steps its
 // members under the batch's schedule, whatever the members' own): blocks of
-// 64 x tile_y columns, or the tile kernel's 16 x 4 tiles, tile_y a workgroup.
+// 64 x tile_y columns, or the tile kernel's 16 x 4 tiles, step_waves a workgroup.
 mbf::Geom step_geom(const mbf_handle* h, const mbf_tuning& t, bool tiles) {
     mbf::Geom g{};
-    const int ty = t.tile_y;
+    const int ty = step_waves(t, tiles);
     g.tiles_x = tiles ? (h->cfg.nx + 15) / 16 : (h->cfg.nx + 63) / 64;
     g.tiles_y = tiles ? (h->cfg.ny + 3) / 4 : (h->cfg.ny + ty - 1) / ty;
     g.zseg = step_zseg(h, t);
@@ -552,20 +558,18 @@ int persist_grid(int ni) {
     return std::max(8, std::min(per_dev[dev], need) / 8 * 8);
 }
 
-// The single-pass kernels at NW (waves per workgroup, or rows of a tile).
+// The tile kernel at NW waves a workgroup.
 template <typename T, int NW, bool LAY>
-void launch_one_pass(hipStream_t st, int variant, const mbf::SimView<T>* vw, const mbf::Geom* gw, const uint32_t* it,
-                     int ni, mbf::StepEnds se, uint32_t* queue, bool multi) {
-    const dim3 g((unsigned)ni), b(64, NW);
+void launch_tiles(hipStream_t st, int variant, const mbf::SimView<T>* vw, const mbf::Geom* gw, const uint32_t* it,
+                  int ni, mbf::StepEnds se, uint32_t* queue, bool multi) {
+    const dim3 g((unsigned)(ni + se.ends)), b(64, NW);
     if (variant == MBF_VARIANT_FUSED_PERSISTENT)
         hipLaunchKernelGGL((mbf::k_step_fused_persist<T, NW, LAY>), dim3((unsigned)persist_grid<T, NW, LAY>(ni)), b, 0,
                            st, vw, gw, it, ni, queue);
-    else if (variant == MBF_VARIANT_FUSED_LDS)
-        hipLaunchKernelGGL((mbf::k_step_lds_batch<T, NW>), g, b, 0, st, vw, gw, it);
     else if (multi)
-        hipLaunchKernelGGL((mbf::k_step_fused_batch<T, NW, LAY, true>), dim3((unsigned)(ni + se.ends)), b, 0, st, vw, gw, it, se);
+        hipLaunchKernelGGL((mbf::k_step_fused_batch<T, NW, LAY, true>), g, b, 0, st, vw, gw, it, se);
     else
-        hipLaunchKernelGGL((mbf::k_step_fused_batch<T, NW, LAY, false>), dim3((unsigned)(ni + se.ends)), b, 0, st, vw, gw, it, se);
+        hipLaunchKernelGGL((mbf::k_step_fused_batch<T, NW, LAY, false>), g, b, 0, st, vw, gw, it, se);
 }
 
 // Whether a schedule's kernels end the step before in the next step's launch;
@@ -586,13 +590,15 @@ bool defers_ends(const mbf_tuning& t) {
 // cost one launch more (2 us), the sums of kAloneParts as much.
 constexpr int64_t kFrontParts = 4096, kAloneParts = 32768;
 // Step q of a sequence of len steps of members [r0, r0 + m), of at most `parts`
-// partials each; box: some member has a loss box.
-mbf::StepEnds step_ends(const mbf_tuning& t, int64_t q, int64_t len, int r0, int m, int parts, bool box) {
+// partials each; box: some member has a loss box; tiles: the tile kernel steps.
+mbf::StepEnds step_ends(const mbf_tuning& t, int64_t q, int64_t len, int r0, int m, int parts, bool box,
+                        bool tiles) {
+    const int waves = step_waves(t, tiles);
     const bool deferred = len > 1 && defers_ends(t);
-    const bool many = deferred ? (int64_t)parts * (16 / t.tile_y) > kFrontParts : parts > kAloneParts;
+    const bool many = deferred ? (int64_t)parts * (16 / waves) > kFrontParts : parts > kAloneParts;
     const int units = many ? (box ? mbf::kEndUnits : mbf::kEndWaves) : 0;
     if (!deferred) return {0, 0, r0, m, units};
-    return {(int)q, (m * (many ? units / t.tile_y : 1) + 7) / 8 * 8, r0, m, units};
+    return {(int)q, (m * (many ? units / waves : 1) + 7) / 8 * 8, r0, m, units};
 }
 // n steps as sequences of kSeqSteps: the place of step s in its sequence, and
 // that sequence's length.
@@ -610,17 +616,25 @@ template <typename T>
 hipError_t launch_fields(hipStream_t st, const mbf_tuning& tun, const mbf::SimView<T>* vw, const mbf::Geom* gw,
                          const uint32_t* it, int ni, mbf::StepEnds se, hipEvent_t evm, uint32_t* queue, bool lay, StepKernels kn) {
     const int var = tun.variant;
-    if (kn.tiles || var == MBF_VARIANT_FUSED_LDS) {
+    if (kn.tiles) {
         if (var == MBF_VARIANT_FUSED_PERSISTENT && !queue) return hipErrorInvalidValue;
-        switch (tun.tile_y * 2 + (lay ? 1 : 0)) {
-            case 4: launch_one_pass<T, 2, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
-            case 5: launch_one_pass<T, 2, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
-            case 8: launch_one_pass<T, 4, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
-            case 9: launch_one_pass<T, 4, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
-            case 32: launch_one_pass<T, 16, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
-            case 33: launch_one_pass<T, 16, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
-            case 16: launch_one_pass<T, 8, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
-            default: launch_one_pass<T, 8, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+        switch (step_waves(tun, true) * 2 + (lay ? 1 : 0)) {
+            case 4: launch_tiles<T, 2, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            case 5: launch_tiles<T, 2, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            case 8: launch_tiles<T, 4, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            case 9: launch_tiles<T, 4, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            case 16: launch_tiles<T, 8, false>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+            default: launch_tiles<T, 8, true>(st, var, vw, gw, it, ni, se, queue, kn.multi); break;
+        }
+        return evm ? hipEventRecord(evm, st) : hipSuccess;
+    }
+    if (var == MBF_VARIANT_FUSED_LDS) {
+        const dim3 g((unsigned)ni), b(64, (unsigned)tun.tile_y);
+        switch (tun.tile_y) {
+            case 2: hipLaunchKernelGGL((mbf::k_step_lds_batch<T, 2>), g, b, 0, st, vw, gw, it); break;
+            case 4: hipLaunchKernelGGL((mbf::k_step_lds_batch<T, 4>), g, b, 0, st, vw, gw, it); break;
+            case 16: hipLaunchKernelGGL((mbf::k_step_lds_batch<T, 16>), g, b, 0, st, vw, gw, it); break;
+            default: hipLaunchKernelGGL((mbf::k_step_lds_batch<T, 8>), g, b, 0, st, vw, gw, it); break;
         }
         return evm ? hipEventRecord(evm, st) : hipSuccess;
     }
@@ -685,9 +699,9 @@ int launch_step(mbf_handle* h, int64_t q, int64_t len, hipEvent_t ev0, hipEvent_
     const int rc = self_tables<T>(h, gm);
     if (rc) return rc;
     mbf::SimView<T> v = view<T>(h);
-    v.n_part = step_parts(h, h->tun, uses_tiles(h));
-    const mbf::StepEnds se = step_ends(h->tun, q, len, 0, 1, v.n_part, h->box_on);
     StepKernels kn = step_kernels(h);
+    v.n_part = step_parts(h, h->tun, kn.tiles);
+    const mbf::StepEnds se = step_ends(h->tun, q, len, 0, 1, v.n_part, h->box_on, kn.tiles);
     kn.multi = gm.march_segs > 1;
     if (ev0) HIPCHK(h, hipEventRecord(ev0, h->stream));
     HIPCHK(h, (launch_fields<T>(h->stream, h->tun, reinterpret_cast<const mbf::SimView<T>*>(h->d_view),
@@ -2608,7 +2622,7 @@ int batch_launch_step(mbf_batch* b, int gi, int64_t q, int64_t len, hipEvent_t e
     const uint32_t* it = b->d_items + gr.i0;
     const int ni = gr.i1 - gr.i0;
     hipStream_t st = b->stream;
-    const mbf::StepEnds se = step_ends(b->tun, q, len, gr.r0, gr.r1 - gr.r0, b->parts, b->any_box);
+    const mbf::StepEnds se = step_ends(b->tun, q, len, gr.r0, gr.r1 - gr.r0, b->parts, b->any_box, b->kn.tiles);
     if (ev0) BHIPCHK(b, hipEventRecord(ev0, st));
     BHIPCHK(b, (launch_fields<T>(st, b->tun, vw, gw, it, ni, se, evm, b->d_queue, b->any_layer, b->kn)));
     if (ev1) BHIPCHK(b, hipEventRecord(ev1, st));

@@ -1,0 +1,38 @@
+"""GPU: cost of the schedules that a caller may ask for, beside their
+neighbours."""
+import time
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _step_us(sim, steps=96):
+    sim.step(steps)
+    sim.sync()
+    t = []
+    for _ in range(5):
+        t0 = time.perf_counter()
+        sim.step(steps)
+        sim.sync()
+        t.append((time.perf_counter() - t0) / steps * 1e6)
+    return min(t)
+
+
+@pytest.mark.parametrize("variant", ["two_pass", "fused", "fused_persistent"])
+def test_fp64_tiles_in_groups_of_sixteen_cost_what_eight_do(variant):
+    # sixteen waves of the FP64 tile kernel in one workgroup spilled registers:
+    # 2.6 times the time of eight
+    from paper_0809_1547_amd import mbf
+    n = 64
+    sim = mbf.Sim(n, boundary="absorb", precision="fp64", E_sp=1e-2)
+    sim.set_material(np.full((n, n, n), 2.25, dtype=np.float32), np.ones((n, n, n), dtype=np.uint8))
+    sim.set_pump(2e24)
+    t = {}
+    for tile_y in (8, 16):
+        sim.set_tuning(variant, tile_y=tile_y, zseg=2)
+        t[tile_y] = _step_us(sim)
+    sim.close()
+    print(variant, t)
+    assert t[16] <= 1.5 * t[8]
