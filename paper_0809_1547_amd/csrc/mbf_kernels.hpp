@@ -1673,8 +1673,11 @@ __device__ __forceinline__ void step_lds_body(const SimView<T>& v, const Geom& g
     if (v.box_on) tile_sums_rows<TY>(v, v.l_part + pb, bx, by, bz, lsum, sh);
 }
 
+// FP32 workgroups of up to four rows: five waves a SIMD, which leave 96 registers
+// (the compiler's own choice is one more, and four waves: 192^3 with layers 297
+// us a step against 260, 96^3 57 against 51).
 template <typename T, int TY>
-__global__ void __launch_bounds__(64 * TY) k_step_lds_batch(const SimView<T>* __restrict__ views,
+__global__ void __launch_bounds__(64 * TY, sizeof(T) == 4 && TY <= 4 ? 5 : 1) k_step_lds_batch(const SimView<T>* __restrict__ views,
                                                           const Geom* __restrict__ geoms,
                                                           const uint32_t* __restrict__ items) {
     int r, w;
