@@ -2201,18 +2201,21 @@ int mbf_pack_md(int n, const double* box, const double* diam, double* centres, c
     const unsigned b256 = (unsigned)((nn + 255) / 256);
     const unsigned bstep = (unsigned)((nn + mbf::kPackThreads / mbf::kPackLanes - 1) / (mbf::kPackThreads / mbf::kPackLanes));
     const unsigned bcell = (unsigned)((nc + 255) / 256);
-    hipLaunchKernelGGL(mbf::k_pack_load, dim3(b256), dim3(256), 0, st, dx, dd, n, P[0], cnt, 3 * gr.ncell);
+    hipLaunchKernelGGL(mbf::k_pack_load, dim3(std::max(b256, std::min(bcell, 4096u))), dim3(256), 0, st, dx, dd, n, P[0],
+                       cnt, 3 * gr.ncell);
     hipLaunchKernelGGL(mbf::k_pack_clear_flag, dim3(1), dim3(64), 0, st, flag);
     hipLaunchKernelGGL(mbf::k_pack_bin, dim3(b256), dim3(256), 0, st, P[0], n, gr, ct[0], lt[0], flag);
     HIPCHK(nullptr, hipGetLastError());
     int cur = 0, par = 0;                             // centres and lists; counts
+    bool first = true;
     for (int m = 0; m <= prm->stages; ++m) {
         const double s = prm->stages > 0 ? prm->s0 + (1.0 - prm->s0) * (double)m / (double)prm->stages : 1.0;
         const int steps = m < prm->stages ? prm->iters : prm->final_iters;
         for (int t = 0; t < steps; ++t) {
             hipLaunchKernelGGL(mbf::k_pack_step, dim3(bstep), dim3(mbf::kPackThreads), 0, st, P[cur], P[cur ^ 1], n,
-                               gr, ct[par], lt[cur], s, prm->eta, ct[(par + 1) % 3], lt[cur ^ 1], ct[(par + 2) % 3],
-                               flag);
+                               gr, ct[par], lt[cur], s, prm->eta, ct[(par + 1) % 3], lt[cur ^ 1],
+                               first ? nullptr : ct[(par + 2) % 3], flag);
+            first = false;
             cur ^= 1;
             par = (par + 1) % 3;
         }

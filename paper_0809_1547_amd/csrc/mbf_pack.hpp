@@ -21,7 +21,10 @@
 // A step is one launch: the lists of 320^3's 7200 spheres hold one or two
 // centres, so a lane orders them itself as it reads them, where a launch of its
 // own to sort them took 4.9 us of a step's 13.8; and the counts rotate through
-// three buffers, one read, one filled, one cleared for the step after.  What
+// three buffers, one read, one filled, one cleared for the step after: of the
+// cells that the centres of two steps ago lie in, whose records the step is
+// about to overwrite, however many cells the box has (8 spheres in 160^3 cells
+// took 407 us a step when every count was cleared, 3 now).  What
 // bounds a step then is the chain centre - count and list - neighbours - sum -
 // new list entry, so the counts and the first eight entries are read together
 // and their centres together (9.4 us before, 8.5 now).  Centres and diameters travel together
@@ -147,18 +150,21 @@ __device__ __forceinline__ double pack_wall(double f, double x, double r, double
 }
 
 // One step at scale s: Q_i = P_i + eta F_i, binned into (cnt_out, lst_out),
-// whose counts start at zero; clears the counts of `clear`.  Lane l < 27 of a sphere's 32 takes the
-// neighbour cell (l / 9 - 1, l / 3 % 3 - 1, l % 3 - 1) in (z, y, x).
+// whose counts start at zero.  Clears the counts of `clear`, those of the centres
+// that Q still holds (nullptr: all zero already, Q holds nothing).  Lane l < 27
+// of a sphere's 32 takes the neighbour cell (l / 9 - 1, l / 3 % 3 - 1, l % 3 - 1) in (z, y, x).
 __global__ void __launch_bounds__(kPackThreads) k_pack_step(const double4* __restrict__ P, double4* __restrict__ Q,
                                                             int n, PackGrid gr, const int* __restrict__ cnt,
                                                             const int* __restrict__ lst, double s, double eta,
                                                             int* __restrict__ cnt_out, int* __restrict__ lst_out,
                                                             int* __restrict__ clear, int* __restrict__ flag) {
-    for (int c = (int)(blockIdx.x * kPackThreads + threadIdx.x); c < gr.ncell; c += (int)(gridDim.x * kPackThreads))
-        clear[c] = 0;
     const int lane = (int)threadIdx.x & (kPackLanes - 1);
     const int i = (int)blockIdx.x * (kPackThreads / kPackLanes) + (int)threadIdx.x / kPackLanes;
     const bool act = i < n;
+    if (act && lane == 0 && clear != nullptr) {       // the lane that writes Q[i] below
+        int ox, oy, oz;
+        clear[pack_cell(gr, Q[i], ox, oy, oz)] = 0;
+    }
     double fx = 0.0, fy = 0.0, fz = 0.0;
     double4 p = make_double4(0.0, 0.0, 0.0, 0.0);
     if (act) {
