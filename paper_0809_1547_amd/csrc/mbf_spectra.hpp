@@ -77,6 +77,23 @@ __global__ void __launch_bounds__(kPowerThreads) k_spec_power(const double* __re
     if (row == 0 && k < nf) pw[k] = s;
 }
 
+// The same sums by one thread a bin, the loads of eight probes in flight.
+__global__ void __launch_bounds__(64) k_spec_power_bins(const double* __restrict__ spec, int np, int nf,
+                                                        double* __restrict__ pw) {
+    const unsigned k = blockIdx.x * 64u + threadIdx.x;
+    if (k >= (unsigned)nf) return;
+    const double2* __restrict__ f = reinterpret_cast<const double2*>(spec);
+    double s = 0.0;
+    for (int p = 0; p < np; p += 8) {
+        double2 v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = p + q < np ? f[(int64_t)(p + q) * nf + k] : make_double2(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += v[q].x * v[q].x + v[q].y * v[q].y;
+    }
+    pw[k] = s;
+}
+
 // Spectra of up to this many bins are held in LDS (statistics) or in registers
 // (peaks) from pass to pass; longer ones are read again.
 constexpr int kSpecHeld = 4096;
@@ -326,9 +343,17 @@ __global__ void __launch_bounds__(kStatThreads) k_spec_peaks(const double* __res
     if (t == 0) *count = found;
 }
 
+// A workgroup for 16 bins shortens the chain of loads of a bin; one round of
+// loads (np <= 8), or bins enough to fill the device, go to a thread each.  us by
+// workgroups and by threads: 256 x 874 4.3 and 6.5, 256 x 16384 13.0 and 16.6;
+// 1 x 256 2.6 and 2.1, 1 x 65536 9.4 and 4.8, 64 x 65536 15.1 and 11.4, 256 x
+// 32768 22.4 and 20.6.
 inline void launch_spec_power(hipStream_t st, const double* spec, int np, int nf, double* pw) {
-    hipLaunchKernelGGL(k_spec_power, dim3((unsigned)((nf - 1) / kPowerBins + 1)), dim3(kPowerThreads), 0, st,
-                       spec, np, nf, pw);
+    if (np <= 8 || nf >= 32768)
+        hipLaunchKernelGGL(k_spec_power_bins, dim3((unsigned)((nf - 1) / 64 + 1)), dim3(64), 0, st, spec, np, nf, pw);
+    else
+        hipLaunchKernelGGL(k_spec_power, dim3((unsigned)((nf - 1) / kPowerBins + 1)), dim3(kPowerThreads), 0, st,
+                           spec, np, nf, pw);
 }
 inline void launch_spec_stats(hipStream_t st, const double* pw, int nf, const double* omega, double level,
                               mbf_spec_stats* out) {
