@@ -245,7 +245,11 @@ __global__ void __launch_bounds__(kStatThreads) k_spec_stats(const double* __res
 // the candidates go to LDS and each finds its own place by counting those that
 // come before it.  Otherwise round r takes the largest candidate below the
 // previous one, a reduction over the workgroup each time (874 bins, eight peaks:
-// 18.6 us in rounds, 5.5 by counting).
+// 18.6 us in rounds, 5.5 by counting).  A round costs as much as comparing with
+// 46 + nf / 19 candidates, and there is one for each peak asked for: many
+// candidates and few peaks take rounds (874 bins, 290 candidates: 16 peaks 41 us
+// in rounds and 21 by counting, one peak 5.5 and 21), and the two largest peaks
+// are not worth collecting candidates for.
 constexpr int kPeakRanked = 512;
 
 template <bool HELD>
@@ -293,9 +297,9 @@ __global__ void __launch_bounds__(kStatThreads) k_spec_peaks(const double* __res
     const auto is_peak = [&](double v, int k) {
         return v > 0.0 && v >= thr && (k == 0 || pw[k - 1] < v) && (k == nf - 1 || v >= pw[k + 1]);
     };
-    if constexpr (HELD) {
-        __shared__ double cv[kPeakRanked];
-        __shared__ int ck[kPeakRanked], n_cand;
+    __shared__ double cv[HELD ? kPeakRanked : 1];
+    __shared__ int ck[HELD ? kPeakRanked : 1], n_cand;
+    if (HELD && max_peaks > 2) {
         if (t == 0) n_cand = 0;
         __syncthreads();
 #pragma unroll
@@ -310,12 +314,14 @@ __global__ void __launch_bounds__(kStatThreads) k_spec_peaks(const double* __res
         }
         __syncthreads();
         const int n = n_cand;
-        if (n <= kPeakRanked) {
+        if (n <= kPeakRanked &&
+            n * ((n + kStatThreads - 1) / kStatThreads) <= min(max_peaks, n + 1) * (46 + nf / 19)) {
             for (int a = t; a < n; a += kStatThreads) {
                 const double v = cv[a];
                 const int k = ck[a];
                 int place = 0;
-                for (int o = 0; o < n; ++o) place += cv[o] > v || (cv[o] == v && ck[o] < k);
+#pragma unroll 8
+                for (int o = 0; o < n; ++o) place += (int)(cv[o] > v) | ((int)(cv[o] == v) & (int)(ck[o] < k));
                 if (place < max_peaks) bins[place] = k;
             }
             if (t == 0) *count = min(n, max_peaks);

@@ -25,3 +25,13 @@ def test_power_kernels_agree_with_oracle(P, K):
     assert got["peak_bin"] == want["peak_bin"]
     for key in ("total", "peak_value", "mean_omega", "std_omega"):
         assert got[key] == pytest.approx(want[key], rel=1e-9), key
+
+
+@pytest.mark.parametrize("K", [30, 257, 874, 1500])
+@pytest.mark.parametrize("top", [1, 2, 7, 16, 200, 1024])
+def test_peaks_among_many_candidates(K, top):
+    from paper_0809_1547_amd import mbf
+    F = _noise(2, K)
+    F[:, 5] = F[:, 9] = F[:, 7] * 0.5                  # equal values
+    spec = np.stack([F.real, F.imag], -1)
+    assert list(mbf.mbf_spectral_peaks(spec, min_rel=0.0, max_peaks=top)) == list(OS.spectral_peaks(F, 0.0, top))
