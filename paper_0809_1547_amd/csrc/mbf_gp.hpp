@@ -230,11 +230,12 @@ __global__ void __launch_bounds__(64) k_gp_solve(GpArgs g) {
 constexpr int kGpSpecE = 8, kGpSpecWaves = 16;
 
 __global__ void __launch_bounds__(64 * kGpSpecWaves) k_gp_spec(const double* __restrict__ phi, double* __restrict__ spec,
-                                                              int n_E, int M, double L, int n_nu, double dnu) {
+                                                              int n_E, int M, double L, int k0, int n_nu, double dnu) {
     __shared__ double sum[kGpSpecE][64];
     const int lane = (int)(threadIdx.x & 63u);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int k = (int)blockIdx.x * 64 + lane, e0 = (int)blockIdx.y * kGpSpecE;
+    const unsigned k = (unsigned)k0 + blockIdx.x * 64u + (unsigned)lane;
+    const int e0 = (int)blockIdx.y * kGpSpecE;
     const double nu = (double)k * dnu, h = 2.0 * L / (double)(M + 1);
     const double* const row = phi + (int64_t)min(e0 + (lane >> 3), n_E - 1) * M;
     const int half = (M + 1) / 2;                     // rows with tau <= 0
@@ -263,7 +264,7 @@ __global__ void __launch_bounds__(64 * kGpSpecWaves) k_gp_spec(const double* __r
         }
         __syncthreads();
     }
-    if (w < kGpSpecE && e0 + w < n_E && k < n_nu) {
+    if (w < kGpSpecE && e0 + w < n_E && k < (unsigned)n_nu) {
         const double f = sum[w][lane] * (h / (2.0 * 3.14159265358979323846));
         spec[(int64_t)(e0 + w) * n_nu + k] = f * f;
     }
@@ -298,8 +299,13 @@ inline void gp_launch(const GpArgs& g, int n, hipStream_t st) {
     if (g.M <= 64 * 4) hipLaunchKernelGGL(k_gp_solve<4>, gs, tb, 0, st, g);
     else if (g.M <= 64 * 8) hipLaunchKernelGGL(k_gp_solve<8>, gs, tb, 0, st, g);
     else hipLaunchKernelGGL(k_gp_solve<16>, gs, tb, 0, st, g);
-    hipLaunchKernelGGL(k_gp_spec, dim3((unsigned)((g.n_nu - 1) / 64 + 1), (unsigned)((n + kGpSpecE - 1) / kGpSpecE)),
-                       dim3(64 * kGpSpecWaves), 0, st, g.phi, g.spec, n, g.M, g.L, g.n_nu, g.dnu);
+    // a launch holds fewer than 2^32 threads along x
+    constexpr int kSlice = 1 << 27;
+    for (int64_t k0 = 0; k0 < g.n_nu; k0 += kSlice) {
+        const int nk = (int)(g.n_nu - k0 < kSlice ? g.n_nu - k0 : kSlice);
+        hipLaunchKernelGGL(k_gp_spec, dim3((unsigned)((nk - 1) / 64 + 1), (unsigned)((n + kGpSpecE - 1) / kGpSpecE)),
+                           dim3(64 * kGpSpecWaves), 0, st, g.phi, g.spec, n, g.M, g.L, (int)k0, g.n_nu, g.dnu);
+    }
     hipLaunchKernelGGL(k_gp_stats, dim3((unsigned)n), dim3(kGpThreads), 0, st, g);
 }
 

@@ -6,6 +6,28 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+def test_bound_state_spectrum_of_more_frequencies_than_a_launch_holds():
+    import torch
+    from paper_0809_1547_amd import mbf
+    n_nu, dnu, M, L = (1 << 28) + 70, 1e-8, 3, 4.0
+    E = torch.tensor([9.0], dtype=torch.float64, device="cuda")
+    phi = torch.empty((1, M), dtype=torch.float64, device="cuda")
+    spec = torch.full((1, n_nu), -1.0, dtype=torch.float64, device="cuda")
+    stats = torch.empty((1, 7), dtype=torch.float64, device="cuda")
+    lib = mbf.lib
+    rc = lib.mbf_gp_solve(E.data_ptr(), 1, M, L, n_nu, dnu, mbf.MBF_MEM_DEVICE, 0, phi.data_ptr(), spec.data_ptr(),
+                          stats.data_ptr())
+    assert rc == 0
+    p = phi.cpu().numpy()[0]
+    h = 2 * L / (M + 1)
+    tau = -L + h * np.arange(1, M + 1)
+    # three terms of order one: a few ulp of the sum
+    for k in (0, 1, (1 << 27) - 1, 1 << 27, (1 << 28) - 1, 1 << 28, n_nu - 1):
+        want = (np.sum(p * np.cos(k * dnu * tau)) * h / (2 * np.pi)) ** 2
+        assert spec[0, k].item() == pytest.approx(want, rel=1e-13)
+    assert float(spec.min()) >= 0.0
+
+
 def test_power_of_more_bins_than_a_tiled_launch_holds():
     import torch
     from paper_0809_1547_amd import mbf
