@@ -403,6 +403,8 @@ struct LaunchShape {
 //    and 259, 152^3 98 and 112);
 //  - two passes split from 300 MB on: 6 x 112^3 286 whole and 265 split, 152^3
 //    (302 MB) 102 and 98, 16 x 64^3 117 and 115; 144^3 (257 MB) 86 and 89.
+// At tile_y 2 the two passes run as they are, whatever the size: the schedule
+// for a caller that wants them.
 constexpr double kCacheBytes = 250e6, kSplitBytes = 300e6, kTilePlane = 640e3, kRowFill = 0.8;
 struct StepKernels {
     bool tiles, split;
@@ -414,7 +416,7 @@ StepKernels step_kernels(const mbf_tuning& t, const LaunchShape& s) {
     if (t.tile_y >= 4 &&
         (s.fp64 || s.bytes <= kCacheBytes || (s.cells <= kRowFill * s.lanes && s.plane <= kTilePlane)))
         return {true, false};
-    return {false, s.bytes > kSplitBytes};
+    return {false, t.tile_y >= 4 && s.bytes > kSplitBytes};
 }
 StepKernels step_kernels(const mbf_handle* h) {
     LaunchShape s;
@@ -506,34 +508,25 @@ void dispatch_order(std::vector<uint32_t>& items, int i0, int i1, const std::vec
 
 // The two passes of a step at tile height ty (evm recorded between them);
 // SPLIT: the split E pass and streaming H stores.
+template <typename T, int TY, bool SPLIT>
+hipError_t launch_rows(hipStream_t st, const mbf::SimView<T>* vw, const mbf::Geom* gw, const uint32_t* it, int ni,
+                       mbf::StepEnds se, hipEvent_t evm) {
+    const dim3 g((unsigned)ni), ge((unsigned)(ni + se.ends)), b(64, TY);
+    hipLaunchKernelGGL((mbf::k_curl_h_batch<T, TY, SPLIT>), g, b, 0, st, vw, gw, it, se.q);
+    const hipError_t e = evm ? hipEventRecord(evm, st) : hipSuccess;
+    hipLaunchKernelGGL((mbf::k_curl_e_batch<T, TY, SPLIT>), ge, b, 0, st, vw, gw, it, se);
+    return e;
+}
 template <typename T, bool SPLIT>
 hipError_t launch_two_pass(hipStream_t st, int ty, const mbf::SimView<T>* vw, const mbf::Geom* gw, const uint32_t* it,
                            int ni, mbf::StepEnds se, hipEvent_t evm) {
-    const dim3 g((unsigned)ni), ge((unsigned)(ni + se.ends));
-    hipError_t e = hipSuccess;
-    switch (ty) {
-        case 2:
-            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 2, SPLIT>), g, dim3(64, 2), 0, st, vw, gw, it, se.q);
-            if (evm) e = hipEventRecord(evm, st);
-            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 2, SPLIT>), ge, dim3(64, 2), 0, st, vw, gw, it, se);
-            break;
-        case 4:
-            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 4, SPLIT>), g, dim3(64, 4), 0, st, vw, gw, it, se.q);
-            if (evm) e = hipEventRecord(evm, st);
-            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 4, SPLIT>), ge, dim3(64, 4), 0, st, vw, gw, it, se);
-            break;
-        case 16:
-            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 16, SPLIT>), g, dim3(64, 16), 0, st, vw, gw, it, se.q);
-            if (evm) e = hipEventRecord(evm, st);
-            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 16, SPLIT>), ge, dim3(64, 16), 0, st, vw, gw, it, se);
-            break;
-        default:
-            hipLaunchKernelGGL((mbf::k_curl_h_batch<T, 8, SPLIT>), g, dim3(64, 8), 0, st, vw, gw, it, se.q);
-            if (evm) e = hipEventRecord(evm, st);
-            hipLaunchKernelGGL((mbf::k_curl_e_batch<T, 8, SPLIT>), ge, dim3(64, 8), 0, st, vw, gw, it, se);
-            break;
+    // whole passes in FP64 have two rows: from four on tiles take the step
+    if constexpr (SPLIT || sizeof(T) == 4) {
+        if (ty == 4) return launch_rows<T, 4, SPLIT>(st, vw, gw, it, ni, se, evm);
+        if (ty == 8) return launch_rows<T, 8, SPLIT>(st, vw, gw, it, ni, se, evm);
+        if (ty == 16) return launch_rows<T, 16, SPLIT>(st, vw, gw, it, ni, se, evm);
     }
-    return e;
+    return ty == 2 ? launch_rows<T, 2, SPLIT>(st, vw, gw, it, ni, se, evm) : hipErrorInvalidValue;
 }
 
 // Workgroups of the persistent fused step for a work table of ni items: what
