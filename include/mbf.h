@@ -344,8 +344,8 @@ int mbf_write_field(mbf_handle* h, int field_id, const void* src, int mem_kind);
  *     256 MB last-level cache, in FP64, and in FP32 where rows of 64 would leave
  *     a fifth of their lanes empty and 48 nx ny is at most 640 KB; the passes of
  *     MBF_VARIANT_TWO_PASS_SPLIT run it from 300 MB on.  With tile_y 2 the two
- *     passes always run as they are.  The fields and monitors are the same bit
- *     for bit.
+ *     passes always run as they are, and mbf_adjoint_run takes its reverse steps
+ *     in two kernels too.  The fields and monitors are the same bit for bit.
  *   MBF_VARIANT_TWO_PASS_SPLIT: the same two passes; the second prefetches
  *     only the dense fields of the next plane and loads the Bloch state at the
  *     start of each plane, and the first writes H with streaming (non-

@@ -3109,7 +3109,8 @@ int adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int mem_ki
     // 124.9, 126.2 and 128.9 for 1, 2 and 4 planes, with the compact arrays in
     // another layout)
     const double adj_bytes = (double)esz * (12.0 * h->nsite + 15.0 * h->glen) + 2.0 * (double)slot + 8.0 * (double)ncell;
-    const bool tiles = adj_bytes <= kCacheBytes;
+    // (two passes of two rows, which always run as they are, keep the reverse step's too)
+    const bool tiles = adj_bytes <= kCacheBytes && !(h->tun.variant == MBF_VARIANT_TWO_PASS && h->tun.tile_y == 2);
     mbf::Geom gm{};
     gm.tiles_x = tiles ? (c.nx + 15) / 16 : h->nbx;
     gm.tiles_y = (c.ny + 3) / 4;

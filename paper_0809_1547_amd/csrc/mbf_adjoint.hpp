@@ -306,7 +306,9 @@ __global__ void __launch_bounds__(64 * TY) k_adj_e(const AdjView<T>* __restrict_
 // lanes beside a site asked for the others).  u and htot are double-buffered
 // like E and H of the forward, [u_a 3][u_b 3][htot_a 3][htot_b 3] in one
 // allocation and [lp 3][lq 3][ln 9] in another, and reverse step n reads
-// buffer n & 1.  The values are those of k_adj_h and k_adj_e bit for bit.
+// buffer n & 1.  u, htot, the Bloch adjoints and the eps gradient are those of
+// k_adj_h and k_adj_e bit for bit; the N_a gradient's partial sums are a tile's
+// instead of a workgroup's.
 // While the state stays in the last-level cache the step is bound by latency,
 // and one pass (all of a plane's loads in flight together, no launch between
 // the parts) shortens it: a run on 40 x 36 x 28 cells with layers took 77.5 us
