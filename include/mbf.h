@@ -393,7 +393,8 @@ int mbf_set_tuning(mbf_handle* h, const mbf_tuning* t);
 int mbf_get_tuning(const mbf_handle* h, mbf_tuning* t);
 
 /* Time candidate schedules (every variant, tile_y 2/4/8, zseg 2/4/8; the
- * default first) on the handle's own grid for about budget_ms (at least one
+ * default first; of those that come to the same kernels and marches only the
+ * first) on the handle's own grid for about budget_ms (at least one
  * candidate), keep the fastest and report it in *chosen (may be NULL).  The
  * simulation state is saved to device memory before the trials and restored
  * after them, so the run continues exactly as if autotune had not been

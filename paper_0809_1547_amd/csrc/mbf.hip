@@ -967,6 +967,21 @@ std::vector<mbf_tuning> tuning_candidates(const mbf_tuning& dflt) {
     return c;
 }
 
+// Whether two schedules step the members m the same way, with the kernels that
+// their rules pick (ka, kb): several variants come to the tile kernel or to the
+// split passes, and segments to the same march.  The autotuners time one of them.
+bool same_step(const std::vector<mbf_handle*>& m, const mbf_tuning& a, StepKernels ka, const mbf_tuning& b, StepKernels kb) {
+    const auto own = [](const mbf_tuning& t) {
+        return t.variant == MBF_VARIANT_FUSED_PERSISTENT || t.variant == MBF_VARIANT_FUSED_LDS ? t.variant : -1;
+    };
+    if (own(a) != own(b) || ka.tiles != kb.tiles || ka.split != kb.split || a.xcd_remap != b.xcd_remap ||
+        a.group_mb != b.group_mb || step_waves(a, ka.tiles) != step_waves(b, kb.tiles))
+        return false;
+    for (const mbf_handle* h : m)
+        if (step_geom(h, a, ka.tiles).march != step_geom(h, b, kb.tiles).march) return false;
+    return true;
+}
+
 uint64_t fnv1a(const uint8_t* p, size_t n, uint64_t hsh = 1469598103934665603ull) {
     for (size_t q = 0; q < n; ++q) {
         hsh ^= p[q];
@@ -1687,8 +1702,14 @@ int mbf_autotune(mbf_handle* h, int budget_ms, mbf_tuning* chosen) {
         return q;
     };
     std::vector<std::pair<double, mbf_tuning>> timed;
+    LaunchShape shape;
+    shape.add(h);
     for (const mbf_tuning& cand : tuning_candidates(solo_default_tuning(h->cfg))) {
         if (rc) break;
+        const StepKernels kc = step_kernels(cand, shape);
+        bool known = false;
+        for (const auto& q : timed) known = known || same_step({h}, q.second, step_kernels(q.second, shape), cand, kc);
+        if (known) continue;
         const double el = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         if (tried > 0 && el > budget_ms) break;
         double t = 0.0;
@@ -2511,10 +2532,10 @@ void batch_free_tables(mbf_batch* b) {
     b->tables = false;
 }
 
-// The kernels of the batch's schedule: the rule goes by the largest group of
+// The kernels of a batch under schedule t: the rule goes by the largest group of
 // members, since a group runs a whole chunk of steps before the next.
-StepKernels step_kernels(const mbf_batch* b) {
-    const double budget = (double)b->tun.group_mb * 1048576.0;
+StepKernels step_kernels(const mbf_batch* b, const mbf_tuning& t) {
+    const double budget = (double)t.group_mb * 1048576.0;
     double gbytes = 0.0;
     LaunchShape group, largest;
     for (const mbf_handle* h : b->m) {
@@ -2527,8 +2548,9 @@ StepKernels step_kernels(const mbf_batch* b) {
         group.add(h);
         if (group.bytes > largest.bytes) largest = group;
     }
-    return step_kernels(b->tun, largest);
+    return step_kernels(t, largest);
 }
+StepKernels step_kernels(const mbf_batch* b) { return step_kernels(b, b->tun); }
 
 // Rebuild the device views, geometries and work table when a member changed.
 template <typename T>
@@ -2944,9 +2966,7 @@ int mbf_batch_autotune(mbf_batch* b, int budget_ms, mbf_tuning* chosen) {
     std::vector<std::pair<double, mbf_tuning>> timed;
     auto consider = [&](const mbf_tuning& cand) {
         for (const mbf_tuning& t : tried)
-            if (t.variant == cand.variant && t.tile_y == cand.tile_y && t.zseg == cand.zseg &&
-                t.group_mb == cand.group_mb)
-                return;
+            if (same_step(b->m, t, step_kernels(b, t), cand, step_kernels(b, cand))) return;
         tried.push_back(cand);
         double ms = 0.0;
         rc = trial(cand, ms);

@@ -36,3 +36,20 @@ def test_fp64_tiles_in_groups_of_sixteen_cost_what_eight_do(variant):
     sim.close()
     print(variant, t)
     assert t[16] <= 1.5 * t[8]
+
+
+@pytest.mark.parametrize("batch", [False, True])
+def test_autotune_times_a_kernel_once(batch):
+    # on grids within the cache the two-pass schedule of four and eight rows runs
+    # the tile kernel, and the fused schedule is the same step: it was timed again
+    # and reported half of the time
+    from paper_0809_1547_amd import mbf
+    for n in ((32, 32, 32), (40, 36, 28), (48, 48, 48), (33, 21, 18), (64, 20, 30), (24, 24, 24)):
+        cfg = dict(boundary="absorb", E_sp=1e-2)
+        sim = mbf.Batch([mbf.make_config(n, realization=r, **cfg) for r in range(2)]) if batch else mbf.Sim(n, **cfg)
+        for s in sim.members if batch else (sim,):
+            s.set_material(np.full(n[::-1], 2.25, dtype=np.float32), np.ones(n[::-1], dtype=np.uint8))
+            s.set_pump(2e24)
+        t = sim.autotune(budget_ms=2000)
+        sim.close()
+        assert not (t["variant"] == "fused" and t["tile_y"] >= 4), (n, t)
