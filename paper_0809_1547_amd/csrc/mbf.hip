@@ -2222,13 +2222,14 @@ int mbf_pack_md(int n, const double* box, const double* diam, double* centres, c
     HIPCHK(nullptr, hipGetLastError());
     int cur = 0, par = 0;                             // centres and lists; counts
     bool first = true;
+    const bool all = nc <= (size_t)bstep * mbf::kPackThreads;   // a thread for every count
     for (int m = 0; m <= prm->stages; ++m) {
         const double s = prm->stages > 0 ? prm->s0 + (1.0 - prm->s0) * (double)m / (double)prm->stages : 1.0;
         const int steps = m < prm->stages ? prm->iters : prm->final_iters;
         for (int t = 0; t < steps; ++t) {
-            hipLaunchKernelGGL(mbf::k_pack_step, dim3(bstep), dim3(mbf::kPackThreads), 0, st, P[cur], P[cur ^ 1], n,
-                               gr, ct[par], lt[cur], s, prm->eta, ct[(par + 1) % 3], lt[cur ^ 1],
-                               first ? nullptr : ct[(par + 2) % 3], flag);
+            hipLaunchKernelGGL(all ? mbf::k_pack_step<true> : mbf::k_pack_step<false>, dim3(bstep), dim3(mbf::kPackThreads),
+                               0, st, P[cur], P[cur ^ 1], n, gr, ct[par], lt[cur], s, prm->eta, ct[(par + 1) % 3], lt[cur ^ 1],
+                               first && !all ? nullptr : ct[(par + 2) % 3], flag);
             first = false;
             cur ^= 1;
             par = (par + 1) % 3;

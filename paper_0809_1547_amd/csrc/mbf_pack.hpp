@@ -21,10 +21,12 @@
 // A step is one launch: the lists of 320^3's 7200 spheres hold one or two
 // centres, so a lane orders them itself as it reads them, where a launch of its
 // own to sort them took 4.9 us of a step's 13.8; and the counts rotate through
-// three buffers, one read, one filled, one cleared for the step after: of the
-// cells that the centres of two steps ago lie in, whose records the step is
-// about to overwrite, however many cells the box has (8 spheres in 160^3 cells
-// took 407 us a step when every count was cleared, 3 now).  What
+// three buffers, one read, one filled, one cleared for the step after.  Every
+// thread clears a count while there are no more of them; in a box of more cells
+// (32 a sphere) a step clears those of the centres of two steps ago, whose
+// records it is about to overwrite (8 spheres in 160^3 cells: 407 us a step when
+// every count was cleared, 3 now; 7200 in 25^3: 8.6 by threads, 8.8 by
+// centres).  What
 // bounds a step then is the chain centre - count and list - neighbours - sum -
 // new list entry, so the counts and the first eight entries are read together
 // and their centres together (9.4 us before, 8.5 now).  Centres and diameters travel together
@@ -150,9 +152,10 @@ __device__ __forceinline__ double pack_wall(double f, double x, double r, double
 }
 
 // One step at scale s: Q_i = P_i + eta F_i, binned into (cnt_out, lst_out),
-// whose counts start at zero.  Clears the counts of `clear`, those of the centres
-// that Q still holds (nullptr: all zero already, Q holds nothing).  Lane l < 27
-// of a sphere's 32 takes the neighbour cell (l / 9 - 1, l / 3 % 3 - 1, l % 3 - 1) in (z, y, x).
+// whose counts start at zero; clears the counts of `clear`.  ALL: all of them, at
+// most one a thread; else those of the centres that Q still holds (nullptr: it
+// holds none yet).  Lane l < 27 of a sphere's 32 takes the neighbour cell (l / 9 - 1, l / 3 % 3 - 1, l % 3 - 1) in (z, y, x).
+template <bool ALL>
 __global__ void __launch_bounds__(kPackThreads) k_pack_step(const double4* __restrict__ P, double4* __restrict__ Q,
                                                             int n, PackGrid gr, const int* __restrict__ cnt,
                                                             const int* __restrict__ lst, double s, double eta,
@@ -161,10 +164,14 @@ __global__ void __launch_bounds__(kPackThreads) k_pack_step(const double4* __res
     const int lane = (int)threadIdx.x & (kPackLanes - 1);
     const int i = (int)blockIdx.x * (kPackThreads / kPackLanes) + (int)threadIdx.x / kPackLanes;
     const bool act = i < n;
-    if (act && lane == 0 && clear != nullptr) {       // the lane that writes Q[i] below
-        int ox, oy, oz;
-        clear[pack_cell(gr, Q[i], ox, oy, oz)] = 0;
+    if constexpr (ALL) {
+        const int c = (int)(blockIdx.x * kPackThreads + threadIdx.x);
+        if (c < gr.ncell) clear[c] = 0;
     }
+    // else lane 1 takes the old centre from Q[i] and writes the new one there
+    [[maybe_unused]] double4 old = make_double4(0.0, 0.0, 0.0, 0.0);
+    if constexpr (!ALL)
+        if (act && lane == 1 && clear != nullptr) old = Q[i];
     double fx = 0.0, fy = 0.0, fz = 0.0;
     double4 p = make_double4(0.0, 0.0, 0.0, 0.0);
     if (act) {
@@ -217,16 +224,27 @@ __global__ void __launch_bounds__(kPackThreads) k_pack_step(const double4* __res
         fy += __shfl_xor(fy, o, kPackLanes);
         fz += __shfl_xor(fz, o, kPackLanes);
     }
-    if (!act || lane != 0) return;
+    if (!act || lane > (ALL ? 0 : 1)) return;
     const double r = s * (0.5 * p.w);
     fx = pack_wall(fx, p.x, r, gr.box[0]);
     fy = pack_wall(fy, p.y, r, gr.box[1]);
     fz = pack_wall(fz, p.z, r, gr.box[2]);
     const double4 q = make_double4(p.x + eta * fx, p.y + eta * fy, p.z + eta * fz, p.w);
-    Q[i] = q;
-    int cx, cy, cz;
-    const int c = pack_cell(gr, q, cx, cy, cz);
-    const int slot = atomicAdd(cnt_out + c, 1);
+    int cx, cy, cz, c, slot;
+    if constexpr (ALL) {
+        Q[i] = q;
+        c = pack_cell(gr, q, cx, cy, cz);
+        slot = atomicAdd(cnt_out + c, 1);
+    } else {
+        // the new centre's cell and the old one's, side by side
+        c = pack_cell(gr, lane == 0 ? q : old, cx, cy, cz);
+        if (lane == 1) {
+            Q[i] = q;
+            if (clear != nullptr) clear[c] = 0;
+            return;
+        }
+        slot = atomicAdd(cnt_out + c, 1);
+    }
     if (slot < kPackCap) lst_out[c * kPackCap + slot] = i;
     else atomicOr(flag, 1);
 }
