@@ -572,26 +572,27 @@ bool defers_ends(const mbf_tuning& t) {
     return t.variant != MBF_VARIANT_FUSED_PERSISTENT && t.variant != MBF_VARIANT_FUSED_LDS;
 }
 // A step's sums by units (StepEnds) where one workgroup would outlast the
-// kernel that runs beside it: at the front of a launch from kFrontParts partials
-// a member on, counted for workgroups of 1024 threads (smaller ones take more
-// turns).  Steps in us with a loss box, variant / rows / planes, one workgroup
-// and units: 256^3 two_pass/2/1 (524288 partials) 1409 and 502, 192^3
-// two_pass_split/4/2 (55296) 207.5 and 197.6, 64^3 two_pass_split/4/1 (4096)
-// 15.1 and 13.5, 48^3 two_pass/2/2 (1728) 17.2 and 12.2.  Fewer partials stay
-// with one workgroup, since the units of many small members take room: 64 x
-// 32^3 two_pass/4 (512 each) 78.2 and 86.8 without a box.  In a launch of its own the units
-// cost one launch more (2 us), the sums of kAloneParts as much.
-constexpr int64_t kFrontParts = 4096, kAloneParts = 32768;
+// kernel that runs beside it: from kFrontLoad partials of a member on, those of
+// the energy and of the loss, counted for workgroups of 1024 threads (smaller
+// ones take more turns).  Steps in us with a loss box, variant / rows / planes,
+// by one workgroup and by units: 256^3 two_pass/2/1 (2 x 524288 partials) 1409
+// and 502, 192^3 two_pass_split/4/2 (2 x 55296) 207.5 and 197.6, 64^3
+// two_pass_split/4/1 (2 x 4096) 15.1 and 13.5, 48^3 two_pass/2/2 (2 x 1728) 17.2
+// and 12.2; without one FP64 64 x 48 x 80 fused/4/1 (3840) 20.6 either way.  Fewer
+// stay with one workgroup, since the units of many small members take room:
+// 64 x 32^3 two_pass/4 (512 each) 78.2 and 86.8.  The launch that ends a sequence
+// sums by units, one launch (2 us) more, from kAloneParts on: steps one by one,
+// 192^3 two_pass_split/2/1 (2 x 110592) 289 and 229.
+constexpr int64_t kFrontLoad = 16384, kAloneParts = 32768;
+unsigned end_waves(bool box) { return box ? mbf::kEndUnits : mbf::kEndWaves; }
 // Step q of a sequence of len steps of members [r0, r0 + m), of at most `parts`
 // partials each; box: some member has a loss box; tiles: the tile kernel steps.
 mbf::StepEnds step_ends(const mbf_tuning& t, int64_t q, int64_t len, int r0, int m, int parts, bool box,
                         bool tiles) {
+    if (len <= 1 || !defers_ends(t)) return {0, 0, r0, m, 0};
     const int waves = step_waves(t, tiles);
-    const bool deferred = len > 1 && defers_ends(t);
-    const bool many = deferred ? (int64_t)parts * (16 / waves) > kFrontParts : parts > kAloneParts;
-    const int units = many ? (box ? mbf::kEndUnits : mbf::kEndWaves) : 0;
-    if (!deferred) return {0, 0, r0, m, units};
-    return {(int)q, (m * (many ? units / waves : 1) + 7) / 8 * 8, r0, m, units};
+    const int units = (int64_t)parts * (16 / waves) * (box ? 2 : 1) >= kFrontLoad ? (int)end_waves(box) : 0;
+    return {(int)q, (m * (units > 0 ? units / waves : 1) + 7) / 8 * 8, r0, m, units};
 }
 // n steps as sequences of kSeqSteps: the place of step s in its sequence, and
 // that sequence's length.
@@ -707,10 +708,11 @@ int launch_step(mbf_handle* h, int64_t q, int64_t len, hipEvent_t ev0, hipEvent_
         hipLaunchKernelGGL(mbf::k_mur<T>, gmur, dim3(256), 0, h->stream, v, se.q);
     }
     if (ends_here(h->tun, q, len)) {
-        if (se.units > 0)
-            hipLaunchKernelGGL(mbf::k_end_units<T>, dim3((unsigned)se.units), dim3(64), 0, h->stream,
+        const bool sum = v.n_part > kAloneParts;
+        if (sum)
+            hipLaunchKernelGGL(mbf::k_end_units<T>, dim3(end_waves(h->box_on)), dim3(64), 0, h->stream,
                                reinterpret_cast<const mbf::SimView<T>*>(h->d_view), se.q);
-        hipLaunchKernelGGL(mbf::k_end_step<T>, dim3(1), dim3(64, mbf::kEndWaves), 0, h->stream, v, se.q, se.units > 0);
+        hipLaunchKernelGGL(mbf::k_end_step<T>, dim3(1), dim3(64, mbf::kEndWaves), 0, h->stream, v, se.q, sum, sum || se.units == 0 || se.q == 0);
     }
     HIPCHK(h, hipGetLastError());
     return MBF_OK;
@@ -2652,9 +2654,11 @@ int batch_launch_step(mbf_batch* b, int gi, int64_t q, int64_t len, hipEvent_t e
         hipLaunchKernelGGL(mbf::k_mur_batch<T>, gm, dim3(256), 0, st, views, se.q);
     }
     if (ends_here(b->tun, q, len)) {
-        if (se.units > 0)
-            hipLaunchKernelGGL(mbf::k_end_units<T>, dim3((unsigned)se.units, nm), dim3(64), 0, st, views, se.q);
-        hipLaunchKernelGGL(mbf::k_end_step_batch<T>, dim3(nm), dim3(64, mbf::kEndWaves), 0, st, views, se.q, se.units > 0);
+        const bool sum = b->parts > kAloneParts;
+        if (sum)
+            hipLaunchKernelGGL(mbf::k_end_units<T>, dim3(end_waves(b->any_box), nm), dim3(64), 0, st, views, se.q);
+        hipLaunchKernelGGL(mbf::k_end_step_batch<T>, dim3(nm), dim3(64, mbf::kEndWaves), 0, st, views, se.q, sum,
+                           sum || se.units == 0 || se.q == 0);
     }
     BHIPCHK(b, hipGetLastError());
     return MBF_OK;

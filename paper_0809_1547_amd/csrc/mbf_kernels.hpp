@@ -619,22 +619,28 @@ __device__ __forceinline__ void set_source(const SimView<T>& v, int64_t n, int t
 template <typename T, int TH>
 __device__ __forceinline__ void front_group(const SimView<T>* __restrict__ views, StepEnds s) {
     if (s.q == 0) return;
-    const int per = s.units == 0 ? 1 : s.units / (TH / 64);   // workgroups a member
+    if (s.units == 0) {
+        if ((int)blockIdx.x >= s.members) return;
+        const SimView<T>& v = views[s.r0 + (int)blockIdx.x];
+        finish_step<T, TH, 4>(v, gld(&v.ctl->step) + s.q - 1);
+        return;
+    }
+    const int per = s.units / (TH / 64);              // workgroups a member
     const int m = (int)blockIdx.x / per;
     if (m >= s.members) return;
     const SimView<T>& v = views[s.r0 + m];
-    const int64_t n = gld(&v.ctl->step) + s.q - 1;
-    if (s.units == 0) finish_step<T, TH, 4>(v, n);
-    else end_units<T, TH, 1>(v, n, (int)blockIdx.x - m * per, s.q >= 2);
+    end_units<T, TH, 1>(v, gld(&v.ctl->step) + s.q - 1, (int)blockIdx.x - m * per, s.q >= 2);
 }
 
-// The end of a sequence, whose last step is ctl->step + q: by one workgroup,
-// or (units) after a launch of k_end_units, which has summed the units.
+// The end of a sequence, whose last step is ctl->step + q.  summed: a launch of
+// k_end_units has summed its units (else this workgroup sums); noted: the step
+// before is noted (else its units are still to be).
 template <typename T>
-__device__ __forceinline__ void end_step_body(const SimView<T>& v, int q, bool units) {
+__device__ __forceinline__ void end_step_body(const SimView<T>& v, int q, bool summed, bool noted) {
     const int64_t n = gld(&v.ctl->step) + q;
     const int t = (int)(threadIdx.x + 64u * threadIdx.y);
-    if (!units) finish_step<T, kEndThreads, 16>(v, n);
+    if (t == 0 && !noted) note_units(v, n - 1);
+    if (!summed) finish_step<T, kEndThreads, 16>(v, n);
     else if (t == 0) note_units(v, n);
     __syncthreads();                                  // every thread has read ctl->step
     if (t == 0) v.ctl->step = n + 1;
@@ -642,14 +648,15 @@ __device__ __forceinline__ void end_step_body(const SimView<T>& v, int q, bool u
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kEndThreads) k_end_step(SimView<T> v, int q, bool units) {
-    end_step_body(v, q, units);
+__global__ void __launch_bounds__(kEndThreads) k_end_step(SimView<T> v, int q, bool summed, bool noted) {
+    end_step_body(v, q, summed, noted);
 }
 
 // Batched: one workgroup per member.
 template <typename T>
-__global__ void __launch_bounds__(kEndThreads) k_end_step_batch(const SimView<T>* __restrict__ views, int q, bool units) {
-    end_step_body(views[blockIdx.x], q, units);
+__global__ void __launch_bounds__(kEndThreads) k_end_step_batch(const SimView<T>* __restrict__ views, int q, bool summed,
+                                                                bool noted) {
+    end_step_body(views[blockIdx.x], q, summed, noted);
 }
 
 // The units of a sequence's last step, one wave each (blockIdx.x), of member
