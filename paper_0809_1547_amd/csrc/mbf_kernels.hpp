@@ -618,18 +618,17 @@ __device__ __forceinline__ void set_source(const SimView<T>& v, int64_t n, int t
 // no workgroup of this step writes.
 template <typename T, int TH>
 __device__ __forceinline__ void front_group(const SimView<T>* __restrict__ views, StepEnds s) {
-    if (s.q == 0) return;
-    if (s.units == 0) {
-        if ((int)blockIdx.x >= s.members) return;
-        const SimView<T>& v = views[s.r0 + (int)blockIdx.x];
-        finish_step<T, TH, 4>(v, gld(&v.ctl->step) + s.q - 1);
+    if (s.units != 0) {
+        const int per = s.units / (TH / 64);          // workgroups a member
+        const int m = (int)blockIdx.x / per;
+        if (m >= s.members || s.q == 0) return;
+        const SimView<T>& v = views[s.r0 + m];
+        end_units<T, TH, 1>(v, gld(&v.ctl->step) + s.q - 1, (int)blockIdx.x - m * per, s.q >= 2);
         return;
     }
-    const int per = s.units / (TH / 64);              // workgroups a member
-    const int m = (int)blockIdx.x / per;
-    if (m >= s.members) return;
-    const SimView<T>& v = views[s.r0 + m];
-    end_units<T, TH, 1>(v, gld(&v.ctl->step) + s.q - 1, (int)blockIdx.x - m * per, s.q >= 2);
+    if ((int)blockIdx.x >= s.members || s.q == 0) return;
+    const SimView<T>& v = views[s.r0 + (int)blockIdx.x];
+    finish_step<T, TH, 4>(v, gld(&v.ctl->step) + s.q - 1);
 }
 
 // The end of a sequence, whose last step is ctl->step + q.  summed: a launch of
