@@ -337,7 +337,8 @@ int mbf_write_field(mbf_handle* h, int field_id, const void* src, int mem_kind);
  * turn): 0 launch order; 1 each XCD a contiguous range of (x tile, y tile,
  * z segment) work items; 2 (default) whole z-segment layers dealt to the XCDs
  * in turn, so neighbouring tiles share an L2 and the XCDs stream one window of
- * planes together.  tile_y must be 2, 4, 8 or 16.
+ * planes together (batches on the single-pass kernel whose layers are of four
+ * workgroups or fewer: as 1).  tile_y must be 2, 4, 8 or 16.
  *   MBF_VARIANT_TWO_PASS: a1 in one kernel, a2-a5 in a second.  With
  *     tile_y 4 and up the kernel of MBF_VARIANT_FUSED runs the step instead
  *     while the state of the launch (E, H, Bloch state, material) stays in the

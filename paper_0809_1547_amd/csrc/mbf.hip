@@ -2556,6 +2556,7 @@ StepKernels step_kernels(const mbf_batch* b, const mbf_tuning& t) {
 StepKernels step_kernels(const mbf_batch* b) { return step_kernels(b, b->tun); }
 
 // Rebuild the device views, geometries and work table when a member changed.
+constexpr int kMemberLayer = 4;   // workgroups of a layer
 template <typename T>
 int batch_tables(mbf_batch* b) {
     const int R = (int)b->m.size();
@@ -2604,9 +2605,17 @@ int batch_tables(mbf_batch* b) {
         }
     }
     // put each group's entries in dispatch order: the hardware deals workgroup
-    // q of a launch to XCD q mod 8, so entry q is the item that XCD should run
-    for (const mbf_batch::Group& gr : b->groups)
-        dispatch_order(items, gr.i0, gr.i1, geoms, b->tun.xcd_remap);
+    // q of a launch to XCD q mod 8, so entry q is the item that XCD should run.
+    // Layers of a few workgroups of tiles, dealt in turn, would spread every
+    // member over all XCDs, each reading its halo planes and layer tables again:
+    // whole members to an XCD (order 1) instead.  us a step, layers in turn and
+    // members: 160 x 32^3 with layers 282 and 236 (two passes 259), without 181
+    // and 177, 200 x 16^3 49 and 37, 100 x 32^3 in FP64 273 and 244; from nine
+    // workgroups a layer on no gain (64 x 48^3 279 both, FP64 459 and 473).
+    int widest = 0;
+    for (const mbf::Geom& g : geoms) widest = std::max(widest, g.per_seg);
+    const int order = b->tun.xcd_remap == 2 && b->kn.tiles && widest <= kMemberLayer ? 1 : b->tun.xcd_remap;
+    for (const mbf_batch::Group& gr : b->groups) dispatch_order(items, gr.i0, gr.i1, geoms, order);
     if (!b->d_queue) {
         if (hipMalloc(&b->d_queue, sizeof(uint32_t) * 9) != hipSuccess)
             return bfail(b, MBF_ENOMEM, "batch table allocation failed");
