@@ -389,20 +389,24 @@ struct LaunchShape {
 // The kernels of a launch: the tile kernel (one pass), or two passes, split
 // (TWO_PASS_SPLIT's) or not.  All give the same fields and monitors bit for
 // bit, so that the two-pass schedule (tile_y 4 and up for tiles) takes the
-// fastest; steps in us, the same segments on both sides:
+// fastest; steps in us with absorbing layers (without, where said), the same
+// segments on both sides, steps' ends included:
 //  - one pass while the state stays in the 256 MB last-level cache: FP32 32^3
-//    13.2 for two passes and 9.0, 96^3 34.6 and 26.3, 136^3 (240 MB) 72.1 and
-//    58.6; FP64 96^3 63.3 and 47.9;
-//  - one pass in FP64, whose rows of 16 fill their lines: 16 x 64^3 247 and 231,
-//    6 x 96^3 342 and 289, 152^3 (604 MB) 224 and 208;
+//    8.9 for two passes and 7.8, 96^3 32.3 and 27.8; FP64 96^3 65.7 and 51.4; it
+//    is level at 136^3 (253 MB), 83.3 and 83.8;
+//  - one pass in FP64, whose rows of 16 fill their lines: 16 x 64^3 296 and 280,
+//    6 x 96^3 416 and 345, 152^3 (604 MB) 252 for the split passes and 238;
 //  - one pass in FP32 where rows of 64 leave a fifth of their lanes empty and a
 //    plane is small enough (640 KB) that a tile finds the lines it shares with
-//    its neighbours in the XCD's L2: 160 x 32^3 179 and 163, 64 x 48^3 254 and
-//    230, 24 x 72^3 336 and 301, 10 x 96^3 269 and 260; else two passes
-//    stream faster (16 x 64^3 115 and 131, 8 x 104^3 305 and 306, 4 x 128^3 239
-//    and 259, 152^3 98 and 112);
-//  - two passes split from 300 MB on: 6 x 112^3 286 whole and 265 split, 152^3
-//    (302 MB) 102 and 98, 16 x 64^3 117 and 115; 144^3 (257 MB) 86 and 89.
+//    its neighbours in the XCD's L2: 160 x 32^3 259 and 238 (200 and 179 without
+//    layers), 64 x 48^3 307 and 277, 24 x 72^3 396 and 352, 10 x 96^3 319 and
+//    311; else two passes stream faster (16 x 64^3 144 and 164, 4 x 128^3 271
+//    and 295, 152^3 113 and 132; 8 x 104^3, whose planes are larger, is level
+//    with the split passes, 336 and 333);
+//  - two passes split from 300 MB on: 6 x 112^3 317 whole and 296 split, 152^3
+//    (302 MB) 119 and 113, 16 x 64^3 145 and 144; 144^3 (257 MB) 103.6 and 103.7.
+// The rule is the two-pass schedule's: the default of 4 Mi cells and more asks
+// for the split passes by name (default_tuning) and gets them, in FP64 too.
 // At tile_y 2 the two passes run as they are, whatever the size: the schedule
 // for a caller that wants them.
 constexpr double kCacheBytes = 250e6, kSplitBytes = 300e6, kTilePlane = 640e3, kRowFill = 0.8;
@@ -426,11 +430,16 @@ StepKernels step_kernels(const mbf_handle* h) {
 bool uses_tiles(const mbf_handle* h) { return step_kernels(h).tiles; }
 
 // The tile kernel marches over up to kMarch planes, a whole number of the
-// schedule's segments, while the grid still makes kMarchWaves waves (two a
-// SIMD): it forms the H of the plane below its march again, and the sums stay
-// the segments'.  Per step in us at 1, 2 and 4 planes: 64^3 (4096 waves at one
-// plane) 10.9, 10.3 and 12.6, FP64 24.7, 20.8 and 23.5; 48^3 with layers (1728)
-// 8.9, 10.2; 96^3 (13824) 26.4, 22.4 and 23.3, FP64 55.9, 48.9 and 47.9.
+// schedule's segments, while the grid still makes kMarchWaves waves: it forms
+// the H of the plane below its march again, and the sums stay the segments'.
+// us a step at 1, 2 and 4 planes (waves): FP32 32^3 (512, 256, 128) 6.0, 8.1 and
+// 11.9, 48^3 (1728, 864, 432) 7.3, 8.6 and 13.2, 64^3 (4096, 2048, 1024) 10.7,
+// 11.0 and 14.1, 80^3 (8000, 4000, 2000) 18.8, 15.8 and 17.9, 96^3 (13824, 6912,
+// 3456) 28.0, 24.8 and 25.5, 128^3 (32768, 16384, 8192) 54.6, 49.2 and 48.5; FP64
+// 64 x 48 x 80 (3840, 1920, 960) 21.1, 17.3 and 20.8, 64^3 21.4, 17.6 and 20.9,
+// 96^3 53.9, 48.3 and 47.6.  In FP64 the line lies between the 1920 waves that
+// are faster and the 1728 that stay at one plane; FP32 would bear one near 3000
+// (64^3 loses 3% here, 80^3 up to 13%, 96^3 3%).
 constexpr int kMarch = 4;
 constexpr int64_t kMarchWaves = 1800;
 
@@ -936,11 +945,13 @@ mbf_tuning default_tuning(int64_t cells) {
 
 // Default schedule of a single grid: as above, and below the split size the
 // longest segment (4, 2 or 1 planes) that still cuts the grid into
-// kFillItems work items or more, so that a small grid spreads over the
-// device's 256 compute units (per step: 32^3 11.3 us at 1 plane against 18.4
-// at 4, 64^3 17.4 against 22.5, 80^3 30.0 at 2 against 33.2; from 96^3 on 4
-// planes already make that many items).  A batch's members together fill
-// the device, so a batch keeps the plain default.
+// kFillItems blocks of 64 x 4 columns or more, so that a small grid spreads over
+// the device's 256 compute units.  On the tile kernel, whose marches may be of
+// several segments, us a step at 1, 2 and 4 planes: 32^3 6.1, 7.6 and 10.9, 48^3
+// 7.3, 8.2 and 12.1, 64^3 11.1, 10.5 and 12.9 (1 taken), 80^3 17.9, 17.4 and 17.0
+// (2 taken), 96^3 25.4, 25.2 and 24.8 (4 taken), 128^3 48.7, 48.3 and 47.9; FP64
+// 64^3 17.8, 17.5 and 20.5 (1 taken), 96^3 47.7, 46.8 and 46.3.  A batch's members
+// together fill the device, so a batch keeps the plain default.
 constexpr int64_t kFillItems = 1024;
 mbf_tuning solo_default_tuning(const mbf_config& c) {
     mbf_tuning t = default_tuning((int64_t)c.nx * c.ny * c.nz);
@@ -3137,11 +3148,12 @@ int adjoint_run(mbf_handle* h, int64_t nsteps, int K, void* grad_eps, int mem_ki
     // reverse steps in one pass while their state (twice E and H, the compact
     // arrays, two trajectory slots, the gradient) stays in the last-level
     // cache.  A whole run (forward, recomputation, reverse) in us a step, two
-    // kernels and one: 48^3 62.8 and 38.4, 64^3 70 and 53.6, 96^3 (130 MB) 118
-    // and 109.9, 112^3 (206 MB) 163.6 and 158.6, 128^3 (307 MB) 237.6 and 243.
-    // One plane a wave: two or four leave such grids short of waves (96^3:
-    // 124.9, 126.2 and 128.9 for 1, 2 and 4 planes, with the compact arrays in
-    // another layout)
+    // kernels and one: 48^3 37.8 and 25.5, 64^3 50.6 and 39.7, 96^3 (163 MB) 107.7
+    // and 100.9, 112^3 (239 MB) 157.9 and 155.1, 120^3 (283 MB) 189.4 and 195.0,
+    // 128^3 (372 MB) 236.2 and 242.6; FP64 goes on a little further (96^3, 298 MB,
+    // 205.8 and 192.5).  One plane a wave: 32^3 with layers 26.0, 29.2 and 36.1 for
+    // 1, 2 and 4 planes, 64^3 with layers 49.1, 46.7 and 51.4, 96^3 100.3, 102.2
+    // and 105.2.
     const double adj_bytes = (double)esz * (12.0 * h->nsite + 15.0 * h->glen) + 2.0 * (double)slot + 8.0 * (double)ncell;
     // (two passes of two rows, which always run as they are, keep the reverse step's too)
     const bool tiles = adj_bytes <= kCacheBytes && !(h->tun.variant == MBF_VARIANT_TWO_PASS && h->tun.tile_y == 2);

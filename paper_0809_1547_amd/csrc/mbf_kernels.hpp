@@ -7,10 +7,10 @@
 // another workgroup of the same launch may already have overwritten.
 //
 // The Bloch state (P^n, P^{n-1}, N1..N3 per component) exists only on gain
-// cells and is stored compactly, one value per gain cell in every component
-// array.  The cells are cut into 64-wide x segments of one row and plane,
-// numbered in memory order (bx + nbx (j + ny k)), and the gain cells in that
-// order.  A cell's number is the count of gain cells before its segment (a
+// cells and is stored compactly, one entry per gain cell in every array, its
+// three components side by side.  The cells are cut into 64-wide x segments of
+// one row and plane, numbered in memory order (bx + nbx (j + ny k)), and the
+// gain cells in that order.  A cell's number is the count of gain cells before its segment (a
 // table with one entry per segment) plus the number of gain lanes below it in
 // the wave that covers the segment (a ballot and a bit count), so the Bloch
 // loads and stores of a wave touch consecutive addresses, every cache line
