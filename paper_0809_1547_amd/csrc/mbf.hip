@@ -57,6 +57,7 @@ struct mbf_handle {
     void* arr[27] = {};       // E_a[3] E_b[3] H_a[3] H_b[3] | P_a[3] P_b[3] N1[3] N2[3] N3[3] (compact: the first entry's component, stride 3)
     int64_t ngain = 0;        // gain cells
     int64_t glen = 0;         // allocated length of each compact array
+    void* slab = nullptr;     // the tables and monitors from here on, up to l_part
     uint32_t* seg_base = nullptr;   // gain cells before each 64-wide x segment of a row
     int nbx = 0;              // segments per row
     uint32_t* seg16 = nullptr;      // the same count before each 16-wide segment
@@ -1166,29 +1167,33 @@ int mbf_create(const mbf_config* cfg, void* stream, mbf_handle** out) {
     for (int q = 0; q < 12; ++q) h->arr[q] = (char*)h->pool + (size_t)q * bytes;
     h->nbx = (c.nx + 63) / 64;
     const size_t n16 = (size_t)((c.nx + 15) / 16) * c.ny * c.nz;
-    if (hipMalloc(&h->seg_base, sizeof(uint32_t) * (size_t)h->nbx * c.ny * c.nz) != hipSuccess ||
-        hipMalloc(&h->seg16, sizeof(uint32_t) * n16) != hipSuccess ||
-        hipMalloc(&h->mat, (size_t)h->nsite) != hipSuccess ||
-        hipMalloc(&h->lut, 5 * mbf::kMaxMat * h->esz) != hipSuccess ||
-        hipMalloc(&h->ctl, sizeof(mbf::Ctl)) != hipSuccess ||
-        hipMalloc(&h->src_tab, sizeof(double) * (mbf::kSeqSteps + 2 * mbf::kEndUnits)) != hipSuccess)
-        return bail(MBF_ENOMEM, "device allocation failed");
     // enough partial-sum slots for every schedule (one per 16 x 2 tile and
     // plane), for a step and the one that ends it
     h->n_part = ((c.nx + 15) / 16) * ((c.ny + 1) / 2) * c.nz;
-    if (hipMalloc(&h->e_part, sizeof(double) * 2 * (size_t)h->n_part) != hipSuccess ||
-        hipMalloc(&h->l_part, sizeof(double) * 2 * (size_t)h->n_part) != hipSuccess)
-        return bail(MBF_ENOMEM, "device allocation failed");
+    // tables and monitors: parts of one allocation
+    const size_t psize = sizeof(double) * 2 * (size_t)h->n_part;
+    const std::pair<void**, size_t> parts[] = {
+        {(void**)&h->ctl, sizeof(mbf::Ctl)},
+        {(void**)&h->src_tab, sizeof(double) * (mbf::kSeqSteps + 2 * mbf::kEndUnits)},
+        {&h->lut, 5 * mbf::kMaxMat * h->esz},
+        {(void**)&h->seg_base, sizeof(uint32_t) * (size_t)h->nbx * c.ny * c.nz},
+        {(void**)&h->seg16, sizeof(uint32_t) * n16},
+        {(void**)&h->mat, (size_t)h->nsite},
+        {(void**)&h->e_part, psize},
+        {(void**)&h->l_part, psize}};
+    size_t slab = 0;
+    for (const auto& q : parts) slab += (q.second + 255) / 256 * 256;
+    if (hipMalloc(&h->slab, slab) != hipSuccess) return bail(MBF_ENOMEM, "device allocation failed");
+    char* at = (char*)h->slab;
+    for (const auto& q : parts) {
+        *q.first = at;
+        at += (q.second + 255) / 256 * 256;
+    }
     h->hist_cap = c.energy_history;
     if (h->hist_cap > 0 && hipMalloc(&h->hist, sizeof(double) * h->hist_cap) != hipSuccess)
         return bail(MBF_ENOMEM, "energy history allocation failed");
     if (hipMemsetAsync(h->pool, 0, bytes * 12, h->stream) != hipSuccess ||
-        hipMemsetAsync(h->seg_base, 0, sizeof(uint32_t) * (size_t)h->nbx * c.ny * c.nz, h->stream) != hipSuccess ||
-        hipMemsetAsync(h->seg16, 0, sizeof(uint32_t) * n16, h->stream) != hipSuccess ||
-        hipMemsetAsync(h->mat, 0, (size_t)h->nsite, h->stream) != hipSuccess ||
-        hipMemsetAsync(h->lut, 0, 5 * mbf::kMaxMat * h->esz, h->stream) != hipSuccess ||
-        hipMemsetAsync(h->ctl, 0, sizeof(mbf::Ctl), h->stream) != hipSuccess ||
-        hipMemsetAsync(h->l_part, 0, sizeof(double) * 2 * (size_t)h->n_part, h->stream) != hipSuccess ||
+        hipMemsetAsync(h->slab, 0, slab, h->stream) != hipSuccess ||
         hipStreamSynchronize(h->stream) != hipSuccess)
         return bail(MBF_EHIP, "device initialisation failed");
     // Mur tasks: (axis a, side, tangential component c)
@@ -1218,9 +1223,7 @@ void mbf_destroy(mbf_handle* h) {
     if (h->stream) hipStreamSynchronize(h->stream);
     drop_graph(h);
     free_probes(h);
-    hipFree(h->pool); hipFree(h->gpool); hipFree(h->seg_base); hipFree(h->seg16);
-    hipFree(h->mat); hipFree(h->lut);
-    hipFree(h->ctl); hipFree(h->src_tab); hipFree(h->e_part); hipFree(h->l_part); hipFree(h->hist); hipFree(h->lev); hipFree(h->lc);
+    hipFree(h->pool); hipFree(h->gpool); hipFree(h->slab); hipFree(h->hist); hipFree(h->lev); hipFree(h->lc);
     hipFree(h->d_view); hipFree(h->d_geom); hipFree(h->d_items); hipFree(h->d_queue); hipFree(h->map);
     if (h->own_stream && h->stream) hipStreamDestroy(h->stream);
     delete h;
@@ -1301,14 +1304,21 @@ int mbf_set_material(mbf_handle* h, const float* eps_r, const uint8_t* gain, int
     const int nb16 = (c.nx + 15) / 16;
     std::vector<uint32_t> seg((size_t)h->nbx * c.ny * c.nz), seg16((size_t)nb16 * c.ny * c.nz);
     for (int k = 0; k < c.nz; ++k)
-        for (int j = 0; j < c.ny; ++j)
-            for (int i = 0; i < c.nx; ++i) {
-                if ((i & 63) == 0) seg[(size_t)(i >> 6) + (size_t)h->nbx * (j + (size_t)c.ny * k)] = (uint32_t)ngain;
-                if ((i & 15) == 0) seg16[(size_t)(i >> 4) + (size_t)nb16 * (j + (size_t)c.ny * k)] = (uint32_t)ngain;
-                if (cell_id[(size_t)i + (size_t)c.nx * (j + (size_t)c.ny * k)] < mbf::kGainId) continue;
-                ++ngain;
-                gsites += (j >= 1 && k >= 1) + (i >= 1 && k >= 1) + (i >= 1 && j >= 1);
+        for (int j = 0; j < c.ny; ++j) {
+            const size_t row = j + (size_t)c.ny * k;
+            const uint8_t* id = cell_id.data() + (size_t)c.nx * row;
+            const int64_t before = ngain;
+            for (int q = 0; q < nb16; ++q) {
+                if ((q & 3) == 0) seg[(size_t)(q >> 2) + (size_t)h->nbx * row] = (uint32_t)ngain;
+                seg16[(size_t)q + (size_t)nb16 * row] = (uint32_t)ngain;
+                int n = 0;
+                for (int i = 16 * q; i < std::min(16 * q + 16, c.nx); ++i) n += id[i] >= mbf::kGainId;
+                ngain += n;
             }
+            // interior sites: Ex off the walls in y and z, Ey in x and z, Ez in x and y
+            const int64_t in_row = ngain - before, off_x = in_row - (id[0] >= mbf::kGainId);
+            gsites += (j >= 1 && k >= 1 ? in_row : 0) + (k >= 1 ? off_x : 0) + (j >= 1 ? off_x : 0);
+        }
     const double Sx = kC0 * h->co.dt / c.dx;
     std::vector<double> inv(mbf::kMaxMat, 1.0), ep(mbf::kMaxMat, 1.0), mur(mbf::kMaxMat, 0.0);
     for (int q = 0; q < mbf::kMaxMat; ++q) {
